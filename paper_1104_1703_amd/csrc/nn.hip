@@ -15,6 +15,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <type_traits>
+
 #include "mg.h"
 #include "mg_core.h"
 #include "nn_core.h"
@@ -240,110 +243,213 @@ __global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina,
 
 // -------------------------------------------------------------- conv bwd W
 // dW[tap][co][ci] += sum_v dout[v][co] * X[v shifted by tap][ci] (X the
-// possibly concatenated, possibly upsampled input), dbias[co] += sum_v dout.
-// GEMM per tap: M = co, N = ci, K = voxels.  A block takes one tap, 64
-// output channels (one 16-channel tile per wave) and a chunk of voxels; 32
-// voxels at a time are staged in LDS (dout rows and shifted input rows,
-// contiguous loads), then read back transposed as MFMA fragments.  Partial
-// sums go to global FP32 with atomics.
-constexpr int BW_KV = 32;
+// possibly concatenated, possibly upsampled input), dbias[co] += sum_v dout:
+// per tap a GEMM with M = co, N = ci, K = voxels.
+//
+// A block owns one 16 x 16 channel tile for all 27 taps and marches up z over
+// a 16 x 16 column of voxels, two rows a wave.  Each plane of X (1-cell xy
+// halo) and of dout is staged once in LDS, channels-last as it comes, with the
+// global loads of the next two planes in flight.  The matrix operands need
+// eight voxels of one channel per lane: LDS transpose reads
+// (ds_read_b64_tr_b16) deliver four voxels of a row each, so one half-fragment
+// covers the 16 voxels of a row (lane group g: voxels 4g .. 4g + 3) and a K
+// step of 32 is the row pair (y, y + 1) of the wave.  A tap's x shift is an
+// address, its y shift picks neighbouring half-fragments (row y + 1 of dy is
+// row y of dy + 1), and its z shift one of the dout fragments of the last three
+// planes, kept in registers: 12 transpose reads of X and two of dout feed 27
+// matrix products.  The waves' sums meet in LDS and go to global FP32 with one
+// atomic per weight and block; one address takes about 50 ns per atomic, so
+// the sums of single waves (8 times as many) took most of a launch.
+//
+// Against the earlier kernel, which re-staged its input for every tap and
+// transposed it element by element (8 x 64^3 voxels unless stated): 16 -> 16
+// channels 1190 -> 46 us (134 MB read: 2.9 TB/s; 34 us of it the march, the
+// rest the sums), 48 -> 16 2360 -> 114 us, 96 -> 32 on 8 x 32^3 600 -> 72 us
+// (650 TFLOP/s), 64 -> 64 on 8 x 16^3 50 -> 18 us.  The fine resolutions are
+// bound by the bytes staged, the coarse ones by the march's latency and the
+// sums at the end.
+constexpr int BW_T = 16;                 // voxels of a row, and rows of the column
+constexpr int BW_H = BW_T + 2;           // ... with halo
+constexpr int BW_NT = 512;
+constexpr int BW_G = 4;                  // taps reduced at a time (28 with the bias)
+constexpr int BW_XN = 2 * BW_H * BW_H;   // 16-byte pieces (8 channels of a voxel) of an X plane
+constexpr int BW_DN = 2 * BW_T * BW_T;   // ... of a dout plane: one per thread
+static_assert(BW_NT == BW_DN && BW_XN <= 2 * BW_NT, "two X pieces and one dout piece per thread");
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-template <int NCI>  // input-channel tiles of 16 (cin = 16 * NCI)
-__global__ __launch_bounds__(NTH) void k_conv_bwd_w(const bf16 *__restrict__ dout, int cout,
-                                                     const bf16 *__restrict__ ina, int ca, int upa,
-                                                     const bf16 *__restrict__ inb, int cb, float *__restrict__ dw,
-                                                     float *__restrict__ dbias, int D, int H, int W, long long V,
-                                                     int chunk) {
-    __shared__ bf16 sd[BW_KV][64 + 8];       // dout rows (64 channels of this block), padded
-    __shared__ bf16 sx[BW_KV][16 * NCI + 8]; // shifted input rows
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// Half-fragment of 16 consecutive voxels x 16 channels at p (LDS, 32 bytes a
+// voxel): lane (g, i) receives channel i of voxels 4g .. 4g + 3.
+__device__ __forceinline__ bf16x4 read_tr(const bf16 *p, int lane_off) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+        (__attribute__((address_space(3))) bf16x4 *)(const_cast<bf16 *>(p) + lane_off));
+}
+
+__device__ __forceinline__ bf16x8 join(const bf16x4 &a, const bf16x4 &b) {
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+struct BwLds {
+    union {
+        struct {
+            bf16 x[2][BW_XN * 8];
+            bf16 d[2][BW_DN * 8];
+        };
+        float red[BW_NT / 64][BW_G * 256];
+    };
+};
+
+// EDGE: the column may leave the box (W or H no multiple of 16; the masking costs a tenth)
+template <bool EDGE>
+__global__ __launch_bounds__(BW_NT, 2) void k_conv_bwd_w(const bf16 *__restrict__ dout, int cout,
+                                                         const bf16 *__restrict__ ina, int ca, int upa,
+                                                         const bf16 *__restrict__ inb, int cb, float *__restrict__ dw,
+                                                         float *__restrict__ dbias, int D, int H, int W, int ntx,
+                                                         int nty, int nzc, int zc) {
+    __shared__ __attribute__((aligned(16))) BwLds lds;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int row = lane & 15, grp = lane >> 4;
-    const int tap = blockIdx.x;  // the 27 taps of one voxel chunk run side by side and share L2
-    const int co_blk = blockIdx.z * 64;
-    const int cin = 16 * NCI;
-    const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
+    int b = blockIdx.x;
+    const int tx = b % ntx;
+    b /= ntx;
+    const int ty = b % nty;
+    b /= nty;
+    const int zk = b % nzc, n = b / nzc;
+    const int x0 = tx * BW_T, y0 = ty * BW_T, z0 = zk * zc, z1 = min(D, z0 + zc);
+    const int cin = ca + cb, nci = cin >> 4;
+    const int ci0 = ((int)blockIdx.y % nci) * 16, co0 = ((int)blockIdx.y / nci) * 16;
     const int Dc = D >> 1, Hc = H >> 1, Wc = W >> 1;
-    const long long v0 = (long long)blockIdx.y * chunk;
-    const long long v1 = v0 + chunk < V ? v0 + chunk : V;
-    f32x4 acc[NCI];
+
+    // staging: a piece's place in its plane is fixed, only z moves.  Offsets in
+    // a z plane of the piece's source (in pieces, -1: outside the box, read as
+    // zero); the 8 channels of a piece come all from a or all from b (8 | ca)
+    const bool fromb = ci0 + (tid & 1) * 8 >= ca;
+    int xoff[2];
 #pragma unroll
-    for (int t = 0; t < NCI; t++) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bsum = 0.f;
-    const bool wave_ok = co_blk + wave * 16 < cout;
-    for (long long vb = v0; vb < v1; vb += BW_KV) {
-        __syncthreads();
-        // stage dout[vb .. vb+32)[co_blk .. co_blk+64) : 32 x 64 bf16, 8 per thread
-        {
-            const int e = threadIdx.x * 8;          // 256 threads x 8 = 2048 = 32 x 64
-            const int vr = e / 64, c = e % 64;
-            const long long v = vb + vr;
-            bf16x8 val = zero8();
-            if (v < v1 && co_blk + c < cout) val = *(const bf16x8 *)(dout + v * cout + co_blk + c);
-#pragma unroll
-            for (int j = 0; j < 8; j++) sd[vr][c + j] = val[j];
-        }
-        // stage X[v + tap shift][0 .. cin) : 32 x cin bf16, 8 per thread per pass
-        for (int e = threadIdx.x * 8; e < BW_KV * cin; e += NTH * 8) {
-            const int vr = e / cin, c = e % cin;
-            const long long v = vb + vr;
-            bf16x8 val = zero8();
-            if (v < v1) {
-                long long t = v;
-                const int x = (int)(t % W) + dx;
-                t /= W;
-                const int y = (int)(t % H) + dy;
-                t /= H;
-                const int z = (int)(t % D) + dz;
-                const int n = (int)(t / D);
-                if (z >= 0 && z < D && y >= 0 && y < H && x >= 0 && x < W) {
-                    if (c < ca) {
-                        size_t vox;
-                        if (upa) vox = (((size_t)n * Dc + (z >> 1)) * Hc + (y >> 1)) * Wc + (x >> 1);
-                        else vox = (((size_t)n * D + z) * H + y) * W + x;
-                        val = *(const bf16x8 *)(ina + vox * ca + c);
-                    } else {
-                        const size_t vox = (((size_t)n * D + z) * H + y) * W + x;
-                        val = *(const bf16x8 *)(inb + vox * cb + (c - ca));
-                    }
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < 8; j++) sx[vr][c + j] = val[j];
-        }
-        __syncthreads();
-        if (wave_ok) {
-            // A[m = co][k = voxel]: lane takes co = row, voxels 8*grp .. 8*grp+7
-            bf16x8 afr;
-#pragma unroll
-            for (int j = 0; j < 8; j++) afr[j] = sd[grp * 8 + j][wave * 16 + row];
-            if (tap == 13 && dbias) {
-#pragma unroll
-                for (int j = 0; j < 8; j++) bsum += (float)afr[j];
-            }
-#pragma unroll
-            for (int t = 0; t < NCI; t++) {
-                bf16x8 bfr;  // B[k = voxel][n = ci]
-#pragma unroll
-                for (int j = 0; j < 8; j++) bfr[j] = sx[grp * 8 + j][t * 16 + row];
-                acc[t] = mfma(afr, bfr, acc[t]);
-            }
-        }
+    for (int q = 0; q < 2; q++) {
+        const int p = tid + q * BW_NT;
+        const int vx = (p >> 1) % BW_H, vy = (p >> 1) / BW_H;
+        const int gx = x0 - 1 + vx, gy = y0 - 1 + vy, c = ci0 + (p & 1) * 8;
+        xoff[q] = -1;
+        if (p < BW_XN && (unsigned)gx < (unsigned)W && (unsigned)gy < (unsigned)H)
+            xoff[q] = fromb ? (gy * W + gx) * (cb >> 3) + ((c - ca) >> 3)
+                    : upa   ? ((gy >> 1) * Wc + (gx >> 1)) * (ca >> 3) + (c >> 3)
+                            : (gy * W + gx) * (ca >> 3) + (c >> 3);
     }
-    if (!wave_ok) return;
-    // D[m = co][n = ci]: lane holds co = 4*grp + r, ci = row
+    const int dx_ = x0 + (tid >> 1) % BW_T, dy_ = y0 + (tid >> 1) / BW_T;
+    const int doff = dx_ < W && dy_ < H ? (dy_ * W + dx_) * (cout >> 3) + (co0 >> 3) + (tid & 1) : -1;
+    const int xsh = !fromb && upa ? 1 : 0;
+    const size_t xplane = fromb ? (size_t)H * W * cb : upa ? (size_t)Hc * Wc * ca : (size_t)H * W * ca;
+    const bf16 *xbase = (fromb ? inb : ina) + (size_t)n * (xsh ? Dc : D) * xplane;
+    const size_t dplane = (size_t)H * W * cout;
+    const bf16 *dbase = dout + (size_t)n * D * dplane;
+    struct Regs {
+        bf16x8 x[2], d;
+    };
+    // X plane z and dout plane z + 1: every lane loads (pieces outside the box
+    // from a clamped place) and keeps zero instead where it is outside, so the
+    // loads of two steps stay in flight under exact wait counts
+    auto fetch = [&](Regs &r, int z) {
+        const bf16x8 *px = (const bf16x8 *)(xbase + (size_t)(min(max(z, 0), D - 1) >> xsh) * xplane);
+        const bf16x8 *pd = (const bf16x8 *)(dbase + (size_t)min(z + 1, D - 1) * dplane);
 #pragma unroll
-    for (int t = 0; t < NCI; t++)
+        for (int q = 0; q < 2; q++) r.x[q] = px[max(xoff[q], 0)];
+        r.d = pd[max(doff, 0)];
+    };
+    // the registers of X plane z -> LDS
+    auto commit = [&](const Regs &r, int z, int buf) {
+        const bool zin = z >= 0 && z < D, din = z + 1 < z1;  // uniform (z + 1 >= z0 always)
+        *(bf16x8 *)(lds.x[buf] + tid * 8) = zin && xoff[0] >= 0 ? r.x[0] : zero8();
+        if (tid + BW_NT < BW_XN) *(bf16x8 *)(lds.x[buf] + (tid + BW_NT) * 8) = zin && xoff[1] >= 0 ? r.x[1] : zero8();
+        *(bf16x8 *)(lds.d[buf] + tid * 8) = din && doff >= 0 ? r.d : zero8();
+    };
+    f32x4 acc[27], accb = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const int co = co_blk + wave * 16 + grp * 4 + r;
-            const int ci = t * 16 + row;
-            if (co < cout) atomicAdd(&dw[((size_t)tap * cout + co) * cin + ci], acc[t][r]);
+    for (int t = 0; t < 27; t++) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 ones;
+#pragma unroll
+    for (int j = 0; j < 8; j++) ones[j] = (bf16)1.0f;
+    const bool bias = dbias && ci0 == 0;  // uniform
+    // this lane's element of a half-fragment: voxel 4 grp + row / 4, channels 4 (row mod 4) ..
+    const int loff = (grp * 4 + (row >> 2)) * 16 + (row & 3) * 4;
+    // an X value takes part only where the dout voxel of its slot is in the box
+    // (the zero staged there would turn an infinity into a NaN): 16 bits a
+    // voxel, applied with EDGE
+    u32x4 keep;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const int x = x0 + grp * 4 + (j & 1) * 2, y = y0 + 2 * wave + (j >> 1);
+        keep[j] = y < H ? (x < W ? 0xffffu : 0u) | (x + 1 < W ? 0xffff0000u : 0u) : 0u;
+    }
+    bf16x8 a[3];  // dout fragments of planes z - 1, z, z + 1 (slot: plane - z0 + 3 mod 3)
+    a[0] = a[1] = a[2] = zero8();
+    // step st: X plane z = z0 - 1 + st against dout planes z + 1 (dz = -1), z, z - 1,
+    // those of the chunk
+    const int nz = z1 - z0, nst = nz + 2;
+    auto step = [&](int st, Regs &r, auto P) {
+        constexpr int p = decltype(P)::value;  // st mod 3: slot of dout plane z + 1
+        const int buf = st & 1;
+        commit(r, z0 - 1 + st, buf);
+        fetch(r, z0 + st + 1);  // (the last two go unused)
+        __syncthreads();
+        const bf16 *xp = lds.x[buf] + (2 * wave) * (BW_H * 16);
+        const bf16 *dp = lds.d[buf] + (2 * wave) * (BW_T * 16);
+        a[p] = join(read_tr(dp, loff), read_tr(dp + BW_T * 16, loff));
+        if (bias) accb = mfma(a[p], ones, accb);
+        bf16x4 h[4][3];  // [row y - 1 .. y + 2][dx]
+#pragma unroll
+        for (int r4 = 0; r4 < 4; r4++)
+#pragma unroll
+            for (int dx = 0; dx < 3; dx++) h[r4][dx] = read_tr(xp + (r4 * BW_H + dx) * 16, loff);
+        bf16x8 x[9];
+#pragma unroll
+        for (int t = 0; t < 9; t++) {
+            x[t] = join(h[t / 3][t % 3], h[t / 3 + 1][t % 3]);
+            if constexpr (EDGE) x[t] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, x[t]) & keep);
         }
-    if (tap == 13 && dbias) {
-        // lanes with the same row hold partial sums of channel co = row over different voxel groups
-        bsum += __shfl_xor(bsum, 16);
-        bsum += __shfl_xor(bsum, 32);
-        if (grp == 0) atomicAdd(&dbias[co_blk + wave * 16 + row], bsum);
+#pragma unroll
+        for (int dz = 0; dz < 3; dz++)
+            if (st >= dz && st < dz + nz)  // uniform
+#pragma unroll
+                for (int t = 0; t < 9; t++) acc[dz * 9 + t] = mfma(a[(p + 3 - dz) % 3], x[t], acc[dz * 9 + t]);
+    };
+    Regs r0, r1;
+    fetch(r0, z0 - 1);
+    fetch(r1, z0);
+#define BW_STEP(k, r, p) \
+    if (st + k < nst) step(st + k, r, std::integral_constant<int, p>())
+    for (int st = 0; st < nst; st += 6) {
+        BW_STEP(0, r0, 0);
+        BW_STEP(1, r1, 1);
+        BW_STEP(2, r0, 2);
+        BW_STEP(3, r1, 0);
+        BW_STEP(4, r0, 1);
+        BW_STEP(5, r1, 2);
+    }
+#undef BW_STEP
+    // D[m = co][n = ci]: lane holds co = 4 grp + r, ci = row of the tile.  The
+    // eight waves' sums of BW_G taps at a time meet in LDS (plain stores and
+    // ordered sums: LDS float atomics took 60 us of a 100 us launch); the bias
+    // sums (every column of the ones product holds them) go with the last taps
+    constexpr int G = BW_G;
+#pragma unroll
+    for (int t0 = 0; t0 < 28; t0 += G) {
+        __syncthreads();  // the last plane, or the group before, has been read
+#pragma unroll
+        for (int g = 0; g < G; g++)
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+                lds.red[wave][g * 256 + (grp * 4 + r) * 16 + row] = t0 + g < 27 ? acc[t0 + g][r] : accb[r];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < G * 256 / BW_NT; k++) {
+            const int e = tid + k * BW_NT, t = t0 + (e >> 8), co = (e >> 4) & 15, ci = e & 15;
+            float v = lds.red[0][e];
+#pragma unroll
+            for (int w = 1; w < BW_NT / 64; w++) v += lds.red[w][e];
+            if (t < 27) atomicAdd(&dw[((size_t)t * cout + co0 + co) * cin + ci0 + ci], v);
+            else if (bias && ci == 0) atomicAdd(&dbias[co0 + co], v);
+        }
     }
 }
 
@@ -722,18 +828,30 @@ inline unsigned blocks_for(long long n, int per = 256) {
     return (unsigned)(g > 0 ? g : 1);
 }
 
-template <int NCI>
 void launch_bww(const bf16 *dout, int cout, const bf16 *ina, int ca, int upa, const bf16 *inb, int cb, float *dw,
-                float *db, int D, int H, int W, long long V, hipStream_t s) {
-    // voxel chunk per block: about 2048 blocks over the 27 taps x channel groups
-    const int groups = (cout + 63) / 64;
-    long long nchunks = 2048 / (27 * groups);
-    if (nchunks < 1) nchunks = 1;
-    long long chunk = (V + nchunks - 1) / nchunks;
-    chunk = ((chunk + BW_KV - 1) / BW_KV) * BW_KV;
-    if (chunk < BW_KV) chunk = BW_KV;
-    dim3 grid(27, (unsigned)((V + chunk - 1) / chunk), (unsigned)groups);
-    k_conv_bwd_w<NCI><<<grid, NTH, 0, s>>>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, V, (int)chunk);
+                float *db, int n, int D, int H, int W, hipStream_t s) {
+    const int ntx = (W + BW_T - 1) / BW_T, nty = (H + BW_T - 1) / BW_T;
+    const long long tiles = (long long)(ca + cb) / 16 * (cout / 16), cols = (long long)ntx * nty * n * tiles;
+    // z chunks: the split with the shortest march over the rounds it takes (one
+    // block per CU at once, two planes more staged than multiplied, and about
+    // six steps' worth of reduction at the end of a block)
+    int nzc = 1;
+    long long best = 0;
+    for (int k = 1; k <= D; k++) {
+        const int zc = (D + k - 1) / k;
+        const long long t = (cols * ((D + zc - 1) / zc) + 255) / 256 * (zc + 8);
+        if (k == 1 || t < best) {
+            best = t;
+            nzc = k;
+        }
+    }
+    const int zc = (D + nzc - 1) / nzc;
+    nzc = (D + zc - 1) / zc;
+    dim3 grid((unsigned)((long long)ntx * nty * nzc * n), (unsigned)tiles);
+    if (W % BW_T || H % BW_T)
+        k_conv_bwd_w<true><<<grid, BW_NT, 0, s>>>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, ntx, nty, nzc, zc);
+    else
+        k_conv_bwd_w<false><<<grid, BW_NT, 0, s>>>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, ntx, nty, nzc, zc);
 }
 
 // ------------------------------------------------ host launchers (nn_core.h)
@@ -791,20 +909,12 @@ bool conv_bwd_weight(const void *dout, int cout, const void *in_a, int ca, int u
         set_error("conv3d weight gradient: invalid arguments (input channels a multiple of 16, output of 16)");
         return false;
     }
-    const long long V = (long long)n * d * h * wd;
     const bf16 *G = (const bf16 *)dout, *A = (const bf16 *)in_a, *B = (const bf16 *)in_b;
-    switch (cin / 16) {
-        case 1: launch_bww<1>(G, cout, A, ca, up_a, B, cb, dw, dbias, d, h, wd, V, s); break;
-        case 2: launch_bww<2>(G, cout, A, ca, up_a, B, cb, dw, dbias, d, h, wd, V, s); break;
-        case 3: launch_bww<3>(G, cout, A, ca, up_a, B, cb, dw, dbias, d, h, wd, V, s); break;
-        case 4: launch_bww<4>(G, cout, A, ca, up_a, B, cb, dw, dbias, d, h, wd, V, s); break;
-        case 6: launch_bww<6>(G, cout, A, ca, up_a, B, cb, dw, dbias, d, h, wd, V, s); break;
-        case 8: launch_bww<8>(G, cout, A, ca, up_a, B, cb, dw, dbias, d, h, wd, V, s); break;
-        case 12: launch_bww<12>(G, cout, A, ca, up_a, B, cb, dw, dbias, d, h, wd, V, s); break;
-        default:
-            set_error("conv3d weight gradient: input channels must be 16, 32, 48, 64, 96, 128 or 192");
-            return false;
+    if (cin != 16 && cin != 32 && cin != 48 && cin != 64 && cin != 96 && cin != 128 && cin != 192) {
+        set_error("conv3d weight gradient: input channels must be 16, 32, 48, 64, 96, 128 or 192");
+        return false;
     }
+    launch_bww(G, cout, A, ca, up_a, B, cb, dw, dbias, n, d, h, wd, s);
     return hip_ok(hipGetLastError(), "conv3d weight gradient launch");
 }
 
