@@ -78,7 +78,10 @@ typedef struct {
                                  (cached in the file named by MG_TUNE_CACHE, if set); 0 = the
                                  defaults below (default 0).  Every choice gives the same
                                  iterates bit for bit; only the order in which the residual
-                                 norm's partial sums are added depends on it. */
+                                 norm's partial sums are added depends on it.  A level of few
+                                 work items (about 10^6 active cells or fewer) whose depth the
+                                 options below do not fix runs its passes over 8 x 8 x 8 cubes
+                                 instead, with the same iterates and norms bit for bit. */
     int32_t item_depth_fine;  /* planes per finest-level work item: 8, 16 or 32; 0 = default
                                  (16) or tuned.  A non-zero value is used as given. */
     int32_t item_depth_l1;    /* level 1: 2, 4 or 8; 0 = default (4) or tuned; 1 = plain passes
@@ -181,8 +184,8 @@ int64_t mg_level_active(const mg_hierarchy *H, int32_t level, int32_t order);
 
 /* Planes per smoother work item of level l in boundary order `order` (the
  * default, the option's or the tuned value; work items are 32 x 8 cell
- * columns), 1 when its plain passes run over whole 8 x 8 x 8 cubes; -1 for
- * an invalid level or order.  Levels run by the
+ * columns), 1 when the option or the tuner picked whole 8 x 8 x 8 cubes for
+ * its plain passes; -1 for an invalid level or order.  Levels run by the
  * one-workgroup small-level kernel keep their lists but use none. */
 int32_t mg_level_item_depth(const mg_hierarchy *H, int32_t level, int32_t order);
 

@@ -504,6 +504,13 @@ void create(mg_hierarchy *H, const int8_t *mask, int nx, int ny, int nz, double 
         HIPCHK(hipEventCreateWithFlags(&H->evn[q], hipEventDisableTiming | hipEventDisableSystemFence));
     HIPCHK(hipStreamSynchronize(s));
     if (H->opt.tune) tune_depths(H);
+    // levels of few work items run every pass over cubes, unless the options
+    // fix their shape
+    for (int o = 1; o <= 2; o++)
+        for (int l = 0; l < H->nlev[o]; l++) {
+            OrderData &od = lev[l].od[o];
+            od.few = !H->opt.fuse_passes && !forced_depth(H->opt, l) && 4 * od.ntiles <= FEW_CUBES;
+        }
     HIPCHK(hipStreamSynchronize(s));
     H->coarse_order_state = 0;
 }
@@ -622,7 +629,7 @@ void mg_level(mg_hierarchy *H, int l, int order, bool zero_start, Cur &cur, bool
                                         e1));
         if (timed) H->kt_used++;
         cur.c[l] = b;
-    } else if (l > 0 && odl.cube && o.n_pre >= 1) {
+    } else if (l > 0 && odl.cubes() && o.n_pre >= 1) {
         // cube levels: the last pre-smoothing pass also restricts the residual
         if (o.n_pre > 1) smooth(H, l, order, o.n_pre - 1, zero_start, cur, f32, in);
         const bool zin = zero_start && o.n_pre == 1;

@@ -32,6 +32,16 @@ constexpr int item_depth(int level) {
 constexpr bool depth_supported(int level, int depth) {
     return level == 0 ? (depth == 8 || depth == 16 || depth == 32) : (depth == 2 || depth == 4 || depth == 8);
 }
+// A level of at most this many 8^3 cubes (four per active tile) runs all its
+// passes over cubes: two rounds of blocks at most, each one memory latency and
+// three barriers, where a march takes a latency and two barriers per plane on a
+// chip its items cannot fill.  Finest passes (plain, norm, residual, prolonging,
+// FP64, march against cubes): 64^3 sphere with holes 15 / 18 / 22 / 20 us
+// against 5.0 / 8.3 / 9.2 / 8.8; 136 x 72 x 104 (2340 cubes) 17 / 21 / 25 / 23
+// against 10.8 / 16.3 / 19.3 / 18.1; at 160 x 144 x 176 (about 3400 active
+// cubes) a whole cycle takes the same either way, above that the cubes' 3.4
+// times larger halo traffic loses.
+constexpr int FEW_CUBES = 4096;
 // Coarse-level option value selecting 8^3 cube items for plain passes (the
 // passes that apply the prolongation keep the default march).
 constexpr int DEPTH_CUBE = 1;
@@ -70,6 +80,8 @@ struct OrderData {
     int ntiles = 0, nsegs = 0;
     int depth = 0;  // planes per work item of segs (its masks hold depth + 4 words per item)
     bool cube = false;  // coarse levels: plain passes over 8^3 cubes loaded whole (no z march)
+    bool few = false;   // too few work items to fill the chip: every pass of the level over cubes
+    bool cubes() const { return cube || few; }
     int64_t nact = 0;
 };
 

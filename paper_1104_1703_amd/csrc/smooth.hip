@@ -101,39 +101,68 @@ __global__ __launch_bounds__(NT, 2) void k_rbgs2(const T *__restrict__ xin, T *_
                                         pm + (size_t)item * (SEGZ + 2 * rb2::H), xc, cnx, cny, cnz);
 }
 
-// Coarse-level pass over 8 x 8 x 8 cubes (four per active 32 x 8 x 8 tile),
-// each loaded whole: cube_core.h.
-template <typename T>
-__global__ __launch_bounds__(cube::NT) void k_rbgs_cube(const T *__restrict__ xin, T *__restrict__ xout,
-                                                      const T *__restrict__ f, const T *__restrict__ d, int nx, int ny,
-                                                      int nz, int ntx, int nty, T h2, const int *__restrict__ tiles,
-                                                      int ntiles, const int *__restrict__ halt) {
-    __shared__ cube::Lds<T> lds;
-    const int item = xcd_item(blockIdx.x, gridDim.x);
-    if (item >= 4 * ntiles || (halt && *halt)) return;
+// Origin of cube `item` (four per active 32 x 8 x 8 tile); false past the last
+// cube and for cubes of a tile wider than the level.
+struct CubeAt {
+    int x0, y0, z0;
+};
+__device__ __forceinline__ bool cube_at(int item, const int *tiles, int ntiles, int ntx, int nty, int nx, CubeAt &c) {
+    if (item >= 4 * ntiles) return false;
     const int tile = tiles[item >> 2];
-    const int tx = tile % ntx, ty = (tile / ntx) % nty, tz = tile / (ntx * nty);
-    const int x0 = tx * TX + (item & 3) * cube::C;
-    if (x0 >= nx) return;  // a tile wider than the level
-    cube::rbgs_cube<T>(lds, xin, xout, f, d, nx, ny, nz, h2, x0, ty * TY, tz * TZ);
+    c.x0 = (tile % ntx) * TX + (item & 3) * cube::C;
+    c.y0 = (tile / ntx) % nty * TY;
+    c.z0 = tile / (ntx * nty) * TZ;
+    return c.x0 < nx;
+}
+
+// Pass over 8 x 8 x 8 cubes, each loaded whole: cube_core.h.
+template <typename T, bool FINE, bool PRO>
+__global__ __launch_bounds__(cube::NT) void k_rbgs_cube(const T *__restrict__ xin, T *__restrict__ xout,
+                                                      const T *__restrict__ f,
+                                                      const cube::DiagT<T, FINE> *__restrict__ d, int nx, int ny,
+                                                      int nz, int ntx, int nty, T h2, const int *__restrict__ tiles,
+                                                      int ntiles, const int *__restrict__ halt,
+                                                      const T *__restrict__ xc, int cnx, int cny, int cnz) {
+    __shared__ cube::Lds<T, FINE, PRO> lds;
+    CubeAt c;
+    if (!cube_at(xcd_item(blockIdx.x, gridDim.x), tiles, ntiles, ntx, nty, nx, c) || (halt && *halt)) return;
+    cube::rbgs_cube<T, FINE, PRO>(lds, xin, xout, f, d, nx, ny, nz, h2, c.x0, c.y0, c.z0, xc, cnx, cny, cnz);
 }
 
 // The cube pass that also forms the residual and its R1 restriction onto
 // the next coarser level (the last pre-smoothing pass of a cube level).
-template <typename T>
+template <typename T, bool FINE>
 __global__ __launch_bounds__(cube::NT) void k_rbgs_cube_restrict(
-    const T *__restrict__ xin, T *__restrict__ xout, const T *__restrict__ f, const T *__restrict__ d, int nx, int ny,
-    int nz, int ntx, int nty, T h2, T ih2, const int *__restrict__ tiles, int ntiles, const int *__restrict__ halt,
-    const T *__restrict__ cd, T *__restrict__ fc, int cnx, int cny, int cnz) {
-    __shared__ cube::LdsRes<T> lds;
-    const int item = xcd_item(blockIdx.x, gridDim.x);
-    if (item >= 4 * ntiles || (halt && *halt)) return;
-    const int tile = tiles[item >> 2];
-    const int tx = tile % ntx, ty = (tile / ntx) % nty, tz = tile / (ntx * nty);
-    const int x0 = tx * TX + (item & 3) * cube::C;
-    if (x0 >= nx) return;  // a tile wider than the level
-    cube::rbgs_cube_restrict<T>(lds, xin, xout, f, d, nx, ny, nz, h2, ih2, x0, ty * TY, tz * TZ, cd, fc, cnx, cny,
-                                cnz);
+    const T *__restrict__ xin, T *__restrict__ xout, const T *__restrict__ f,
+    const cube::DiagT<T, FINE> *__restrict__ d, int nx, int ny, int nz, int ntx, int nty, T h2, T ih2,
+    const int *__restrict__ tiles, int ntiles, const int *__restrict__ halt, const T *__restrict__ cd,
+    T *__restrict__ fc, int cnx, int cny, int cnz) {
+    __shared__ cube::LdsRes<T, FINE> lds;
+    CubeAt c;
+    if (!cube_at(xcd_item(blockIdx.x, gridDim.x), tiles, ntiles, ntx, nty, nx, c) || (halt && *halt)) return;
+    cube::rbgs_cube_restrict<T, FINE>(lds, xin, xout, f, d, nx, ny, nz, h2, ih2, c.x0, c.y0, c.z0, cd, fc, cnx, cny,
+                                      cnz);
+}
+
+// A finest cube pass whose launch also forms the residual-norm partials of
+// its input: the first nitems blocks take one work item's partial each (as
+// launch_resnorm does), the others one cube.
+__global__ __launch_bounds__(cube::NT) void k_rbgs_cube_norm(
+    const double *__restrict__ xin, double *__restrict__ xout, const double *__restrict__ f,
+    const uint8_t *__restrict__ code, int nx, int ny, int nz, int ntx, int nty, double h2, double ih2,
+    const int *__restrict__ tiles, int ntiles, const Seg *__restrict__ segs, int nitems, const int *__restrict__ halt,
+    double *__restrict__ part) {
+    __shared__ cube::Lds<double, true, false> lds;
+    if (halt && *halt) return;
+    const int b = blockIdx.x;
+    if (b < nitems) {  // uniform per block
+        const double t = tr::block_sum(tr::item_norm(segs[b], xin, f, code, nx, ny, nz, ih2));
+        if (threadIdx.x == 0) part[b] = t;
+        return;
+    }
+    CubeAt c;
+    if (!cube_at(xcd_item(b - nitems, gridDim.x - nitems), tiles, ntiles, ntx, nty, nx, c)) return;
+    cube::rbgs_cube<double, true, false>(lds, xin, xout, f, code, nx, ny, nz, h2, c.x0, c.y0, c.z0);
 }
 
 inline unsigned grid8(int items) { return (unsigned)(((items + 7) / 8) * 8); }
@@ -157,30 +186,50 @@ hipError_t launch_k(void (*k)(P...), unsigned grid, hipStream_t s, hipEvent_t e0
 
 }  // namespace
 
-template <typename T>
-void launch_cube_restrict(const T *xin, T *xout, const T *f, const T *d, const Level &L, const OrderData &od, T h2,
-                          T ih2, const Level &C, const T *cd, T *fc, hipStream_t s) {
-    if (od.ntiles == 0) return;
-    k_rbgs_cube_restrict<T><<<grid8(4 * od.ntiles), cube::NT, 0, s>>>(xin, xout, f, d, L.nx, L.ny, L.nz, L.ntx,
-                                                                     L.nty, h2, ih2, od.tiles, od.ntiles, L.halt, cd,
-                                                                     fc, C.nx, C.ny, C.nz);
+// The level's diagonal as the cube kernels take it.
+template <typename T, bool FINE>
+const cube::DiagT<T, FINE> *cube_diag(const Level &L, const OrderData &od) {
+    if constexpr (FINE) return L.code;
+    else if constexpr (sizeof(T) == 8) return od.d;
+    else return od.d32;
+}
+
+template <typename T, bool FINE>
+hipError_t launch_cube_restrict(const T *xin, T *xout, const T *f, const Level &L, const OrderData &od,
+                                const Level &C, const T *cd, T *fc, hipStream_t s, hipEvent_t e0 = nullptr,
+                                hipEvent_t e1 = nullptr) {
+    if (od.ntiles == 0) return hipSuccess;
+    return launch_k(k_rbgs_cube_restrict<T, FINE>, grid8(4 * od.ntiles), s, e0, e1, xin, xout, f,
+                    cube_diag<T, FINE>(L, od), L.nx, L.ny, L.nz, L.ntx, L.nty, (T)(L.h * L.h),
+                    (T)(1.0 / (L.h * L.h)), od.tiles, od.ntiles, L.halt, cd, fc, C.nx, C.ny, C.nz);
+}
+
+template <typename T, bool FINE, bool PRO = false>
+hipError_t launch_cube(const T *xin, T *xout, const T *f, const Level &L, const OrderData &od, hipStream_t s,
+                       hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr, const T *xc = nullptr,
+                       const Level *C = nullptr) {
+    static_assert(TX == 4 * cube::C && TY == cube::C && TZ == cube::C, "a tile holds four cubes");
+    if (od.ntiles == 0) return hipSuccess;
+    return launch_k(k_rbgs_cube<T, FINE, PRO>, grid8(4 * od.ntiles), s, e0, e1, xin, xout, f,
+                    cube_diag<T, FINE>(L, od), L.nx, L.ny, L.nz, L.ntx, L.nty, (T)(L.h * L.h), od.tiles, od.ntiles,
+                    L.halt, xc, C ? C->nx : 0, C ? C->ny : 0, C ? C->nz : 0);
 }
 
 void launch_rbgs_restrict(const Level &L, const Level &C, int order, const OrderData &od, const double *xin,
                           double *xout, const double *f, double *fc, hipStream_t s) {
-    launch_cube_restrict<double>(xin, xout, f, od.d, L, od, L.h * L.h, 1.0 / (L.h * L.h), C, C.od[order].d, fc, s);
+    (void)launch_cube_restrict<double, false>(xin, xout, f, L, od, C, C.od[order].d, fc, s);
 }
 
 void launch_rbgs_restrict32(const Level &L, const Level &C, int order, const OrderData &od, const float *xin,
                             float *xout, const float *f, float *fc, hipStream_t s) {
-    launch_cube_restrict<float>(xin, xout, f, od.d32, L, od, (float)(L.h * L.h), (float)(1.0 / (L.h * L.h)), C,
-                                C.od[order].d32, fc, s);
+    (void)launch_cube_restrict<float, false>(xin, xout, f, L, od, C, C.od[order].d32, fc, s);
 }
 
 template <typename T>
 hipError_t launch_fine_res(const Level &L, const OrderData &od, const T *xin, T *xout, const T *f, const Level &C,
                            const T *cd, T *fc, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     if (od.nsegs == 0) return hipSuccess;
+    if (od.few) return launch_cube_restrict<T, true>(xin, xout, f, L, od, C, cd, fc, s, e0, e1);
     const T h2 = (T)(L.h * L.h), ih2 = (T)(1.0 / (L.h * L.h));
     hipError_t err = hipSuccess;
     with_fine_depth(od.depth, [&](auto Z) {
@@ -200,15 +249,6 @@ hipError_t launch_rbgs_res_fine32(const Level &L, const Level &C, int order, con
                                   float *xout, const float *f, float *fc, hipStream_t s, hipEvent_t e0,
                                   hipEvent_t e1) {
     return launch_fine_res<float>(L, od, xin, xout, f, C, C.od[order].d32, fc, s, e0, e1);
-}
-
-template <typename T>
-void launch_cube(const T *xin, T *xout, const T *f, const T *d, const Level &L, const OrderData &od, T h2,
-                 hipStream_t s) {
-    static_assert(TX == 4 * cube::C && TY == cube::C && TZ == cube::C, "a tile holds four cubes");
-    if (od.ntiles == 0) return;
-    k_rbgs_cube<T><<<grid8(4 * od.ntiles), cube::NT, 0, s>>>(xin, xout, f, d, L.nx, L.ny, L.nz, L.ntx, L.nty, h2,
-                                                            od.tiles, od.ntiles, L.halt);
 }
 
 // Coarse levels: the kernel instance for the level's item depth.
@@ -235,6 +275,7 @@ static_assert((SEGZ_COARSE1 == 2 || SEGZ_COARSE1 == 4 || SEGZ_COARSE1 == 8) &&
 template <typename T>
 hipError_t launch_fine(const Level &L, const OrderData &od, const T *xin, T *xout, const T *f, T h2, hipStream_t s,
                        hipEvent_t e0, hipEvent_t e1) {
+    if (od.few) return launch_cube<T, true>(xin, xout, f, L, od, s, e0, e1);
     hipError_t err = hipSuccess;
     with_fine_depth(od.depth, [&](auto Z) {
         err = launch_k(k_rbgs<T, true, decltype(Z)::value>, grid8(od.nsegs), s, e0, e1, xin, xout, f, L.code,
@@ -250,8 +291,8 @@ hipError_t launch_rbgs(const Level &L, int level, const OrderData &od, const dou
     const double h2 = L.h * L.h;
     if (level == 0)
         return launch_fine<double>(L, od, xin, xout, f, h2, s, e0, e1);
-    else if (od.cube)
-        launch_cube<double>(xin, xout, f, od.d, L, od, h2, s);
+    else if (od.cubes())
+        return launch_cube<double, false>(xin, xout, f, L, od, s);
     else
         launch_coarse<double>(od.depth, xin, xout, f, od.d, L, od, h2, s);
     return hipSuccess;
@@ -260,6 +301,10 @@ hipError_t launch_rbgs(const Level &L, int level, const OrderData &od, const dou
 hipError_t launch_rbgs_norm(const Level &L, const OrderData &od, const double *xin, double *xout, const double *f,
                             double *part, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     if (od.nsegs == 0) return hipSuccess;
+    if (od.few)
+        return launch_k(k_rbgs_cube_norm, (unsigned)od.nsegs + grid8(4 * od.ntiles), s, e0, e1, xin, xout, f, L.code,
+                        L.nx, L.ny, L.nz, L.ntx, L.nty, L.h * L.h, 1.0 / (L.h * L.h), od.tiles, od.ntiles, od.segs,
+                        od.nsegs, L.halt, part);
     hipError_t err = hipSuccess;
     with_fine_depth(od.depth, [&](auto Z) {
         err = launch_k(k_rbgs_norm<decltype(Z)::value>, grid8(od.nsegs), s, e0, e1, xin, xout, f, L.code, L.nx, L.ny,
@@ -272,6 +317,9 @@ hipError_t launch_rbgs_prolong(const Level &L, int level, const OrderData &od, c
                                const double *xin, double *xout, const double *f, hipStream_t s, hipEvent_t e0,
                                hipEvent_t e1) {
     if (od.nsegs == 0) return hipSuccess;
+    if (od.few)
+        return level == 0 ? launch_cube<double, true, true>(xin, xout, f, L, od, s, e0, e1, xc, &C)
+                          : launch_cube<double, false, true>(xin, xout, f, L, od, s, e0, e1, xc, &C);
     const double h2 = L.h * L.h;
     hipError_t err = hipSuccess;
     if (level == 0)
@@ -293,6 +341,9 @@ hipError_t launch_rbgs_prolong32(const Level &L, int level, const OrderData &od,
                                  const float *xin, float *xout, const float *f, hipStream_t s, hipEvent_t e0,
                                  hipEvent_t e1) {
     if (od.nsegs == 0) return hipSuccess;
+    if (od.few)
+        return level == 0 ? launch_cube<float, true, true>(xin, xout, f, L, od, s, e0, e1, xc, &C)
+                          : launch_cube<float, false, true>(xin, xout, f, L, od, s, e0, e1, xc, &C);
     const float h2 = (float)(L.h * L.h);
     hipError_t err = hipSuccess;
     if (level == 0)
@@ -357,8 +408,8 @@ hipError_t launch_rbgs32(const Level &L, int level, const OrderData &od, const f
     const float h2 = (float)(L.h * L.h);
     if (level == 0)
         return launch_fine<float>(L, od, xin, xout, f, h2, s, e0, e1);
-    else if (od.cube)
-        launch_cube<float>(xin, xout, f, od.d32, L, od, h2, s);
+    else if (od.cubes())
+        return launch_cube<float, false>(xin, xout, f, L, od, s);
     else
         launch_coarse<float>(od.depth, xin, xout, f, od.d32, L, od, h2, s);
     return hipSuccess;

@@ -71,6 +71,17 @@ __global__ __launch_bounds__(NT) void k_resnorm(const int *__restrict__ tiles, i
     if (threadIdx.x == 0) part[w] = s;
 }
 
+// The norm partials of a finest level of few work items, bit for bit those of
+// k_residual_march<.., RM_NORM>.
+__global__ __launch_bounds__(NT) void k_item_norm(const double *__restrict__ x, const double *__restrict__ f,
+                                                  const uint8_t *__restrict__ code, int nx, int ny, int nz, double ih2,
+                                                  const Seg *__restrict__ segs, double *__restrict__ part,
+                                                  const int *__restrict__ halt) {
+    if (halt && *halt) return;
+    const double t = block_sum(item_norm(segs[blockIdx.x], x, f, code, nx, ny, nz, ih2));
+    if (threadIdx.x == 0) part[blockIdx.x] = t;
+}
+
 __global__ __launch_bounds__(1024) void k_finalize(const double *__restrict__ part, int n, double *__restrict__ out,
                                                    int slot, StopTest *__restrict__ stop, int *__restrict__ halt,
                                                    double *__restrict__ host_out = nullptr) {
@@ -281,7 +292,9 @@ void launch_resnorm(const Level &L, int level, const OrderData &od, const double
                     double *out, int slot, hipStream_t s, const StopTest *stop, double *host_out) {
     const double ih2 = 1.0 / (L.h * L.h);
     if (level == 0) {
-        if (od.nsegs)
+        if (od.nsegs && od.few)
+            k_item_norm<<<od.nsegs, NT, 0, s>>>(x, f, L.code, L.nx, L.ny, L.nz, ih2, od.segs, part, L.halt);
+        else if (od.nsegs)
             with_fine_depth(od.depth, [&](auto Z) {
                 k_residual_march<double, decltype(Z)::value, RM_NORM><<<grid8(od.nsegs), NT, 0, s>>>(
                     x, f, L.code, L.nx, L.ny, L.nz, ih2, od.segs, od.pmask, od.nsegs, nullptr, 0, 0, nullptr, part,

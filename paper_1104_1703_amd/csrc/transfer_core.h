@@ -207,6 +207,39 @@ __device__ __forceinline__ double resnorm_col(const Col &c, int nx, int ny, int 
     return acc;
 }
 
+// ---- residual norm of one finest smoother work item, without a march ----
+// This thread's sum of (L x - f)^2 over its column of the item (one cell per
+// plane, planes in order): the terms, their expression and their order are
+// those of the residual-norm march, so the block sums are bit for bit the
+// march's.  Four planes of loads are issued at a time (about four memory
+// latencies an item, where the march takes one and a barrier per plane): the
+// choice for a finest level of few work items.  x may be null (x = 0).
+__device__ __forceinline__ double item_norm(const Seg sg, const double *__restrict__ x, const double *__restrict__ f,
+                                            const uint8_t *__restrict__ code, int nx, int ny, int nz, double ih2) {
+    const int i = sg.x0 + (int)(threadIdx.x % TX), j = sg.y0 + (int)(threadIdx.x / TX);
+    const int z0 = sg.z0 < 0 ? 0 : sg.z0, z1 = sg.z1 < nz ? sg.z1 : nz;
+    double sq = 0.0;
+    if (i >= nx || j >= ny) return sq;
+    for (int k = z0; k < z1; k += QZ) {
+        double r[QZ], dv[QZ];
+        if (x) {
+            column_residual<double, true>(x, f, code, nullptr, i, j, k, true, nx, ny, nz, ih2, r, dv);
+        } else {
+            const size_t pl = (size_t)nx * ny, c0 = (size_t)j * nx + i;
+#pragma unroll
+            for (int q = 0; q < QZ; q++) {
+                const size_t p = (size_t)clampi(k + q, nz - 1) * pl + c0;
+                dv[q] = (double)code[p];
+                r[q] = dv[q] != 0.0 ? -f[p] : 0.0;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < QZ; q++)
+            if (k + q < z1) sq += r[q] * r[q];
+    }
+    return sq;
+}
+
 // ---- R1 restriction of the residual (Sec. 2 steps 2-5) ----
 // Coarse active cell t gets f_c = -(1/8) sum over its active children of
 // r = L x - f; the coarse problem is Delta_c dPhi = -r_c.  The 2 x 2 x 2
