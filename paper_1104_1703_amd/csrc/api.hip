@@ -485,6 +485,20 @@ void create(mg_hierarchy *H, const int8_t *mask, int nx, int ny, int nz, double 
         // sweeps are then one launch instead of one launch each
         const int last = H->nlev[o] - 1;
         if (H->ls[o] < 0 && last >= 1 && small_lds_bytes(H, o, last, false) <= (size_t)small_lim) H->ls[o] = last;
+        // a small deepest level below others is solved by its relaxation's matrix
+        if (H->ls[o] >= 0 && H->ls[o] < last && deep_matrix_fits(lev[last])) {
+            OrderData &od = lev[last].od[o];
+            od.deep = alloc_n<double>(H, lev[last].n * lev[last].n);
+            if (mixed) od.deep32 = alloc_n<float>(H, lev[last].n * lev[last].n);
+            launch_deep_matrix(lev[last], od, H->opt.n_cycles * H->opt.n_coarse_sweeps, s);
+        }
+        if (H->ls[o] >= 0 && small_fast_levels(H, o, H->ls[o]))
+            for (int l = H->ls[o]; l < std::min(H->nlev[o], H->ls[o] + 2); l++) {
+                OrderData &od = lev[l].od[o];
+                od.rd = alloc_n<double>(H, lev[l].n);
+                if (mixed) od.rd32 = alloc_n<float>(H, lev[l].n);
+                launch_reciprocals(lev[l], od, s);
+            }
     }
     H->part_cap = std::max(1, lev[0].od[2].ntiles * TZ);
     H->part = alloc_n<double>(H, (size_t)H->part_cap);

@@ -164,7 +164,10 @@ __global__ __launch_bounds__(NTS) void kb_small(const BRef *__restrict__ refs, i
     if (state[p] != order) return;
     const BLev &L = lev[r.lev];
     const int sel = r.w >> WBITS;
-    small::small_tail<double, NTS>(reinterpret_cast<double *>(smem_raw), sl[p], L.f, L.x[sel & 1], (sel & 2) == 0);
+    double *sm = reinterpret_cast<double *>(smem_raw);
+    const small::SmallLevels<double> &S = sl[p];
+    if (S.fast) small::small_fast<double, NTS>(sm, S, L.f, L.x[sel & 1], (sel & 2) == 0);
+    else small::small_tail<double, NTS>(sm, S, L.f, L.x[sel & 1], (sel & 2) == 0);
 }
 
 // Per patch p: the sum of part[first[p] .. first[p] + cnt[p]) in the same
@@ -738,9 +741,12 @@ std::vector<small::SmallLevels<double>> small_levels(mg_batch *B, int o) {
             S.h2[q] = L.h * L.h;
             S.ih2[q] = 1.0 / (L.h * L.h);
             S.d[q] = L.od[o].d;
+            if (q < 2) S.rd[q] = L.od[o].rd;
             S.off[q] = off;
             off += 3 * (int)L.n;
         }
+        S.fast = small_fast_levels(H, o, ls) ? 1 : 0;
+        S.deep = H->lev[H->nlev[o] - 1].od[o].deep;
         S.n_pre = B->opt.n_pre;
         S.n_post = B->opt.n_post;
         S.n_cycles = B->opt.n_cycles;

@@ -23,7 +23,31 @@ template <typename T>
 __global__ __launch_bounds__(NTC) void k_coarse(SmallLevels<T> S) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     if (S.halt && *S.halt) return;
-    small_tail<T, NTC>(reinterpret_cast<T *>(smem_raw), S, S.f0, S.x0, S.load_x != 0);
+    T *sm = reinterpret_cast<T *>(smem_raw);
+    if (S.fast) small_fast<T, NTC>(sm, S, S.f0, S.x0, S.load_x != 0);
+    else small_tail<T, NTC>(sm, S, S.f0, S.x0, S.load_x != 0);
+}
+
+// Column blockIdx.x of the deepest level's relaxation matrix (deep_solve):
+// `passes` passes from zero on the unit right-hand side of that cell.
+__global__ __launch_bounds__(DEEP_MAX) void k_deep_matrix(Lv<double> L, const double *__restrict__ d, int passes,
+                                                         double *__restrict__ M, float *__restrict__ M32) {
+    __shared__ double sx[DEEP_MAX], sf[DEEP_MAX], sd[DEEP_MAX];
+    const int e = threadIdx.x, j = blockIdx.x;
+    if (e < L.n) {
+        sx[e] = 0.0;
+        sd[e] = d[e];
+        sf[e] = e == j && sd[e] != 0.0 ? 1.0 : 0.0;
+    }
+    L.x = sx;
+    L.f = sf;
+    L.d = sd;
+    __syncthreads();
+    smooth<double, DEEP_MAX>(L, passes);
+    if (e < L.n) {
+        M[e * L.n + j] = sx[e];
+        if (M32) M32[e * L.n + j] = (float)sx[e];
+    }
 }
 
 template <typename T>
@@ -45,26 +69,86 @@ void launch_impl(const mg_hierarchy *H, int order, int ls, bool zero_start, cons
         S.h2[q] = (T)(L.h * L.h);
         S.ih2[q] = (T)(1.0 / (L.h * L.h));
         S.d[q] = f32 ? (const T *)L.od[order].d32 : (const T *)L.od[order].d;
+        if (q < 2) S.rd[q] = f32 ? (const T *)L.od[order].rd32 : (const T *)L.od[order].rd;
         S.off[q] = off;
         off += 3 * (int)L.n;
     }
     S.f0 = f0;
     S.x0 = x0;
     S.load_x = zero_start ? 0 : 1;
+    S.deep = f32 ? (const T *)H->lev[last].od[order].deep32 : (const T *)H->lev[last].od[order].deep;
     S.halt = H->lev[0].halt;
     S.n_pre = H->opt.n_pre;
     S.n_post = H->opt.n_post;
     S.n_cycles = H->opt.n_cycles;
     S.n_coarse = H->opt.n_coarse_sweeps;
-    const size_t bytes = (size_t)off * sizeof(T);
+    S.fast = small_fast_levels(H, order, ls) ? 1 : 0;
+    const size_t bytes = small_lds_bytes(H, order, ls, f32);
     k_coarse<T><<<1, NTC, bytes, s>>>(S);
 }
 
 }  // namespace
 
+bool deep_matrix_fits(const Level &L) { return L.n <= (size_t)DEEP_MAX; }
+
+void launch_deep_matrix(const Level &L, const OrderData &od, int passes, hipStream_t s) {
+    Lv<double> v{};
+    v.nx = L.nx;
+    v.ny = L.ny;
+    v.nz = L.nz;
+    v.n = (int)L.n;
+    v.mx = div_magic((unsigned)L.nx);
+    v.mxy = div_magic((unsigned)(L.nx * L.ny));
+    v.hx = (L.nx + 1) / 2;
+    v.mh = div_magic((unsigned)v.hx);
+    v.mhy = div_magic((unsigned)(v.hx * L.ny));
+    v.h2 = L.h * L.h;
+    v.ih2 = 1.0 / (L.h * L.h);
+    k_deep_matrix<<<(unsigned)L.n, DEEP_MAX, 0, s>>>(v, od.d, passes, od.deep, od.deep32);
+}
+
+__global__ void k_reciprocals(const double *__restrict__ d, size_t n, double *__restrict__ rd,
+                              float *__restrict__ rd32) {
+    const size_t p = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+    if (p >= n) return;
+    rd[p] = d[p] != 0.0 ? 1.0 / d[p] : 0.0;
+    if (rd32) rd32[p] = d[p] != 0.0 ? 1.0f / (float)d[p] : 0.0f;
+}
+
+void launch_reciprocals(const Level &L, const OrderData &od, hipStream_t s) {
+    k_reciprocals<<<(unsigned)((L.n + 255) / 256), 256, 0, s>>>(od.d, L.n, od.rd, od.rd32);
+}
+
+namespace {
+
+// Dims of the levels ls .. last (at most three) for fast_fits / fast_lds.
+struct SmallDims {
+    int n = 0, nx[3], ny[3], nz[3];
+    bool direct = false;
+    SmallDims(const mg_hierarchy *H, int order, int ls) {
+        const int last = H->nlev[order] - 1;
+        n = last - ls + 1;
+        for (int q = 0; q < n && q < 3; q++) {
+            const Level &L = H->lev[ls + q];
+            nx[q] = L.nx, ny[q] = L.ny, nz[q] = L.nz;
+        }
+        direct = last > ls && deep_matrix_fits(H->lev[last]);
+    }
+};
+
+}  // namespace
+
+bool small_fast_levels(const mg_hierarchy *H, int order, int ls) {
+    const SmallDims d(H, order, ls);
+    return fast_fits(d.n, d.direct, d.nx, d.ny, d.nz, NTC);
+}
+
 size_t small_lds_bytes(const mg_hierarchy *H, int order, int ls, bool f32) {
     size_t n = 0;
     for (int l = ls; l < H->nlev[order]; l++) n += 3 * H->lev[l].n;
+    const SmallDims d(H, order, ls);
+    if (fast_fits(d.n, d.direct, d.nx, d.ny, d.nz, NTC))
+        n = std::max(n, (size_t)fast_lds(d.n, d.direct, d.nx, d.ny, d.nz).end);
     return n * (f32 ? sizeof(float) : sizeof(double));
 }
 

@@ -8,6 +8,13 @@
 namespace mg {
 namespace small {
 
+// One fused multiply-add in T (named, so that every path rounds alike).
+template <typename T>
+__device__ __forceinline__ T fma_t(T a, T b, T c) {
+    if constexpr (sizeof(T) == 8) return __builtin_fma(a, b, c);
+    else return __builtin_fmaf(a, b, c);
+}
+
 template <typename T>
 struct SmallLevels {
     int n;                 // number of levels held (ls..last)
@@ -17,10 +24,13 @@ struct SmallLevels {
     T h2[MAXS];            // h^2 per level
     T ih2[MAXS];           // 1/h^2 per level
     const T *d[MAXS];      // diagonal per level (global), 0 off the domain
+    const T *rd[2];        // reciprocals 1/d of the first two levels (global; small_fast)
+    int fast;              // the call takes small_fast
     int off[MAXS];         // LDS offset (elements) of the level's x; f and d follow
     const T *f0;           // right-hand side of level ls (global)
     T *x0;                 // iterate of level ls (global, in/out)
     int load_x;            // 1: start from x0, 0: start from zero
+    const T *deep;         // matrix of the deepest level's relaxation (deep_solve), nullptr: relax it
     const int *halt;       // the solve loop's halt flag (nullable): the call does nothing when set
     int n_pre, n_post, n_cycles, n_coarse;
 };
@@ -228,6 +238,31 @@ __device__ void smooth(const Lv<T> &L, int passes) {
         }
 }
 
+// The deepest level's whole share of a cycle as one matrix product.  Its
+// n_cycles x n_coarse passes start from zero and are linear in f, so they are
+// x = M f with M formed once per hierarchy (column j: the passes applied to the
+// unit right-hand side of cell j, k_deep_matrix); 64 half-sweeps of a 4^3 level
+// take 9 us, each an LDS round trip, the product about 1 us.  16 lanes share a
+// row, lane q summing columns q, q + 16, ... in order, then an exchange tree:
+// the same sums for any thread count.  DEEP_MAX cells: a matrix of 512 KB, which
+// one workgroup reads in less time than the passes take.
+constexpr int DEEP_MAX = 256;
+
+template <typename T, int NTH>
+__device__ void deep_solve(const Lv<T> &L, const T *__restrict__ M) {
+    const int q = threadIdx.x & 15;
+    for (int row0 = 0; row0 < L.n; row0 += NTH / 16) {
+        const int row = row0 + (int)(threadIdx.x >> 4);
+        T s = T(0);
+        if (row < L.n)
+            for (int j = q; j < L.n; j += 16) s = fma_t<T>(M[row * L.n + j], L.f[j], s);
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        if (row < L.n && q == 0) L.x[row] = L.d[row] != T(0) ? s : T(0);
+    }
+    __syncthreads();
+}
+
 // f_c = -(1/8) sum over active children of (L x - f); x_c = 0.
 template <typename T, int NTH>
 __device__ void restrict_to(const Lv<T> &L, const Lv<T> &C) {
@@ -241,7 +276,8 @@ __device__ void restrict_to(const Lv<T> &L, const Lv<T> &C) {
                 const int i = 2 * I + (c & 1), j = 2 * J + ((c >> 1) & 1), k = 2 * K + (c >> 2);
                 const int p = (k * L.ny + j) * L.nx + i;
                 const T d = L.d[p];
-                if (d != T(0)) s += (nb_sum(L.x, i, j, k, L.nx, L.ny, L.nz) - d * L.x[p]) * L.ih2 - L.f[p];
+                if (d != T(0))
+                    s += fma_t<T>(fma_t<T>(-d, L.x[p], nb_sum(L.x, i, j, k, L.nx, L.ny, L.nz)), L.ih2, -L.f[p]);
             }
             s = -s / T(8);
         }
@@ -272,11 +308,300 @@ __device__ void prolong_from(const Lv<T> &L, const Lv<T> &C) {
                     T v = T(0);
                     if (ci >= 0 && ci < C.nx && cj >= 0 && cj < C.ny && ck >= 0 && ck < C.nz)
                         v = C.x[(ck * C.ny + cj) * C.nx + ci];
-                    s += w[a] * w[b] * w[c] * v;
+                    s = fma_t<T>(w[a] * w[b] * w[c], v, s);
                 }
         L.x[e] += s;
     }
     __syncthreads();
+}
+
+// ---- the call on one to three levels with the cells in registers ----
+// One CU issues the whole call, so its instruction count decides: a phase of
+// the general path spends most of its instructions on cell indices, box-edge
+// selects and reciprocals, once per phase and level.  Here each thread owns the
+// same cells throughout (up to two of each colour on the first level A, one of
+// each on the second, B), holds their diagonal, its reciprocal (formed once
+// per hierarchy) and right-hand side in registers, and x lies in LDS with a
+// ring of zeros around the box, so a relaxation is six reads, the sum and the
+// quotient.  The deepest level D is the matrix of deep_solve.  Every value is
+// formed by the expression, in the order, of the general path (bit for bit).
+// Levels A, D or A, B (relaxed n_coarse times, no matrix) or A, B, D, or A
+// alone, relaxed n_coarse times.
+// 16^3 + 8^3 + 4^3: 14 us a call at a 32^3 or 64^3 finest level and 17 us at
+// 256^3, against 25 and 29 us in the general path (30 and 32 us with the
+// deepest level relaxed); in a W-cycle 17 against 57 us.  The general
+// path stays for boxes above 4096 cells, more than three levels and blocks of
+// fewer threads.
+struct FastLds {  // offsets in elements
+    int xa, ra, xb, rb, xd, fd, end;
+};
+
+__host__ __device__ constexpr int padded(int nx, int ny, int nz) { return (nx + 2) * (ny + 2) * (nz + 2); }
+
+// Whether levels with these dims can take the fast path with NTH threads, and
+// the LDS it needs.  direct: the deepest level has its matrix.
+__host__ __device__ inline FastLds fast_lds(int n, bool direct, const int *nx, const int *ny, const int *nz) {
+    FastLds o{};
+    const bool hasb = n == 3 || (n == 2 && !direct);
+    const int d = n - 1;
+    o.xa = 0;
+    o.ra = padded(nx[0], ny[0], nz[0]);
+    o.xb = o.ra + (n > 1 ? nx[0] * ny[0] * nz[0] : 0);
+    o.rb = o.xb + (hasb ? padded(nx[1], ny[1], nz[1]) : 0);
+    o.xd = o.rb + (n == 3 ? nx[1] * ny[1] * nz[1] : 0);
+    o.fd = o.xd + (direct ? padded(nx[d], ny[d], nz[d]) : 0);
+    o.end = o.fd + (direct ? nx[d] * ny[d] * nz[d] : 0);
+    return o;
+}
+inline bool fast_fits(int n, bool direct, const int *nx, const int *ny, const int *nz, int nth) {
+    if (n < 1 || n > 3 || (n == 3 && !direct)) return false;
+    if (((nx[0] + 1) >> 1) * ny[0] * nz[0] > 2 * nth) return false;
+    return n == 1 || (n == 2 && direct) || ((nx[1] + 1) >> 1) * ny[1] * nz[1] <= nth;
+}
+
+// ((x pair) + (y pair) + (z pair) - h^2 f) / d at LDS cell x (strides sy, sz).
+template <typename T>
+__device__ __forceinline__ T relaxed(const T *x, int sy, int sz, T h2, T f, T d, T y) {
+#pragma clang fp contract(off)
+    const T sum = (x[-1] + x[1]) + (x[-sy] + x[sy]) + (x[-sz] + x[sz]);
+    return rb::div_small<T>(sum - h2 * f, d, y);
+}
+
+// L x - f at LDS cell x.
+template <typename T>
+__device__ __forceinline__ T residual_at(const T *x, int sy, int sz, T ih2, T f, T d) {
+    const T sum = (x[-1] + x[1]) + (x[-sy] + x[sy]) + (x[-sz] + x[sz]);
+    return fma_t<T>(fma_t<T>(-d, x[0], sum), ih2, -f);
+}
+
+// -(1/8) of the sum of the 8 children's residuals (0 on inactive ones) from r,
+// whose row and plane strides are nx and nxy; b: the first child.
+template <typename T>
+__device__ __forceinline__ T coarse_rhs(const T *r, int b, int nx, int nxy) {
+    T s = T(0);
+#pragma unroll
+    for (int c = 0; c < 8; c++) s += r[b + (c & 1) + ((c >> 1) & 1) * nx + (c >> 2) * nxy];
+    return -s / T(8);
+}
+
+// P2 at a fine cell of parities (i, j, k): v = the parent in its ring-padded
+// level of strides sy, sz.
+template <typename T>
+__device__ __forceinline__ T interpolated(const T *v, int i, int j, int k, int sy, int sz) {
+    const T w[2] = {T(0.75), T(0.25)};
+    const int ox = (i & 1) ? 1 : -1, oy = (j & 1) ? sy : -sy, oz = (k & 1) ? sz : -sz;
+    T s = T(0);
+#pragma unroll
+    for (int c = 0; c < 2; c++)
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+#pragma unroll
+            for (int a = 0; a < 2; a++)
+                s = fma_t<T>(w[a] * w[b] * w[c], v[(a ? ox : 0) + (b ? oy : 0) + (c ? oz : 0)], s);
+    return s;
+}
+
+// Cells of one slot of a level: slot s = (row m, j, k), colour c at
+// i = 2m + ((c + j + k) mod 2).
+struct SlotAt {
+    int i0, j, k;  // i0: the red cell's i
+    __device__ __forceinline__ int i(int c) const { return i0 + (c ? 1 - 2 * (i0 & 1) : 0); }
+};
+__device__ __forceinline__ SlotAt slot_at(int s, int hx, int ny, unsigned long long mh, unsigned long long mhy) {
+    SlotAt t;
+    t.k = qdiv(s, mhy);
+    const int r = s - t.k * hx * ny;
+    t.j = qdiv(r, mh);
+    t.i0 = 2 * (r - t.j * hx) + ((t.j + t.k) & 1);
+    return t;
+}
+
+template <typename T, int NTH>
+__device__ __forceinline__ void small_fast(T *sm, const SmallLevels<T> &S, const T *__restrict__ f0,
+                                           T *__restrict__ x0, bool load_x) {
+    const int tid = threadIdx.x;
+    const bool direct = S.n > 1 && S.deep != nullptr;
+    const bool one = S.n == 1, three = S.n == 3, hasb = three || (S.n == 2 && !direct);
+    const FastLds o = fast_lds(S.n, direct, S.nx, S.ny, S.nz);
+    T *const xa = sm + o.xa, *const ra = sm + o.ra, *const xb = sm + o.xb, *const rbs = sm + o.rb,
+             *const xd = sm + o.xd, *const fd = sm + o.fd;
+    // level A: this thread's cells [slot][colour]; A's strides in the padded x and in r
+    const int nxa = S.nx[0], nya = S.ny[0], nxya = nxa * nya;
+    const int sya = nxa + 2, sza = sya * (nya + 2);
+    const int hxa = (nxa + 1) >> 1, slots = hxa * nya * S.nz[0];
+    int pa[2][2], ea[2][2];  // padded index, cell index (-1: none)
+    SlotAt ta[2];
+    T da[2][2], ya[2][2], fa[2][2], va[2][2];
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+        const int s = tid + u * NTH;
+        ta[u] = slot_at(s < slots ? s : 0, hxa, nya, S.mh[0], S.mhy[0]);
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+            const bool in = s < slots && ta[u].i(c) < nxa;
+            const int e = in ? (ta[u].k * nya + ta[u].j) * nxa + ta[u].i(c) : -1;
+            ea[u][c] = e;
+            da[u][c] = in ? S.d[0][e] : T(0);
+            ya[u][c] = in ? S.rd[0][e] : T(0);
+            fa[u][c] = in ? f0[e] : T(0);
+            va[u][c] = in && load_x ? x0[e] : T(0);
+            pa[u][c] = (ta[u].k + 1) * sza + (ta[u].j + 1) * sya + ta[u].i(c) + 1;
+        }
+    }
+    // level B: one slot; its first child in A's cells, padded parent rows
+    int pb[2] = {0, 0}, eb[2] = {0, 0}, cb[2] = {0, 0};
+    SlotAt tb{0, 0, 0};
+    T db[2] = {T(0), T(0)}, yb[2] = {T(0), T(0)}, fb[2] = {T(0), T(0)};
+    const int nxb = S.nx[hasb ? 1 : 0], nyb = S.ny[hasb ? 1 : 0], nxyb = nxb * nyb;
+    const int syb = nxb + 2, szb = syb * (nyb + 2);
+    if (hasb) {
+        const int hxb = (nxb + 1) >> 1;
+        if (tid < hxb * nyb * S.nz[1]) {
+            tb = slot_at(tid, hxb, nyb, S.mh[1], S.mhy[1]);
+#pragma unroll
+            for (int c = 0; c < 2; c++) {
+                const int i = tb.i(c);
+                if (i >= nxb) continue;
+                eb[c] = (tb.k * nyb + tb.j) * nxb + i;
+                pb[c] = (tb.k + 1) * szb + (tb.j + 1) * syb + i + 1;
+                cb[c] = 2 * tb.k * nxya + 2 * tb.j * nxa + 2 * i;
+                db[c] = S.d[1][eb[c]];
+                yb[c] = S.rd[1][eb[c]];
+            }
+        }
+    }
+    // level D: the matrix (its first rows in registers for a level of up to 64 cells)
+    const int ld = S.n - 1, nd = S.nx[ld] * S.ny[ld] * S.nz[ld];
+    const int q = tid & 15;
+    T mreg[4] = {T(0), T(0), T(0), T(0)};
+    const bool inreg = direct && nd <= 64 && NTH >= 1024;
+    if (inreg && (tid >> 4) < nd)
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            if (q + 16 * k < nd) mreg[k] = S.deep[(tid >> 4) * nd + q + 16 * k];
+    for (int e = tid; e < o.end; e += NTH) sm[e] = T(0);
+    __syncthreads();
+    if (load_x) {
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+#pragma unroll
+            for (int c = 0; c < 2; c++)
+                if (ea[u][c] >= 0) xa[pa[u][c]] = va[u][c];
+        __syncthreads();
+    }
+    const T h2a = S.h2[0], h2b = S.h2[1];
+    auto smooth_a = [&](int passes) {
+        for (int p = 0; p < passes; p++)
+#pragma unroll
+            for (int c = 0; c < 2; c++) {
+#pragma unroll
+                for (int u = 0; u < 2; u++)
+                    if (da[u][c] != T(0))
+                        xa[pa[u][c]] = relaxed<T>(xa + pa[u][c], sya, sza, h2a, fa[u][c], da[u][c], ya[u][c]);
+                __syncthreads();
+            }
+    };
+    auto smooth_b = [&](int passes) {
+        for (int p = 0; p < passes; p++)
+#pragma unroll
+            for (int c = 0; c < 2; c++) {
+                if (db[c] != T(0)) xb[pb[c]] = relaxed<T>(xb + pb[c], syb, szb, h2b, fb[c], db[c], yb[c]);
+                __syncthreads();
+            }
+    };
+    auto store = [&]() {
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+#pragma unroll
+            for (int c = 0; c < 2; c++)
+                if (ea[u][c] >= 0) x0[ea[u][c]] = xa[pa[u][c]];
+    };
+    // D's right-hand side from r of the level above (row and plane strides fx, fxy)
+    const int nxd = S.nx[ld], nyd = S.ny[ld], nxyd = nxd * nyd, syd = nxd + 2, szd = syd * (nyd + 2);
+    auto solve_d = [&](const T *r, int fx, int fxy) {
+        for (int e = tid; e < nd; e += NTH) {
+            const int k = qdiv(e, S.mxy[ld]), r2 = e - k * nxyd, j = qdiv(r2, S.mx[ld]), i = r2 - j * nxd;
+            fd[e] = S.d[ld][e] != T(0) ? coarse_rhs<T>(r, 2 * k * fxy + 2 * j * fx + 2 * i, fx, fxy) : T(0);
+        }
+        __syncthreads();
+        for (int row0 = 0; row0 < nd; row0 += NTH / 16) {
+            const int row = row0 + (tid >> 4);
+            T s = T(0);
+            if (row < nd) {
+                if (inreg) {
+#pragma unroll
+                    for (int k = 0; k < 4; k++)
+                        if (q + 16 * k < nd) s = fma_t<T>(mreg[k], fd[q + 16 * k], s);
+                } else {
+                    for (int j = q; j < nd; j += 16) s = fma_t<T>(S.deep[row * nd + j], fd[j], s);
+                }
+            }
+#pragma unroll
+            for (int w = 8; w > 0; w >>= 1) s += __shfl_xor(s, w);
+            if (row < nd && q == 0 && S.d[ld][row] != T(0)) {
+                const int k = qdiv(row, S.mxy[ld]), r2 = row - k * nxyd, j = qdiv(r2, S.mx[ld]), i = r2 - j * nxd;
+                xd[(k + 1) * szd + (j + 1) * syd + i + 1] = s;
+            }
+        }
+        __syncthreads();
+    };
+    if (one) {
+        smooth_a(S.n_coarse);
+        store();
+        return;
+    }
+    smooth_a(S.n_pre);
+#pragma unroll
+    for (int u = 0; u < 2; u++)
+#pragma unroll
+        for (int c = 0; c < 2; c++)
+            if (da[u][c] != T(0))
+                ra[ea[u][c]] = residual_at<T>(xa + pa[u][c], sya, sza, S.ih2[0], fa[u][c], da[u][c]);
+    __syncthreads();
+    if (hasb) {
+#pragma unroll
+        for (int c = 0; c < 2; c++)
+            if (db[c] != T(0)) fb[c] = coarse_rhs<T>(ra, cb[c], nxa, nxya);
+        if (three) {
+            for (int v = 0; v < S.n_cycles; v++) {  // (x starts at zero, later visits go on from it)
+                smooth_b(S.n_pre);
+#pragma unroll
+                for (int c = 0; c < 2; c++)
+                    if (db[c] != T(0)) rbs[eb[c]] = residual_at<T>(xb + pb[c], syb, szb, S.ih2[1], fb[c], db[c]);
+                __syncthreads();
+                solve_d(rbs, nxb, nxyb);
+#pragma unroll
+                for (int c = 0; c < 2; c++)
+                    if (db[c] != T(0)) {
+                        const int i = tb.i(c);
+                        xb[pb[c]] += interpolated<T>(
+                            xd + ((tb.k >> 1) + 1) * szd + ((tb.j >> 1) + 1) * syd + (i >> 1) + 1, i, tb.j, tb.k, syd, szd);
+                    }
+                __syncthreads();
+                smooth_b(S.n_post);
+            }
+        } else {
+            for (int v = 0; v < S.n_cycles; v++) smooth_b(S.n_coarse);
+        }
+    } else {
+        solve_d(ra, nxa, nxya);
+    }
+    {
+        const T *xc = hasb ? xb : xd;
+        const int syc = hasb ? syb : syd, szc = hasb ? szb : szd;
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+#pragma unroll
+            for (int c = 0; c < 2; c++)
+                if (da[u][c] != T(0)) {
+                    const int i = ta[u].i(c), j = ta[u].j, k = ta[u].k;
+                    xa[pa[u][c]] += interpolated<T>(xc + ((k >> 1) + 1) * szc + ((j >> 1) + 1) * syc + (i >> 1) + 1, i,
+                                                    j, k, syc, szc);
+                }
+        __syncthreads();
+    }
+    smooth_a(S.n_post);
+    store();
 }
 
 // One call MG(ls) for the levels held in S, all resident at `sm`: in LDS
@@ -362,13 +687,15 @@ __device__ void small_tail(T *sm, const SmallLevels<T> &S, const T *f0, T *x0, b
     // MG(l+1) from zero, prolong, post-smooth; the deepest level is relaxed.
     // visits: 3 bits per level (N_cycles <= 4).
     const int last = S.n - 1;
+    const bool direct = last > 0 && S.deep;  // (a single level may start from a non-zero iterate)
     unsigned visits = 0;
     int l = 0;
     bool down = true;
     while (true) {
         if (down) {
             if (l == last) {
-                smooth<T, NTH, WAVE>(level(l), S.n_coarse);
+                if (direct) deep_solve<T, NTH>(level(l), S.deep);
+                else smooth<T, NTH, WAVE>(level(l), S.n_coarse);
                 down = false;
                 continue;
             }
@@ -381,7 +708,7 @@ __device__ void small_tail(T *sm, const SmallLevels<T> &S, const T *f0, T *x0, b
         if (l == 0) break;
         const unsigned vc = ((visits >> (3 * l)) & 7u) + 1u;
         visits = (visits & ~(7u << (3 * l))) | (vc << (3 * l));
-        if ((int)vc < S.n_cycles) {
+        if ((int)vc < S.n_cycles && !(direct && l == last)) {  // (the matrix holds all its visits)
             down = true;
             continue;
         }

@@ -66,6 +66,10 @@ struct StopTest {
 struct OrderData {
     double *d = nullptr;   // operator diagonal (coarse levels), 0 off the active set
     float *d32 = nullptr;  // float copy for the mixed-precision inner cycle
+    double *rd = nullptr;     // first two levels of the one-workgroup call: 1/d (0 off the active set)
+    float *rd32 = nullptr;    // ... of the float diagonal
+    double *deep = nullptr;   // deepest level: matrix of its relaxation from zero (coarse_core.h)
+    float *deep32 = nullptr;  // ... float copy for the mixed-precision inner cycle
     int *tiles = nullptr;  // active tile ids (device)
     Seg *segs = nullptr;   // smoother work items (device)
     unsigned long long *pmask = nullptr;  // per item and plane activity masks (device)
@@ -254,6 +258,13 @@ void launch_rbgs2_prolong32(const Level &L, const OrderData &od, const Level &C,
 
 // -------- small levels in one workgroup (coarse.hip) --------
 size_t small_lds_bytes(const mg_hierarchy *H, int order, int ls, bool f32);
+// Whether that call takes the register path (coarse_core.h small_fast).
+bool small_fast_levels(const mg_hierarchy *H, int order, int ls);
+void launch_reciprocals(const Level &L, const OrderData &od, hipStream_t s);
+bool deep_matrix_fits(const Level &L);
+// Forms od.deep (and od.deep32, if allocated) of a deepest level: `passes`
+// red-black passes from zero as a matrix.
+void launch_deep_matrix(const Level &L, const OrderData &od, int passes, hipStream_t s);
 int small_init();  // usable dynamic LDS bytes of the one-workgroup kernel (0: none)
 // One call MG(ls) for the levels ls..deepest; x0 is level ls's iterate (in/out).
 void launch_small(const mg_hierarchy *H, int order, int ls, bool zero_start, const double *f0, double *x0,
