@@ -92,25 +92,41 @@ enum : int {
     K_SM0N,   // red-black pass, finest level, with the residual-norm partials of its input
 };
 
-// Block -> work item; false for grid padding and for patches this program
-// does not serve.
-__device__ __forceinline__ bool take(const BRef *__restrict__ refs, int count, const int *__restrict__ state,
-                                     int order, BRef &r) {
-    const int w = rb::xcd_item(blockIdx.x, gridDim.x);
+// Block -> work item r at position w of the launch's list; false for grid
+// padding and for patches this program does not serve.  map (may be null):
+// the positions of the items of the patches it serves, `count` of them.
+__device__ __forceinline__ bool take(const BRef *__restrict__ refs, const int *__restrict__ map, int count,
+                                     const int *__restrict__ state, int order, BRef &r, int &w) {
+    w = rb::xcd_item(blockIdx.x, gridDim.x);
     if (w >= count) return false;
+    if (map) w = map[w];
     r = refs[w];
     return state[r.lev / MAXL] == order;
+}
+
+// A launch walks the items of every patch; once some patches have stopped or
+// follow the other boundary order, their blocks only read their state word and
+// leave, yet a finest launch of dead blocks still took 15-22 us of its 58 (96
+// patches).  Each span copies the positions of one patch's items of one launch
+// into that launch's map, so that its grid holds live items only.
+struct Span {
+    int src, dst, n;
+};
+__global__ void kb_spans(const Span *__restrict__ spans, int *__restrict__ map) {
+    const Span s = spans[blockIdx.x];
+    for (int i = threadIdx.x; i < s.n; i += blockDim.x) map[s.dst + i] = s.src + i;
 }
 
 // NORMIN: the pass also writes its item's partial of the residual norm of
 // its input to part[poff + position] (the single-grid norm-forming pass).
 template <bool FINE, int SEGZ, bool PRO, bool NORMIN = false>
-__global__ __launch_bounds__(rb::NT, NORMIN ? 4 : 5) void kb_smooth(const BRef *__restrict__ refs, int count,
+__global__ __launch_bounds__(rb::NT, NORMIN ? 4 : 5) void kb_smooth(const BRef *__restrict__ refs, const int *__restrict__ map, int count,
                                                        const BLev *__restrict__ lev, const int *__restrict__ state,
                                                        int order, double *__restrict__ part = nullptr, int poff = 0) {
     __shared__ rb::RbgsLds<double, FINE, PRO> lds;
     BRef r;
-    if (!take(refs, count, state, order, r)) return;
+    int w;
+    if (!take(refs, map, count, state, order, r, w)) return;
     const BLev &L = lev[r.lev];
     const int idx = r.w & IDX_MASK, sel = r.w >> WBITS, a = sel & 1;
     const double sq = rb::rbgs_item<double, FINE, SEGZ, PRO, NORMIN>(
@@ -118,17 +134,18 @@ __global__ __launch_bounds__(rb::NT, NORMIN ? 4 : 5) void kb_smooth(const BRef *
         L.pm + (size_t)idx * (SEGZ + 4), PRO ? L.cx[(sel >> 2) & 1] : nullptr, L.cnx, L.cny, L.cnz, L.ih2);
     if constexpr (NORMIN) {
         const double t = tr::block_sum(sq);
-        if (threadIdx.x == 0) part[poff + rb::xcd_item(blockIdx.x, gridDim.x)] = t;
+        if (threadIdx.x == 0) part[poff + w] = t;
     }
 }
 
 template <int MODE>
-__global__ __launch_bounds__(tr::NT) void kb_residual(const BRef *__restrict__ refs, int count,
+__global__ __launch_bounds__(tr::NT) void kb_residual(const BRef *__restrict__ refs, const int *__restrict__ map, int count,
                                                       const BLev *__restrict__ lev, const int *__restrict__ state,
                                                       int order, double *__restrict__ part, int poff = 0) {
     __shared__ tr::ResLds<double> lds;
     BRef r;
-    if (!take(refs, count, state, order, r)) return;
+    int w;
+    if (!take(refs, map, count, state, order, r, w)) return;
     const BLev &L = lev[r.lev];
     const int idx = r.w & IDX_MASK, sel = r.w >> WBITS;
     constexpr bool RS = MODE == tr::RM_RESTRICT;
@@ -138,15 +155,16 @@ __global__ __launch_bounds__(tr::NT) void kb_residual(const BRef *__restrict__ r
         RS ? L.cf : nullptr, nullptr, nullptr, nullptr);
     if constexpr (!RS) {
         const double t = tr::block_sum(sq);
-        if (threadIdx.x == 0) part[poff + rb::xcd_item(blockIdx.x, gridDim.x)] = t;
+        if (threadIdx.x == 0) part[poff + w] = t;
     }
 }
 
-__global__ __launch_bounds__(tr::NT) void kb_restrict(const BRef *__restrict__ refs, int count,
+__global__ __launch_bounds__(tr::NT) void kb_restrict(const BRef *__restrict__ refs, const int *__restrict__ map, int count,
                                                       const BLev *__restrict__ lev, const int *__restrict__ state,
                                                       int order) {
     BRef r;
-    if (!take(refs, count, state, order, r)) return;
+    int w;
+    if (!take(refs, map, count, state, order, r, w)) return;
     const BLev &L = lev[r.lev];
     const int idx = r.w & IDX_MASK, sel = r.w >> WBITS;
     const tr::TileCoord t = tr::tile_cell(L.ctiles[idx / TZ], idx % TZ, L.cntx, L.cnty, L.cnx, L.cny, L.cnz);
@@ -154,12 +172,12 @@ __global__ __launch_bounds__(tr::NT) void kb_restrict(const BRef *__restrict__ r
                                      L.cf);
 }
 
-__global__ __launch_bounds__(NTS) void kb_small(const BRef *__restrict__ refs, int count,
+__global__ __launch_bounds__(NTS) void kb_small(const BRef *__restrict__ refs, const int *__restrict__ map, int count,
                                                 const BLev *__restrict__ lev, const int *__restrict__ state,
                                                 int order, const small::SmallLevels<double> *__restrict__ sl) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     if ((int)blockIdx.x >= count) return;
-    const BRef r = refs[blockIdx.x];
+    const BRef r = refs[map ? map[blockIdx.x] : blockIdx.x];
     const int p = r.lev / MAXL;
     if (state[p] != order) return;
     const BLev &L = lev[r.lev];
@@ -192,24 +210,26 @@ __global__ __launch_bounds__(1024) void kb_finalize(const int *__restrict__ firs
     if (threadIdx.x == 0) out[2 * p + slot] = sm[0];
 }
 
-__global__ __launch_bounds__(tr::NT) void kb_fold(const BRef *__restrict__ refs, int count,
+__global__ __launch_bounds__(tr::NT) void kb_fold(const BRef *__restrict__ refs, const int *__restrict__ map, int count,
                                                   const BLev *__restrict__ lev, const int *__restrict__ state,
                                                   int order, const double *const *__restrict__ rho,
                                                   const double *const *__restrict__ dir,
                                                   const double *const *__restrict__ phi) {
     BRef r;
-    if (!take(refs, count, state, order, r)) return;
+    int w;
+    if (!take(refs, map, count, state, order, r, w)) return;
     const BLev &L = lev[r.lev];
     const int p = r.lev / MAXL, idx = r.w & IDX_MASK;
     tr::fold_cell(tr::tile_cell(L.tiles[idx / TZ], idx % TZ, L.ntx, L.nty, L.nx, L.ny, L.nz), L.nx, L.ny, L.ih2,
                   L.code, rho[p], dir[p], phi[p], L.f, L.x[0]);
 }
 
-__global__ __launch_bounds__(tr::NT) void kb_store(const BRef *__restrict__ refs, int count,
+__global__ __launch_bounds__(tr::NT) void kb_store(const BRef *__restrict__ refs, const int *__restrict__ map, int count,
                                                    const BLev *__restrict__ lev, const int *__restrict__ state,
                                                    int order, double *const *__restrict__ phi) {
     BRef r;
-    if (!take(refs, count, state, order, r)) return;
+    int w;
+    if (!take(refs, map, count, state, order, r, w)) return;
     const BLev &L = lev[r.lev];
     const int p = r.lev / MAXL, idx = r.w & IDX_MASK, sel = r.w >> WBITS;
     tr::store_cell(tr::tile_cell(L.tiles[idx / TZ], idx % TZ, L.ntx, L.nty, L.nx, L.ny, L.nz), L.nx, L.ny, L.code,
@@ -485,9 +505,19 @@ struct mg_batch {
     struct Prog {
         std::vector<mg::Launch> k;
         hipGraphExec_t exec = nullptr;
+        // direct launches: each launch's item ranges by patch, the patches the
+        // launches' maps hold now (empty: none) and their live items
+        struct Range {
+            int launch, patch, first, n;
+        };
+        std::vector<Range> ranges;
+        std::vector<char> mapped;
+        std::vector<int> live;
+        mg::Span *spans = nullptr, *pin_spans = nullptr;  // device, pinned: one per range
     };
     Prog begin, end, pre, cycle[3];
     mg::BRef *refs = nullptr;                    // device, all programs' work items
+    int *map = nullptr;                          // device, as long as refs: each launch's live positions
     mg::BLev *lev[3] = {};                       // device [n * MAXL] per order
     mg::small::SmallLevels<double> *sl[3] = {};  // device [n] per order
     int *state[4] = {};                          // device [n]: [0] every patch 2, [o] this cycle's order-o patches,
@@ -932,6 +962,21 @@ bool build_programs(mg_batch *B) {
         }
     }
     B->refs = upload(B, refs);
+    B->map = balloc<int>(B, refs.size());
+    for (mg_batch::Prog *g : {&B->pre, &B->cycle[1], &B->cycle[2]}) {
+        for (size_t i = 0; i < g->k.size(); i++) {
+            const Launch &k = g->k[i];
+            if (k.kind == K_FIN) continue;
+            for (int j = 0; j < k.count;) {  // a launch lists its patches one after the other
+                const int p = refs[k.first + j].lev / MAXL, j0 = j;
+                while (j < k.count && refs[k.first + j].lev / MAXL == p) j++;
+                g->ranges.push_back({(int)i, p, j0, j - j0});
+            }
+        }
+        g->spans = balloc<Span>(B, g->ranges.size());
+        BHIP(hipHostMalloc((void **)&g->pin_spans, std::max<size_t>(1, g->ranges.size()) * sizeof(Span),
+                           hipHostMallocDefault));
+    }
     B->nfirst = upload(B, first);
     B->ncnt = upload(B, cnt);
     B->nfirst1 = upload(B, first1);
@@ -1025,46 +1070,77 @@ void build_batch(mg_batch *B, const int8_t *const *masks, const int32_t *dims, c
     BHIP(hipStreamSynchronize(B->stream));
 }
 
-void launch(mg_batch *B, const Launch &k, int order, const int *state) {
+// live: the number of items in the launch's map, -1 for all of its items
+void launch(mg_batch *B, const Launch &k, int order, const int *state, int live = -1) {
     const BRef *r = B->refs + k.first;
+    const int *map = live < 0 ? nullptr : B->map + k.first;
+    const int count = live < 0 ? k.count : live;
     const BLev *lev = B->lev[order];
     hipStream_t s = B->stream;
-    const unsigned g = grid8(k.count);
+    const unsigned g = grid8(count);
     constexpr int NT = rb::NT;
     switch (k.kind) {
-        case K_SM0: kb_smooth<true, FINE_Z, false><<<g, NT, 0, s>>>(r, k.count, lev, state, order); break;
-        case K_SM0P: kb_smooth<true, FINE_Z, true><<<g, NT, 0, s>>>(r, k.count, lev, state, order); break;
-        case K_SM1: kb_smooth<false, SEGZ_COARSE1, false><<<g, NT, 0, s>>>(r, k.count, lev, state, order); break;
-        case K_SM1P: kb_smooth<false, SEGZ_COARSE1, true><<<g, NT, 0, s>>>(r, k.count, lev, state, order); break;
-        case K_SM2: kb_smooth<false, SEGZ_COARSE, false><<<g, NT, 0, s>>>(r, k.count, lev, state, order); break;
-        case K_SM2P: kb_smooth<false, SEGZ_COARSE, true><<<g, NT, 0, s>>>(r, k.count, lev, state, order); break;
+        case K_SM0: kb_smooth<true, FINE_Z, false><<<g, NT, 0, s>>>(r, map, count, lev, state, order); break;
+        case K_SM0P: kb_smooth<true, FINE_Z, true><<<g, NT, 0, s>>>(r, map, count, lev, state, order); break;
+        case K_SM1: kb_smooth<false, SEGZ_COARSE1, false><<<g, NT, 0, s>>>(r, map, count, lev, state, order); break;
+        case K_SM1P: kb_smooth<false, SEGZ_COARSE1, true><<<g, NT, 0, s>>>(r, map, count, lev, state, order); break;
+        case K_SM2: kb_smooth<false, SEGZ_COARSE, false><<<g, NT, 0, s>>>(r, map, count, lev, state, order); break;
+        case K_SM2P: kb_smooth<false, SEGZ_COARSE, true><<<g, NT, 0, s>>>(r, map, count, lev, state, order); break;
         case K_RES0:
-            kb_residual<tr::RM_RESTRICT><<<g, NT, 0, s>>>(r, k.count, lev, state, order, nullptr);
+            kb_residual<tr::RM_RESTRICT><<<g, NT, 0, s>>>(r, map, count, lev, state, order, nullptr);
             break;
-        case K_RESC: kb_restrict<<<g, NT, 0, s>>>(r, k.count, lev, state, order); break;
-        case K_SMALL: kb_small<<<k.count, NTS, k.lds, s>>>(r, k.count, lev, state, order, B->sl[order]); break;
+        case K_RESC: kb_restrict<<<g, NT, 0, s>>>(r, map, count, lev, state, order); break;
+        case K_SMALL: kb_small<<<count, NTS, k.lds, s>>>(r, map, count, lev, state, order, B->sl[order]); break;
         case K_NORM:
-            kb_residual<tr::RM_NORM><<<g, NT, 0, s>>>(r, k.count, lev, state, order, B->part, k.poff);
+            kb_residual<tr::RM_NORM><<<g, NT, 0, s>>>(r, map, count, lev, state, order, B->part, k.poff);
             break;
         case K_SM0N:
-            kb_smooth<true, FINE_Z, false, true><<<g, NT, 0, s>>>(r, k.count, lev, state, order, B->part, k.poff);
+            kb_smooth<true, FINE_Z, false, true><<<g, NT, 0, s>>>(r, map, count, lev, state, order, B->part, k.poff);
             break;
         case K_FIN:
             kb_finalize<<<B->n, 1024, 0, s>>>(k.lay ? B->nfirst1 : B->nfirst, k.lay ? B->ncnt1 : B->ncnt, B->n,
                                               B->part, B->norm2, k.slot, state, order);
             break;
         case K_FOLD:
-            kb_fold<<<g, NT, 0, s>>>(r, k.count, lev, state, order, B->in_rho, B->in_dir,
+            kb_fold<<<g, NT, 0, s>>>(r, map, count, lev, state, order, B->in_rho, B->in_dir,
                                      (const double *const *)B->in_phi);
             break;
-        case K_STORE: kb_store<<<g, NT, 0, s>>>(r, k.count, lev, state, order, B->in_phi); break;
+        case K_STORE: kb_store<<<g, NT, 0, s>>>(r, map, count, lev, state, order, B->in_phi); break;
         default: break;
     }
 }
 
+// The program for the patches marked in `on` (the ones `state` gives to
+// `order`): launches of live items only.
+void run_live(mg_batch *B, mg_batch::Prog &g, int order, const int *state, const std::vector<char> &on) {
+    if (g.mapped != on) {
+        g.live.assign(g.k.size(), 0);
+        int ns = 0;
+        for (const auto &r : g.ranges)
+            if (on[r.patch]) {
+                g.pin_spans[ns++] = Span{r.first, g.k[r.launch].first + g.live[r.launch], r.n};
+                g.live[r.launch] += r.n;
+            }
+        g.mapped = on;
+        if (ns > 0) {
+            BHIP(hipMemcpyAsync(g.spans, g.pin_spans, ns * sizeof(Span), hipMemcpyHostToDevice, B->stream));
+            kb_spans<<<ns, 256, 0, B->stream>>>(g.spans, B->map);
+        }
+    }
+    for (size_t i = 0; i < g.k.size(); i++) {
+        const Launch &k = g.k[i];
+        if (k.kind == K_FIN || g.live[i] == k.count) launch(B, k, order, state);
+        else if (g.live[i] > 0) launch(B, k, order, state, g.live[i]);
+    }
+    BHIP(hipGetLastError());
+}
+
 // One program on the batch stream, replayed from its captured graph when
-// the options ask for graphs.
-void run_program(mg_batch *B, mg_batch::Prog &g, int order, const int *state) {
+// the options ask for graphs.  on (may be null): the patches it serves; direct
+// launches then leave out the others' items.
+void run_program(mg_batch *B, mg_batch::Prog &g, int order, const int *state,
+                 const std::vector<char> *on = nullptr) {
+    if (!B->opt.use_graph && on) return run_live(B, g, order, state, *on);
     if (!B->opt.use_graph) {
         for (const Launch &k : g.k) launch(B, k, order, state);
         BHIP(hipGetLastError());
@@ -1293,15 +1369,19 @@ mg_status solve_batch_phased(mg_batch *B, const double *const *rho, double *cons
     // patch that stops keeps its iterate in buffer 0.  The first round's norm
     // is the initial one, already taken.
     std::vector<int> run;
+    std::vector<char> on(n);
     for (int round = 0;; round++) {
         run.clear();
         for (int p = 0; p < n; p++)
             if (S[p].active) run.push_back(p);
         if (run.empty()) break;
         int *sp = B->pin_state;  // slot 0 of the pinned staging: the pre program's patches
-        for (int p = 0; p < n; p++) sp[p] = S[p].active ? 2 : 0;
+        for (int p = 0; p < n; p++) {
+            sp[p] = S[p].active ? 2 : 0;
+            on[p] = S[p].active;
+        }
         BHIP(hipMemcpyAsync(B->state[3], sp, n * sizeof(int), hipMemcpyHostToDevice, s));
-        run_program(B, B->pre, 2, B->state[3]);
+        run_program(B, B->pre, 2, B->state[3], &on);
         BHIP(hipMemcpyAsync(B->norm2_host, B->norm2, 2 * n * sizeof(double), hipMemcpyDeviceToHost, s));
         BHIP(hipStreamSynchronize(s));
         if (round > 0) {
@@ -1319,11 +1399,12 @@ mg_status solve_batch_phased(mg_batch *B, const double *const *rho, double *cons
             bool use = false;
             for (int p = 0; p < n; p++) {
                 sv[p] = (S[p].active && S[p].order == o) ? o : 0;
+                on[p] = sv[p] != 0;
                 use |= sv[p] != 0;
             }
             if (!use) continue;
             BHIP(hipMemcpyAsync(B->state[o], sv, n * sizeof(int), hipMemcpyHostToDevice, s));
-            run_program(B, B->cycle[o], o, B->state[o]);
+            run_program(B, B->cycle[o], o, B->state[o], &on);
         }
     }
     run_program(B, B->end, 2, B->state[0]);
@@ -1390,6 +1471,8 @@ void mg_destroy_batch(mg_batch *B) {
     if (B->norm2_host) (void)hipHostFree(B->norm2_host);
     if (B->pin_ptrs) (void)hipHostFree((void *)B->pin_ptrs);
     if (B->pin_state) (void)hipHostFree(B->pin_state);
+    for (mg_batch::Prog *g : {&B->pre, &B->cycle[1], &B->cycle[2]})
+        if (g->pin_spans) (void)hipHostFree(g->pin_spans);
     if (B->perr_host) (void)hipHostFree(B->perr_host);
     if (B->ev0) (void)hipEventDestroy(B->ev0);
     if (B->ev1) (void)hipEventDestroy(B->ev1);
