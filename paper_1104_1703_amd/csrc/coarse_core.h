@@ -316,36 +316,41 @@ __device__ void prolong_from(const Lv<T> &L, const Lv<T> &C) {
 }
 
 // ---- the call on one to three levels with the cells in registers ----
-// One CU issues the whole call, so its instruction count decides: a phase of
-// the general path spends most of its instructions on cell indices, box-edge
-// selects and reciprocals, once per phase and level.  Here each thread owns the
-// same cells throughout (up to two of each colour on the first level A, one of
-// each on the second, B), holds their diagonal, its reciprocal (formed once
-// per hierarchy) and right-hand side in registers, and x lies in LDS with a
-// ring of zeros around the box, so a relaxation is six reads, the sum and the
-// quotient.  The deepest level D is the matrix of deep_solve.  Every value is
-// formed by the expression, in the order, of the general path (bit for bit).
-// Levels A, D or A, B (relaxed n_coarse times, no matrix) or A, B, D, or A
-// alone, relaxed n_coarse times.
+// One CU issues the whole call, so its instructions and LDS cycles decide: a
+// phase of the general path spends most of its instructions on cell indices,
+// box-edge selects and reciprocals, once per phase and level, and its x rows
+// put the cells of one colour 16 bytes apart (two-way bank conflicts).  Here
+// each thread owns the same cells throughout (up to two of each colour on the
+// first level A, one of each on the second, B), holds their diagonal, its
+// reciprocal (formed once per hierarchy) and right-hand side in registers, and
+// x lies in LDS inside a ring of zeros, A's colours in arrays of their own, so a
+// relaxation is six conflict-free reads, the sum and the quotient.  The deepest
+// level D is the matrix of deep_solve.  Every value is formed by the expression,
+// in the order, of the general path (bit for bit).
+// Levels A, D or A, B (relaxed n_coarse times, no matrix) or A, B, D; A alone,
+// relaxed n_coarse times, is small_one, with up to four cells of a colour per
+// thread.
 // 16^3 + 8^3 + 4^3: 14 us a call at a 32^3 or 64^3 finest level and 17 us at
 // 256^3, against 25 and 29 us in the general path (30 and 32 us with the
-// deepest level relaxed); in a W-cycle 17 against 57 us.  The general
-// path stays for boxes above 4096 cells, more than three levels and blocks of
-// fewer threads.
+// deepest level relaxed); in a W-cycle 17 against 57 us; 17 x 9 x 13 relaxed 32
+// times 22 against 25 us, 6 x 32 x 32 in a batch 35 against 99 us.  The general
+// path stays for larger boxes, more than three levels and blocks of fewer
+// threads.
 struct FastLds {  // offsets in elements
-    int xa, ra, xb, rb, xd, fd, end;
+    int ra, xb, rb, xd, fd, end;
 };
 
 __host__ __device__ constexpr int padded(int nx, int ny, int nz) { return (nx + 2) * (ny + 2) * (nz + 2); }
+// one colour of a level with its ring
+__host__ __device__ constexpr int padded_half(int nx, int ny, int nz) { return padded((nx + 1) >> 1, ny, nz); }
 
-// Whether levels with these dims can take the fast path with NTH threads, and
-// the LDS it needs.  direct: the deepest level has its matrix.
+// The LDS of the levels with these dims (A's colours come first).  direct: the
+// deepest level has its matrix.
 __host__ __device__ inline FastLds fast_lds(int n, bool direct, const int *nx, const int *ny, const int *nz) {
     FastLds o{};
     const bool hasb = n == 3 || (n == 2 && !direct);
     const int d = n - 1;
-    o.xa = 0;
-    o.ra = padded(nx[0], ny[0], nz[0]);
+    o.ra = 2 * padded_half(nx[0], ny[0], nz[0]);
     o.xb = o.ra + (n > 1 ? nx[0] * ny[0] * nz[0] : 0);
     o.rb = o.xb + (hasb ? padded(nx[1], ny[1], nz[1]) : 0);
     o.xd = o.rb + (n == 3 ? nx[1] * ny[1] * nz[1] : 0);
@@ -353,9 +358,10 @@ __host__ __device__ inline FastLds fast_lds(int n, bool direct, const int *nx, c
     o.end = o.fd + (direct ? nx[d] * ny[d] * nz[d] : 0);
     return o;
 }
+// Whether blocks of nth threads can run these levels this way.
 inline bool fast_fits(int n, bool direct, const int *nx, const int *ny, const int *nz, int nth) {
     if (n < 1 || n > 3 || (n == 3 && !direct)) return false;
-    if (((nx[0] + 1) >> 1) * ny[0] * nz[0] > 2 * nth) return false;
+    if (((nx[0] + 1) >> 1) * ny[0] * nz[0] > (n == 1 ? 4 : 2) * nth) return false;
     return n == 1 || (n == 2 && direct) || ((nx[1] + 1) >> 1) * ny[1] * nz[1] <= nth;
 }
 
@@ -404,55 +410,153 @@ __device__ __forceinline__ T interpolated(const T *v, int i, int j, int k, int s
 // Cells of one slot of a level: slot s = (row m, j, k), colour c at
 // i = 2m + ((c + j + k) mod 2).
 struct SlotAt {
-    int i0, j, k;  // i0: the red cell's i
-    __device__ __forceinline__ int i(int c) const { return i0 + (c ? 1 - 2 * (i0 & 1) : 0); }
+    int m, j, k;
+    __device__ __forceinline__ int i(int c) const { return 2 * m + ((c + j + k) & 1); }
 };
 __device__ __forceinline__ SlotAt slot_at(int s, int hx, int ny, unsigned long long mh, unsigned long long mhy) {
     SlotAt t;
     t.k = qdiv(s, mhy);
     const int r = s - t.k * hx * ny;
     t.j = qdiv(r, mh);
-    t.i0 = 2 * (r - t.j * hx) + ((t.j + t.k) & 1);
+    t.m = r - t.j * hx;
     return t;
+}
+
+// Level A: this thread's U slots, tid + u NTH, both colours.  Colour c of slot
+// (m, j, k) is element (k + 1) sz + (j + 1) sy + m + 1 of the array x[c]; its x
+// neighbours are the other colour's slots m - 1 + q and m + q of the row, q the
+// cell's i mod 2 (for red, (j + k) mod 2; for black the other), its y and z
+// neighbours the same m of the neighbouring rows.
+template <typename T, int NTH, int U>
+struct Finest {
+    T *x[2];
+    int nx, ny, hx, sy, sz, slots;
+    T h2;
+    int p[U];
+    SlotAt at[U];
+    T d[U][2], y[U][2], f[U][2];
+
+    __device__ __forceinline__ void init(T *sm, const SmallLevels<T> &S) {
+        nx = S.nx[0], ny = S.ny[0], hx = (nx + 1) >> 1, sy = hx + 2, sz = sy * (ny + 2);
+        slots = hx * ny * S.nz[0];
+        h2 = S.h2[0];
+        x[0] = sm;
+        x[1] = sm + sz * (S.nz[0] + 2);
+    }
+    __device__ __forceinline__ int cell(int u, int c) const {  // -1: none
+        const int i = at[u].i(c);
+        return (int)threadIdx.x + u * NTH < slots && i < nx ? (at[u].k * ny + at[u].j) * nx + i : -1;
+    }
+    // diagonals, reciprocals and right-hand sides; v: the start (0 unless load_x)
+    __device__ __forceinline__ void load(const SmallLevels<T> &S, const T *__restrict__ f0, const T *__restrict__ x0,
+                                         bool load_x, T (&v)[U][2]) {
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int s = (int)threadIdx.x + u * NTH;
+            at[u] = slot_at(s < slots ? s : 0, hx, ny, S.mh[0], S.mhy[0]);
+            p[u] = (at[u].k + 1) * sz + (at[u].j + 1) * sy + at[u].m + 1;
+#pragma unroll
+            for (int c = 0; c < 2; c++) {
+                const int e = cell(u, c);
+                d[u][c] = e >= 0 ? S.d[0][e] : T(0);
+                y[u][c] = e >= 0 ? S.rd[0][e] : T(0);
+                f[u][c] = e >= 0 ? f0[e] : T(0);
+                v[u][c] = e >= 0 && load_x ? x0[e] : T(0);
+            }
+        }
+    }
+    __device__ __forceinline__ T sum(int u, int c) const {
+#pragma clang fp contract(off)
+        const T *o = x[c ^ 1];
+        const int l = p[u] - 1 + ((c + at[u].j + at[u].k) & 1);
+        return (o[l] + o[l + 1]) + (o[p[u] - sy] + o[p[u] + sy]) + (o[p[u] - sz] + o[p[u] + sz]);
+    }
+    __device__ __forceinline__ T relaxed(int u, int c) const {
+#pragma clang fp contract(off)
+        return rb::div_small<T>(sum(u, c) - h2 * f[u][c], d[u][c], y[u][c]);
+    }
+    __device__ __forceinline__ void smooth(int passes) {
+        for (int n = 0; n < passes; n++)
+#pragma unroll
+            for (int c = 0; c < 2; c++) {
+#pragma unroll
+                for (int u = 0; u < U; u++)
+                    if (d[u][c] != T(0)) x[c][p[u]] = relaxed(u, c);
+                __syncthreads();
+            }
+    }
+    __device__ __forceinline__ T residual(int u, int c, T ih2) const {
+        return fma_t<T>(fma_t<T>(-d[u][c], x[c][p[u]], sum(u, c)), ih2, -f[u][c]);
+    }
+    __device__ __forceinline__ void set(const T (&v)[U][2]) {
+#pragma unroll
+        for (int u = 0; u < U; u++)
+#pragma unroll
+            for (int c = 0; c < 2; c++)
+                if (cell(u, c) >= 0) x[c][p[u]] = v[u][c];
+    }
+    __device__ __forceinline__ void store(T *__restrict__ x0) const {
+#pragma unroll
+        for (int u = 0; u < U; u++)
+#pragma unroll
+            for (int c = 0; c < 2; c++) {
+                const int e = cell(u, c);
+                if (e >= 0) x0[e] = x[c][p[u]];
+            }
+    }
+};
+
+// A single level, relaxed n_coarse times.
+template <typename T, int NTH, int U>
+__device__ __forceinline__ void small_one(T *sm, const SmallLevels<T> &S, const T *__restrict__ f0,
+                                          T *__restrict__ x0, bool load_x) {
+    Finest<T, NTH, U> A;
+    T v[U][2];
+    A.init(sm, S);
+    A.load(S, f0, x0, load_x, v);
+    for (int e = threadIdx.x; e < 2 * A.sz * (S.nz[0] + 2); e += NTH) sm[e] = T(0);
+    __syncthreads();
+    if (load_x) {
+        A.set(v);
+        __syncthreads();
+    }
+    A.smooth(S.n_coarse);
+    A.store(x0);
 }
 
 template <typename T, int NTH>
 __device__ __forceinline__ void small_fast(T *sm, const SmallLevels<T> &S, const T *__restrict__ f0,
                                            T *__restrict__ x0, bool load_x) {
+    if (S.n == 1) {
+        if (((S.nx[0] + 1) >> 1) * S.ny[0] * S.nz[0] <= 2 * NTH) small_one<T, NTH, 2>(sm, S, f0, x0, load_x);
+        else small_one<T, NTH, 4>(sm, S, f0, x0, load_x);
+        return;
+    }
+    constexpr int U = 2;
     const int tid = threadIdx.x;
-    const bool direct = S.n > 1 && S.deep != nullptr;
-    const bool one = S.n == 1, three = S.n == 3, hasb = three || (S.n == 2 && !direct);
+    const bool direct = S.deep != nullptr;
+    const bool three = S.n == 3, hasb = three || !direct;
     const FastLds o = fast_lds(S.n, direct, S.nx, S.ny, S.nz);
-    T *const xa = sm + o.xa, *const ra = sm + o.ra, *const xb = sm + o.xb, *const rbs = sm + o.rb,
-             *const xd = sm + o.xd, *const fd = sm + o.fd;
-    // level A: this thread's cells [slot][colour]; A's strides in the padded x and in r
-    const int nxa = S.nx[0], nya = S.ny[0], nxya = nxa * nya;
-    const int sya = nxa + 2, sza = sya * (nya + 2);
-    const int hxa = (nxa + 1) >> 1, slots = hxa * nya * S.nz[0];
-    int pa[2][2], ea[2][2];  // padded index, cell index (-1: none)
-    SlotAt ta[2];
-    T da[2][2], ya[2][2], fa[2][2], va[2][2];
-#pragma unroll
-    for (int u = 0; u < 2; u++) {
-        const int s = tid + u * NTH;
-        ta[u] = slot_at(s < slots ? s : 0, hxa, nya, S.mh[0], S.mhy[0]);
-#pragma unroll
-        for (int c = 0; c < 2; c++) {
-            const bool in = s < slots && ta[u].i(c) < nxa;
-            const int e = in ? (ta[u].k * nya + ta[u].j) * nxa + ta[u].i(c) : -1;
-            ea[u][c] = e;
-            da[u][c] = in ? S.d[0][e] : T(0);
-            ya[u][c] = in ? S.rd[0][e] : T(0);
-            fa[u][c] = in ? f0[e] : T(0);
-            va[u][c] = in && load_x ? x0[e] : T(0);
-            pa[u][c] = (ta[u].k + 1) * sza + (ta[u].j + 1) * sya + ta[u].i(c) + 1;
+    T *const ra = sm + o.ra, *const xb = sm + o.xb, *const rbs = sm + o.rb, *const xd = sm + o.xd,
+             *const fd = sm + o.fd;
+    Finest<T, NTH, U> A;
+    {
+        T v[U][2];
+        A.init(sm, S);
+        A.load(S, f0, x0, load_x, v);
+        for (int e = tid; e < o.end; e += NTH) sm[e] = T(0);
+        __syncthreads();
+        if (load_x) {
+            A.set(v);
+            __syncthreads();
         }
     }
-    // level B: one slot; its first child in A's cells, padded parent rows
+    const int nxa = A.nx, nxya = A.nx * A.ny;
+    // level B: one slot; its first child in A's cells
     int pb[2] = {0, 0}, eb[2] = {0, 0}, cb[2] = {0, 0};
     SlotAt tb{0, 0, 0};
     T db[2] = {T(0), T(0)}, yb[2] = {T(0), T(0)}, fb[2] = {T(0), T(0)};
-    const int nxb = S.nx[hasb ? 1 : 0], nyb = S.ny[hasb ? 1 : 0], nxyb = nxb * nyb;
+    const int nxb = S.nx[1], nyb = S.ny[1], nxyb = nxb * nyb;
     const int syb = nxb + 2, szb = syb * (nyb + 2);
     if (hasb) {
         const int hxb = (nxb + 1) >> 1;
@@ -470,7 +574,7 @@ __device__ __forceinline__ void small_fast(T *sm, const SmallLevels<T> &S, const
             }
         }
     }
-    // level D: the matrix (its first rows in registers for a level of up to 64 cells)
+    // level D: the matrix (in registers for a level of up to 64 cells)
     const int ld = S.n - 1, nd = S.nx[ld] * S.ny[ld] * S.nz[ld];
     const int q = tid & 15;
     T mreg[4] = {T(0), T(0), T(0), T(0)};
@@ -479,42 +583,14 @@ __device__ __forceinline__ void small_fast(T *sm, const SmallLevels<T> &S, const
 #pragma unroll
         for (int k = 0; k < 4; k++)
             if (q + 16 * k < nd) mreg[k] = S.deep[(tid >> 4) * nd + q + 16 * k];
-    for (int e = tid; e < o.end; e += NTH) sm[e] = T(0);
-    __syncthreads();
-    if (load_x) {
-#pragma unroll
-        for (int u = 0; u < 2; u++)
-#pragma unroll
-            for (int c = 0; c < 2; c++)
-                if (ea[u][c] >= 0) xa[pa[u][c]] = va[u][c];
-        __syncthreads();
-    }
-    const T h2a = S.h2[0], h2b = S.h2[1];
-    auto smooth_a = [&](int passes) {
-        for (int p = 0; p < passes; p++)
-#pragma unroll
-            for (int c = 0; c < 2; c++) {
-#pragma unroll
-                for (int u = 0; u < 2; u++)
-                    if (da[u][c] != T(0))
-                        xa[pa[u][c]] = relaxed<T>(xa + pa[u][c], sya, sza, h2a, fa[u][c], da[u][c], ya[u][c]);
-                __syncthreads();
-            }
-    };
+    const T h2b = S.h2[1];
     auto smooth_b = [&](int passes) {
-        for (int p = 0; p < passes; p++)
+        for (int n = 0; n < passes; n++)
 #pragma unroll
             for (int c = 0; c < 2; c++) {
                 if (db[c] != T(0)) xb[pb[c]] = relaxed<T>(xb + pb[c], syb, szb, h2b, fb[c], db[c], yb[c]);
                 __syncthreads();
             }
-    };
-    auto store = [&]() {
-#pragma unroll
-        for (int u = 0; u < 2; u++)
-#pragma unroll
-            for (int c = 0; c < 2; c++)
-                if (ea[u][c] >= 0) x0[ea[u][c]] = xa[pa[u][c]];
     };
     // D's right-hand side from r of the level above (row and plane strides fx, fxy)
     const int nxd = S.nx[ld], nyd = S.ny[ld], nxyd = nxd * nyd, syd = nxd + 2, szd = syd * (nyd + 2);
@@ -545,25 +621,19 @@ __device__ __forceinline__ void small_fast(T *sm, const SmallLevels<T> &S, const
         }
         __syncthreads();
     };
-    if (one) {
-        smooth_a(S.n_coarse);
-        store();
-        return;
-    }
-    smooth_a(S.n_pre);
+    A.smooth(S.n_pre);
 #pragma unroll
-    for (int u = 0; u < 2; u++)
+    for (int u = 0; u < U; u++)
 #pragma unroll
         for (int c = 0; c < 2; c++)
-            if (da[u][c] != T(0))
-                ra[ea[u][c]] = residual_at<T>(xa + pa[u][c], sya, sza, S.ih2[0], fa[u][c], da[u][c]);
+            if (A.d[u][c] != T(0)) ra[A.cell(u, c)] = A.residual(u, c, S.ih2[0]);
     __syncthreads();
     if (hasb) {
 #pragma unroll
         for (int c = 0; c < 2; c++)
             if (db[c] != T(0)) fb[c] = coarse_rhs<T>(ra, cb[c], nxa, nxya);
         if (three) {
-            for (int v = 0; v < S.n_cycles; v++) {  // (x starts at zero, later visits go on from it)
+            for (int n = 0; n < S.n_cycles; n++) {  // (x starts at zero, later visits go on from it)
                 smooth_b(S.n_pre);
 #pragma unroll
                 for (int c = 0; c < 2; c++)
@@ -581,7 +651,7 @@ __device__ __forceinline__ void small_fast(T *sm, const SmallLevels<T> &S, const
                 smooth_b(S.n_post);
             }
         } else {
-            for (int v = 0; v < S.n_cycles; v++) smooth_b(S.n_coarse);
+            for (int n = 0; n < S.n_cycles; n++) smooth_b(S.n_coarse);
         }
     } else {
         solve_d(ra, nxa, nxya);
@@ -590,18 +660,18 @@ __device__ __forceinline__ void small_fast(T *sm, const SmallLevels<T> &S, const
         const T *xc = hasb ? xb : xd;
         const int syc = hasb ? syb : syd, szc = hasb ? szb : szd;
 #pragma unroll
-        for (int u = 0; u < 2; u++)
+        for (int u = 0; u < U; u++)
 #pragma unroll
             for (int c = 0; c < 2; c++)
-                if (da[u][c] != T(0)) {
-                    const int i = ta[u].i(c), j = ta[u].j, k = ta[u].k;
-                    xa[pa[u][c]] += interpolated<T>(xc + ((k >> 1) + 1) * szc + ((j >> 1) + 1) * syc + (i >> 1) + 1, i,
-                                                    j, k, syc, szc);
+                if (A.d[u][c] != T(0)) {
+                    const int i = A.at[u].i(c), j = A.at[u].j, k = A.at[u].k;
+                    A.x[c][A.p[u]] += interpolated<T>(
+                        xc + ((k >> 1) + 1) * szc + ((j >> 1) + 1) * syc + (i >> 1) + 1, i, j, k, syc, szc);
                 }
         __syncthreads();
     }
-    smooth_a(S.n_post);
-    store();
+    A.smooth(S.n_post);
+    A.store(x0);
 }
 
 // One call MG(ls) for the levels held in S, all resident at `sm`: in LDS
