@@ -495,6 +495,10 @@ struct mg_batch {
     mg_options opt;
     hipStream_t stream = nullptr;
     bool own_stream = false;
+    // direct launches: the first-order patches' cycle runs on `side` beside the
+    // second-order patches' (they share no buffer), after `forked`, until `joined`
+    hipStream_t side = nullptr;
+    hipEvent_t forked = nullptr, joined = nullptr;
     std::vector<mg_hierarchy *> patches;  // all enqueue on `stream`
     std::vector<void *> allocs;           // batch-owned device memory
     bool phased_ok = false;               // phase programs built
@@ -1040,6 +1044,9 @@ void build_batch(mg_batch *B, const int8_t *const *masks, const int32_t *dims, c
     const int n = B->n;
     BHIP(hipEventCreate(&B->ev0));
     BHIP(hipEventCreate(&B->ev1));
+    BHIP(hipStreamCreateWithFlags(&B->side, hipStreamNonBlocking));
+    BHIP(hipEventCreateWithFlags(&B->forked, hipEventDisableTiming));
+    BHIP(hipEventCreateWithFlags(&B->joined, hipEventDisableTiming));
     B->patches.resize(n, nullptr);
     for (int p = 0; p < n; p++) {
         mg_options o = B->opt;
@@ -1071,12 +1078,11 @@ void build_batch(mg_batch *B, const int8_t *const *masks, const int32_t *dims, c
 }
 
 // live: the number of items in the launch's map, -1 for all of its items
-void launch(mg_batch *B, const Launch &k, int order, const int *state, int live = -1) {
+void launch(mg_batch *B, const Launch &k, int order, const int *state, hipStream_t s, int live = -1) {
     const BRef *r = B->refs + k.first;
     const int *map = live < 0 ? nullptr : B->map + k.first;
     const int count = live < 0 ? k.count : live;
     const BLev *lev = B->lev[order];
-    hipStream_t s = B->stream;
     const unsigned g = grid8(count);
     constexpr int NT = rb::NT;
     switch (k.kind) {
@@ -1112,7 +1118,8 @@ void launch(mg_batch *B, const Launch &k, int order, const int *state, int live 
 
 // The program for the patches marked in `on` (the ones `state` gives to
 // `order`): launches of live items only.
-void run_live(mg_batch *B, mg_batch::Prog &g, int order, const int *state, const std::vector<char> &on) {
+void run_live(mg_batch *B, mg_batch::Prog &g, int order, const int *state, const std::vector<char> &on,
+              hipStream_t s) {
     if (g.mapped != on) {
         g.live.assign(g.k.size(), 0);
         int ns = 0;
@@ -1123,14 +1130,14 @@ void run_live(mg_batch *B, mg_batch::Prog &g, int order, const int *state, const
             }
         g.mapped = on;
         if (ns > 0) {
-            BHIP(hipMemcpyAsync(g.spans, g.pin_spans, ns * sizeof(Span), hipMemcpyHostToDevice, B->stream));
-            kb_spans<<<ns, 256, 0, B->stream>>>(g.spans, B->map);
+            BHIP(hipMemcpyAsync(g.spans, g.pin_spans, ns * sizeof(Span), hipMemcpyHostToDevice, s));
+            kb_spans<<<ns, 256, 0, s>>>(g.spans, B->map);
         }
     }
     for (size_t i = 0; i < g.k.size(); i++) {
         const Launch &k = g.k[i];
-        if (k.kind == K_FIN || g.live[i] == k.count) launch(B, k, order, state);
-        else if (g.live[i] > 0) launch(B, k, order, state, g.live[i]);
+        if (k.kind == K_FIN || g.live[i] == k.count) launch(B, k, order, state, s);
+        else if (g.live[i] > 0) launch(B, k, order, state, s, g.live[i]);
     }
     BHIP(hipGetLastError());
 }
@@ -1139,17 +1146,17 @@ void run_live(mg_batch *B, mg_batch::Prog &g, int order, const int *state, const
 // the options ask for graphs.  on (may be null): the patches it serves; direct
 // launches then leave out the others' items.
 void run_program(mg_batch *B, mg_batch::Prog &g, int order, const int *state,
-                 const std::vector<char> *on = nullptr) {
-    if (!B->opt.use_graph && on) return run_live(B, g, order, state, *on);
+                 const std::vector<char> *on = nullptr, hipStream_t s = nullptr) {
+    if (!B->opt.use_graph && on) return run_live(B, g, order, state, *on, s ? s : B->stream);
     if (!B->opt.use_graph) {
-        for (const Launch &k : g.k) launch(B, k, order, state);
+        for (const Launch &k : g.k) launch(B, k, order, state, B->stream);
         BHIP(hipGetLastError());
         return;
     }
     if (!g.exec) {
         hipGraph_t graph = nullptr;
         BHIP(hipStreamBeginCapture(B->stream, hipStreamCaptureModeThreadLocal));
-        for (const Launch &k : g.k) launch(B, k, order, state);
+        for (const Launch &k : g.k) launch(B, k, order, state, B->stream);
         const hipError_t le = hipGetLastError();
         BHIP(hipStreamEndCapture(B->stream, &graph));
         BHIP(le);
@@ -1394,6 +1401,10 @@ mg_status solve_batch_phased(mg_batch *B, const double *const *rho, double *cons
                 if (st != MG_OK) return st;
             }
         }
+        // The two orders' patches share no buffer, so their cycles run side by
+        // side: few patches in one order leave most of the chip to the other.
+        // (The fork waits for the buffers an order switch has just cleared.)
+        BHIP(hipEventRecord(B->forked, s));
         for (int o = 2; o >= 1; o--) {
             int *sv = B->pin_state + o * n;  // the previous round's copies have finished
             bool use = false;
@@ -1403,8 +1414,15 @@ mg_status solve_batch_phased(mg_batch *B, const double *const *rho, double *cons
                 use |= sv[p] != 0;
             }
             if (!use) continue;
-            BHIP(hipMemcpyAsync(B->state[o], sv, n * sizeof(int), hipMemcpyHostToDevice, s));
-            run_program(B, B->cycle[o], o, B->state[o], &on);
+            const bool aside = o == 1 && !B->opt.use_graph;
+            const hipStream_t so = aside ? B->side : s;
+            if (aside) BHIP(hipStreamWaitEvent(so, B->forked, 0));
+            BHIP(hipMemcpyAsync(B->state[o], sv, n * sizeof(int), hipMemcpyHostToDevice, so));
+            run_program(B, B->cycle[o], o, B->state[o], &on, so);
+            if (aside) {
+                BHIP(hipEventRecord(B->joined, so));
+                BHIP(hipStreamWaitEvent(s, B->joined, 0));
+            }
         }
     }
     run_program(B, B->end, 2, B->state[0]);
@@ -1461,6 +1479,7 @@ extern "C" {
 void mg_destroy_batch(mg_batch *B) {
     if (!B) return;
     if (B->stream) (void)hipStreamSynchronize(B->stream);
+    if (B->side) (void)hipStreamSynchronize(B->side);
     for (auto *g : {&B->begin, &B->end, &B->pre, &B->cycle[1], &B->cycle[2]})
         if (g->exec) (void)hipGraphExecDestroy(g->exec);
     for (mg_hierarchy *H : B->patches) mg_destroy_hierarchy(H);
@@ -1476,6 +1495,9 @@ void mg_destroy_batch(mg_batch *B) {
     if (B->perr_host) (void)hipHostFree(B->perr_host);
     if (B->ev0) (void)hipEventDestroy(B->ev0);
     if (B->ev1) (void)hipEventDestroy(B->ev1);
+    if (B->forked) (void)hipEventDestroy(B->forked);
+    if (B->joined) (void)hipEventDestroy(B->joined);
+    if (B->side) (void)hipStreamDestroy(B->side);
     if (B->own_stream && B->stream) (void)hipStreamDestroy(B->stream);
     delete B;
 }
