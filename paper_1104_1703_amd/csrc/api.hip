@@ -74,25 +74,64 @@ void dev_free(mg_hierarchy *H, void *p) {
         }
 }
 
-// Active tile list, smoother work items of `depth` planes and their activity
-// masks of level l in boundary order `order`, written to od (its diagonals
-// and active count are left as they are).
-void build_lists(mg_hierarchy *H, int l, int order, int depth, OrderData &od) {
-    Level &L = H->lev[l];
-    const int nt = L.ntx * L.nty * L.ntz;
-    uint8_t *flags = alloc_n<uint8_t>(H, (size_t)nt);
-    launch_tile_flags(L, l, order, flags, H->stream);
-    std::vector<uint8_t> hf(nt);
-    HIPCHK(hipMemcpyAsync(hf.data(), flags, nt, hipMemcpyDeviceToHost, H->stream));
-    HIPCHK(hipStreamSynchronize(H->stream));
-    dev_free(H, flags);
+// Device memory of a hierarchy, asked for piece by piece and allocated in one
+// go: a hierarchy has some sixty arrays, and an allocation of their own costs
+// each a call through the allocator (and a free).  Arrays of 16 MiB and more
+// still get one.
+struct Arena {
+    struct Want {
+        void **p;
+        size_t bytes;
+    };
+    std::vector<Want> wants;
+    template <typename T>
+    void want(T *&p, size_t n) {
+        wants.push_back({(void **)&p, std::max<size_t>(n, 1) * sizeof(T)});
+    }
+    // zero: also clear the memory, on the hierarchy's stream
+    void alloc(mg_hierarchy *H, bool zero = false) {
+        constexpr size_t BIG = (size_t)16 << 20, ALIGN = 256;
+        size_t total = 0;
+        for (const Want &w : wants)
+            if (w.bytes < BIG) total += (w.bytes + ALIGN - 1) / ALIGN * ALIGN;
+        char *base = total ? (char *)alloc_n<char>(H, total) : nullptr;
+        if (zero && total) HIPCHK(hipMemsetAsync(base, 0, total, H->stream));
+        for (const Want &w : wants) {
+            if (w.bytes < BIG) {
+                *w.p = base;
+                base += (w.bytes + ALIGN - 1) / ALIGN * ALIGN;
+            } else {
+                *w.p = alloc_n<char>(H, w.bytes);
+                if (zero) HIPCHK(hipMemsetAsync(*w.p, 0, w.bytes, H->stream));
+            }
+        }
+        wants.clear();
+    }
+};
+
+// Host side of a level's lists: active tiles, smoother work items of `depth`
+// planes and, on level 1, whole tiles for the FP64 prolongation pass.
+struct ListPlan {
+    int l = 0, order = 2;
+    OrderData *od = nullptr;
     std::vector<int> tiles;
+    std::vector<Seg> segs, s8;
+};
+
+// The lists of level l from the activity flags hf of its tiles; od's depth and
+// counts are set (its diagonals and active count are left as they are).
+ListPlan plan_lists(mg_hierarchy *H, int l, int order, int depth, const uint8_t *hf, OrderData &od) {
+    const Level &L = H->lev[l];
+    ListPlan P;
+    P.l = l;
+    P.order = order;
+    P.od = &od;
+    const int nt = L.ntx * L.nty * L.ntz;
     for (int t = 0; t < nt; t++)
-        if (hf[t]) tiles.push_back(t);
+        if (hf[t]) P.tiles.push_back(t);
     // smoother items: on the finest level runs of active tiles along z, cut
     // every depth / TZ tiles; on coarse levels one active tile cut into
     // depth-plane items
-    std::vector<Seg> segs;
     for (int ty = 0; ty < L.nty; ty++)
         for (int tx = 0; tx < L.ntx; tx++) {
             int tz = 0;
@@ -105,81 +144,126 @@ void build_lists(mg_hierarchy *H, int l, int order, int depth, OrderData &od) {
                 if (l == 0) {
                     const int per = depth / TZ;
                     while (t1 < L.ntz && hf[(t1 * L.nty + ty) * L.ntx + tx] && t1 - tz < per) t1++;
-                    segs.push_back(Seg{tx * TX, ty * TY, tz * TZ, std::min(L.nz, t1 * TZ)});
+                    P.segs.push_back(Seg{tx * TX, ty * TY, tz * TZ, std::min(L.nz, t1 * TZ)});
                 } else {
                     t1 = tz + 1;
                     for (int z = tz * TZ; z < std::min(L.nz, t1 * TZ); z += depth)
-                        segs.push_back(Seg{tx * TX, ty * TY, z, std::min(std::min(L.nz, t1 * TZ), z + depth)});
+                        P.segs.push_back(Seg{tx * TX, ty * TY, z, std::min(std::min(L.nz, t1 * TZ), z + depth)});
                 }
                 tz = t1;
             }
         }
-    std::sort(segs.begin(), segs.end(), [](const Seg &a, const Seg &b) {
+    const auto by_slab = [](const Seg &a, const Seg &b) {
         if (a.z0 != b.z0) return a.z0 < b.z0;
         if (a.y0 != b.y0) return a.y0 < b.y0;
         return a.x0 < b.x0;
-    });
-    od.depth = depth;
-    od.ntiles = (int)tiles.size();
-    od.nsegs = (int)segs.size();
-    od.tiles = alloc_n<int>(H, std::max<size_t>(1, tiles.size()));
-    od.segs = alloc_n<Seg>(H, std::max<size_t>(1, segs.size()));
-    if (!tiles.empty())
-        HIPCHK(hipMemcpyAsync(od.tiles, tiles.data(), tiles.size() * sizeof(int), hipMemcpyHostToDevice, H->stream));
-    if (!segs.empty())
-        HIPCHK(hipMemcpyAsync(od.segs, segs.data(), segs.size() * sizeof(Seg), hipMemcpyHostToDevice, H->stream));
-    const int npl = depth + 4;
-    od.pmask = alloc_n<unsigned long long>(H, std::max<size_t>(1, segs.size() * npl));
-    launch_item_masks(L, l, order, od, npl, od.pmask, H->stream);
-    od.pmask3 = nullptr;
-    if (l == 0 && H->opt.fuse_restrict && !H->opt.fuse_passes) {  // the last finest pre-smoothing pass
-        const int npl3 = depth + 6;
-        od.pmask3 = alloc_n<unsigned long long>(H, std::max<size_t>(1, segs.size() * npl3));
-        launch_item_masks(L, l, order, od, npl3, od.pmask3, H->stream, 3);
-    }
-    od.pmask2 = nullptr;
-    if (H->opt.fuse_passes) {
-        const int npl2 = depth + 8;
-        od.pmask2 = alloc_n<unsigned long long>(H, std::max<size_t>(1, segs.size() * npl2));
-        launch_item_masks(L, l, order, od, npl2, od.pmask2, H->stream, 4);
-    }
-    std::vector<Seg> s8;
-    if (l == 1) {  // whole tiles for the FP64 prolongation pass
+    };
+    std::sort(P.segs.begin(), P.segs.end(), by_slab);
+    if (l == 1) {
         for (int ty = 0; ty < L.nty; ty++)
             for (int tx = 0; tx < L.ntx; tx++)
                 for (int tz = 0; tz < L.ntz; tz++)
                     if (hf[(tz * L.nty + ty) * L.ntx + tx])
-                        s8.push_back(Seg{tx * TX, ty * TY, tz * TZ, std::min(L.nz, (tz + 1) * TZ)});
-        std::sort(s8.begin(), s8.end(), [](const Seg &a, const Seg &b) {
-            if (a.z0 != b.z0) return a.z0 < b.z0;
-            if (a.y0 != b.y0) return a.y0 < b.y0;
-            return a.x0 < b.x0;
-        });
-        od.nsegs8 = (int)s8.size();
-        od.segs8 = alloc_n<Seg>(H, std::max<size_t>(1, s8.size()));
-        if (!s8.empty())
-            HIPCHK(hipMemcpyAsync(od.segs8, s8.data(), s8.size() * sizeof(Seg), hipMemcpyHostToDevice, H->stream));
-        constexpr int npl8 = TZ + 4;
-        od.pmask8 = alloc_n<unsigned long long>(H, std::max<size_t>(1, s8.size() * npl8));
+                        P.s8.push_back(Seg{tx * TX, ty * TY, tz * TZ, std::min(L.nz, (tz + 1) * TZ)});
+        std::sort(P.s8.begin(), P.s8.end(), by_slab);
+    }
+    od.depth = depth;
+    od.ntiles = (int)P.tiles.size();
+    od.nsegs = (int)P.segs.size();
+    od.nsegs8 = (int)P.s8.size();
+    return P;
+}
+
+// The lists' device arrays and activity masks.  Staged: the lists themselves
+// (contiguous in `host`, copied by the caller with one transfer).
+void want_masks(mg_hierarchy *H, Arena &A, const ListPlan &P) {
+    OrderData &od = *P.od;
+    od.pmask2 = od.pmask3 = od.pmask8 = nullptr;
+    A.want(od.pmask, P.segs.size() * (od.depth + 4));
+    if (P.l == 0 && H->opt.fuse_restrict && !H->opt.fuse_passes)  // the last finest pre-smoothing pass
+        A.want(od.pmask3, P.segs.size() * (od.depth + 6));
+    if (H->opt.fuse_passes) A.want(od.pmask2, P.segs.size() * (od.depth + 8));
+    if (P.l == 1) A.want(od.pmask8, P.s8.size() * (TZ + 4));
+}
+
+size_t staged_bytes(const ListPlan &P) {
+    return (P.segs.size() + P.s8.size()) * sizeof(Seg) + (P.tiles.size() + 3) / 4 * 4 * sizeof(int);
+}
+
+// Appends the plan's lists to `host` and points od at their places in the
+// device copy `dev` (16-byte aligned throughout).
+void stage_lists(const ListPlan &P, std::vector<char> &host, char *dev) {
+    OrderData &od = *P.od;
+    const auto put = [&](const void *src, size_t bytes, size_t room) {
+        char *at = dev + host.size();
+        const size_t o = host.size();
+        host.resize(o + room);
+        if (bytes) memcpy(host.data() + o, src, bytes);
+        return at;
+    };
+    od.segs = (Seg *)put(P.segs.data(), P.segs.size() * sizeof(Seg), P.segs.size() * sizeof(Seg));
+    od.segs8 = (Seg *)put(P.s8.data(), P.s8.size() * sizeof(Seg), P.s8.size() * sizeof(Seg));
+    od.tiles = (int *)put(P.tiles.data(), P.tiles.size() * sizeof(int), (P.tiles.size() + 3) / 4 * 4 * sizeof(int));
+    if (P.l != 1) od.segs8 = nullptr;
+}
+static_assert(sizeof(Seg) == 16, "staged lists stay 16-byte aligned");
+
+void form_masks(mg_hierarchy *H, const ListPlan &P) {
+    const Level &L = H->lev[P.l];
+    OrderData &od = *P.od;
+    launch_item_masks(L, P.l, P.order, od, od.depth + 4, od.pmask, H->stream);
+    if (od.pmask3) launch_item_masks(L, P.l, P.order, od, od.depth + 6, od.pmask3, H->stream, 3);
+    if (od.pmask2) launch_item_masks(L, P.l, P.order, od, od.depth + 8, od.pmask2, H->stream, 4);
+    if (od.pmask8) {
         OrderData t = od;
         t.segs = od.segs8;
         t.nsegs = od.nsegs8;
-        launch_item_masks(L, l, order, t, npl8, od.pmask8, H->stream);
+        launch_item_masks(L, P.l, P.order, t, TZ + 4, od.pmask8, H->stream);
     }
-    // the host vectors staged above (tiles, segs, s8) are the sources of
-    // asynchronous copies: wait for them before the vectors go away
+}
+
+// Lists of one more depth for level l (the tuner's candidates), in device
+// memory of their own.
+void build_lists(mg_hierarchy *H, int l, int order, int depth, OrderData &od) {
+    Level &L = H->lev[l];
+    const int nt = L.ntx * L.nty * L.ntz;
+    uint8_t *flags = alloc_n<uint8_t>(H, (size_t)nt);
+    launch_tile_flags(L, l, order, flags, H->stream);
+    std::vector<uint8_t> hf(nt);
+    HIPCHK(hipMemcpyAsync(hf.data(), flags, nt, hipMemcpyDeviceToHost, H->stream));
+    HIPCHK(hipStreamSynchronize(H->stream));
+    dev_free(H, flags);
+    const ListPlan P = plan_lists(H, l, order, depth, hf.data(), od);
+    od.lists = alloc_n<char>(H, std::max<size_t>(16, staged_bytes(P)));
+    std::vector<char> host;
+    stage_lists(P, host, od.lists);
+    if (!host.empty())
+        HIPCHK(hipMemcpyAsync(od.lists, host.data(), host.size(), hipMemcpyHostToDevice, H->stream));
+    size_t words = 0;
+    Arena A;
+    want_masks(H, A, P);
+    for (const Arena::Want &w : A.wants) words += w.bytes / sizeof(unsigned long long);
+    od.masks = alloc_n<unsigned long long>(H, words);
+    unsigned long long *at = od.masks;
+    for (const Arena::Want &w : A.wants) {
+        *w.p = at;
+        at += w.bytes / sizeof(unsigned long long);
+    }
+    form_masks(H, P);
+    // `host` is the source of an asynchronous copy: wait before it goes away
     HIPCHK(hipStreamSynchronize(H->stream));
 }
 
-// Frees the lists build_lists made (the stream must be idle).
+// Frees the lists build_lists made (the stream must be idle); those of the
+// hierarchy's creation stay with it.
 void free_lists(mg_hierarchy *H, OrderData &od) {
-    for (void *p : {(void *)od.tiles, (void *)od.segs, (void *)od.pmask, (void *)od.pmask2, (void *)od.pmask3,
-                    (void *)od.segs8, (void *)od.pmask8})
-        dev_free(H, p);
+    dev_free(H, od.lists);
+    dev_free(H, od.masks);
+    od.lists = nullptr;
+    od.masks = nullptr;
     od.tiles = nullptr;
-    od.segs = nullptr;
-    od.pmask = od.pmask2 = od.pmask8 = nullptr;
-    od.segs8 = nullptr;
+    od.segs = od.segs8 = nullptr;
+    od.pmask = od.pmask2 = od.pmask3 = od.pmask8 = nullptr;
 }
 
 mg_status validate_options(const mg_options &o) {
@@ -394,13 +478,45 @@ void create(mg_hierarchy *H, const int8_t *mask, int nx, int ny, int nz, double 
         v.nty = (v.ny + TY - 1) / TY;
         v.ntz = (v.nz + TZ - 1) / TZ;
     }
-    // validation on the device: bad values, non-inactive frame, active count
-    unsigned long long *ctr = alloc_n<unsigned long long>(H, 3 + 2 * MAXL + 1);
-    HIPCHK(hipMemsetAsync(ctr, 0, (3 + 2 * MAXL + 1) * sizeof(unsigned long long), s));
+    // Validation (bad values, non-inactive frame, active count), the integer
+    // mask counts per level (R1 of the mask), the finest code, the diagonals
+    // and tile flags per order: enqueued together and read back with one copy.
+    // (An invalid mask's counts are formed like any other's, then refused.)
+    constexpr int NCTR = 3 + 2 * MAXL + 1;
+    size_t nflags = 0;
+    for (int l = 0; l < L; l++) nflags += (size_t)lev[l].ntx * lev[l].nty * lev[l].ntz * (l ? 2 : 1);
+    Arena A;
+    char *back = nullptr;  // the counters, then the flags of (0, 2), (1, 1), (1, 2), (2, 1) ...
+    const size_t nback = NCTR * sizeof(unsigned long long) + nflags;
+    A.want(back, nback);
+    for (int l = 0; l < L; l++) {
+        A.want(lev[l].cnt, lev[l].n);
+        if (l == 0) A.want(lev[0].code, lev[0].n);
+        else
+            for (int o = 1; o <= 2; o++) A.want(lev[l].od[o].d, lev[l].n);
+    }
+    A.alloc(H);
+    unsigned long long *ctr = (unsigned long long *)back, *nact = ctr + 3;
+    uint8_t *flags = (uint8_t *)(ctr + NCTR);
+    HIPCHK(hipMemsetAsync(ctr, 0, NCTR * sizeof(unsigned long long), s));
     launch_validate(mask, nx, ny, nz, ctr, s);
-    unsigned long long hv[3 + 2 * MAXL + 1];
-    HIPCHK(hipMemcpyAsync(hv, ctr, 3 * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
+    launch_count0(mask, lev[0].cnt, lev[0].n, s);
+    for (int l = 1; l < L; l++) launch_count_up(lev[l - 1], lev[l], s);
+    launch_code0(lev[0], nact, s);
+    {
+        uint8_t *fl = flags;
+        for (int l = 0; l < L; l++)
+            for (int o = l ? 1 : 2; o <= 2; o++) {
+                if (l) launch_diag(lev[l], l, o, lev[l].od[o].d, nact + 2 * l + (o - 1), s);
+                launch_tile_flags(lev[l], l, o, fl, s);
+                fl += (size_t)lev[l].ntx * lev[l].nty * lev[l].ntz;
+            }
+    }
+    std::vector<char> hb(nback);
+    HIPCHK(hipMemcpyAsync(hb.data(), back, nback, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
+    unsigned long long hv[NCTR];
+    memcpy(hv, hb.data(), sizeof(hv));
     if (hv[0]) {
         set_error("mask holds " + std::to_string(hv[0]) + " values other than +1/-1");
         throw Fail{MG_ERR_ARG};
@@ -413,63 +529,68 @@ void create(mg_hierarchy *H, const int8_t *mask, int nx, int ny, int nz, double 
         set_error("mask has no active cell");
         throw Fail{MG_ERR_NO_ACTIVE};
     }
-    // integer mask counts per level (R1 of the mask)
-    for (int l = 0; l < L; l++) lev[l].cnt = alloc_n<int32_t>(H, lev[l].n);
-    launch_count0(mask, lev[0].cnt, lev[0].n, s);
-    for (int l = 1; l < L; l++) launch_count_up(lev[l - 1], lev[l], s);
-    // finest code, coarse diagonals per order
-    lev[0].code = alloc_n<uint8_t>(H, lev[0].n);
-    unsigned long long *nact = ctr + 3;
-    launch_code0(lev[0], nact, s);
-    for (int o = 1; o <= 2; o++)
-        for (int l = 1; l < L; l++) {
-            lev[l].od[o].d = alloc_n<double>(H, lev[l].n);
-            launch_diag(lev[l], l, o, lev[l].od[o].d, nact + 2 * l + (o - 1), s);
-        }
-    HIPCHK(hipMemcpyAsync(hv, nact, (2 * MAXL + 1) * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    lev[0].od[1].nact = lev[0].od[2].nact = (int64_t)hv[0];
+    const unsigned long long *ha = hv + 3;
+    lev[0].od[1].nact = lev[0].od[2].nact = (int64_t)ha[0];
     for (int o = 1; o <= 2; o++) {
         H->nlev[o] = 1;
         for (int l = 1; l < L; l++) {
-            lev[l].od[o].nact = (int64_t)hv[2 * l + (o - 1)];
+            lev[l].od[o].nact = (int64_t)ha[2 * l + (o - 1)];
             if (lev[l].od[o].nact > 0 && H->nlev[o] == l) H->nlev[o] = l + 1;
         }
     }
-    // active tile lists and work items (default or fixed depths; tuned below)
-    build_lists(H, 0, 2, start_depth(H->opt, 0), lev[0].od[2]);
-    lev[0].od[1] = lev[0].od[2];
-    for (int o = 1; o <= 2; o++)
-        for (int l = 1; l < H->nlev[o]; l++) {
-            build_lists(H, l, o, start_depth(H->opt, l), lev[l].od[o]);
-            lev[l].od[o].cube = forced_depth(H->opt, l) == DEPTH_CUBE;
-        }
-    // level buffers
+    // active tile lists and work items (default or fixed depths; tuned below),
+    // staged together and copied at once
+    std::vector<ListPlan> plans;
+    {
+        const uint8_t *hf = (const uint8_t *)hb.data() + NCTR * sizeof(unsigned long long);
+        for (int l = 0; l < L; l++)
+            for (int o = l ? 1 : 2; o <= 2; o++) {
+                if (l < H->nlev[o]) plans.push_back(plan_lists(H, l, o, start_depth(H->opt, l), hf, lev[l].od[o]));
+                hf += (size_t)lev[l].ntx * lev[l].nty * lev[l].ntz;
+            }
+    }
+    size_t nstage = 0;
+    for (const ListPlan &P : plans) {
+        want_masks(H, A, P);
+        nstage += staged_bytes(P);
+    }
+    char *lists = nullptr;
+    A.want(lists, nstage);
     const int nl = std::max(H->nlev[1], H->nlev[2]);
     const bool mixed = H->opt.precision == MG_MIXED;
+    if (mixed)
+        for (int o = 1; o <= 2; o++)
+            for (int l = 1; l < H->nlev[o]; l++) A.want(lev[l].od[o].d32, lev[l].n);
+    A.alloc(H);
+    std::vector<char> staged;
+    staged.reserve(nstage);
+    for (const ListPlan &P : plans) stage_lists(P, staged, lists);
+    if (!staged.empty())
+        HIPCHK(hipMemcpyAsync(lists, staged.data(), staged.size(), hipMemcpyHostToDevice, s));
+    for (const ListPlan &P : plans) form_masks(H, P);
+    lev[0].od[1] = lev[0].od[2];
+    for (int o = 1; o <= 2; o++)
+        for (int l = 1; l < H->nlev[o]; l++) lev[l].od[o].cube = forced_depth(H->opt, l) == DEPTH_CUBE;
+    // level buffers, and the solve loop's own: all start at zero
     for (int l = 0; l < nl; l++) {
         Level &v = lev[l];
-        for (int b = 0; b < 2; b++) {
-            v.x[b] = alloc_n<double>(H, v.n);
-            HIPCHK(hipMemsetAsync(v.x[b], 0, v.n * sizeof(double), s));
-        }
-        v.f = alloc_n<double>(H, v.n);
-        HIPCHK(hipMemsetAsync(v.f, 0, v.n * sizeof(double), s));
+        for (int b = 0; b < 2; b++) A.want(v.x[b], v.n);
+        A.want(v.f, v.n);
         if (mixed) {
-            for (int b = 0; b < 2; b++) {
-                v.x32[b] = alloc_n<float>(H, v.n);
-                HIPCHK(hipMemsetAsync(v.x32[b], 0, v.n * sizeof(float), s));
-            }
-            v.f32 = alloc_n<float>(H, v.n);
-            HIPCHK(hipMemsetAsync(v.f32, 0, v.n * sizeof(float), s));
-            if (l > 0)
-                for (int o = 1; o <= 2; o++)
-                    if (l < H->nlev[o]) {
-                        v.od[o].d32 = alloc_n<float>(H, v.n);
-                        launch_to_float(v.od[o].d, v.od[o].d32, v.n, s);
-                    }
+            for (int b = 0; b < 2; b++) A.want(v.x32[b], v.n);
+            A.want(v.f32, v.n);
         }
     }
+    H->part_cap = std::max(1, lev[0].od[2].ntiles * TZ);
+    A.want(H->part, (size_t)H->part_cap);
+    A.want(H->norm_dev, 8);
+    A.want(H->halt_dev, 1);
+    A.want(H->stop_dev, 1);
+    A.alloc(H, true);
+    for (int l = 0; l < MAXL; l++) lev[l].halt = H->halt_dev;
+    if (mixed)
+        for (int o = 1; o <= 2; o++)
+            for (int l = 1; l < H->nlev[o]; l++) launch_to_float(lev[l].od[o].d, lev[l].od[o].d32, lev[l].n, s);
     // first level of the one-workgroup kernel, per order
     const int small_lim = small_init();
     for (int o = 1; o <= 2; o++) {
@@ -488,27 +609,23 @@ void create(mg_hierarchy *H, const int8_t *mask, int nx, int ny, int nz, double 
         // a small deepest level below others is solved by its relaxation's matrix
         if (H->ls[o] >= 0 && H->ls[o] < last && deep_matrix_fits(lev[last])) {
             OrderData &od = lev[last].od[o];
-            od.deep = alloc_n<double>(H, lev[last].n * lev[last].n);
-            if (mixed) od.deep32 = alloc_n<float>(H, lev[last].n * lev[last].n);
-            launch_deep_matrix(lev[last], od, H->opt.n_cycles * H->opt.n_coarse_sweeps, s);
+            A.want(od.deep, lev[last].n * lev[last].n);
+            if (mixed) A.want(od.deep32, lev[last].n * lev[last].n);
         }
         if (H->ls[o] >= 0 && small_fast_levels(H, o, H->ls[o]))
             for (int l = H->ls[o]; l < std::min(H->nlev[o], H->ls[o] + 2); l++) {
                 OrderData &od = lev[l].od[o];
-                od.rd = alloc_n<double>(H, lev[l].n);
-                if (mixed) od.rd32 = alloc_n<float>(H, lev[l].n);
-                launch_reciprocals(lev[l], od, s);
+                A.want(od.rd, lev[l].n);
+                if (mixed) A.want(od.rd32, lev[l].n);
             }
     }
-    H->part_cap = std::max(1, lev[0].od[2].ntiles * TZ);
-    H->part = alloc_n<double>(H, (size_t)H->part_cap);
-    H->norm_dev = alloc_n<double>(H, 8);
-    H->halt_dev = alloc_n<int>(H, 1);
-    HIPCHK(hipMemsetAsync(H->halt_dev, 0, sizeof(int), s));
-    H->stop_dev = alloc_n<StopTest>(H, 1);
-    HIPCHK(hipMemsetAsync(H->stop_dev, 0, sizeof(StopTest), s));
-    for (int l = 0; l < MAXL; l++) lev[l].halt = H->halt_dev;
-    HIPCHK(hipMemsetAsync(H->norm_dev, 0, 8 * sizeof(double), s));
+    if (!A.wants.empty()) A.alloc(H);
+    for (int o = 1; o <= 2; o++)
+        for (int l = 1; l < H->nlev[o]; l++) {
+            const OrderData &od = lev[l].od[o];
+            if (od.deep) launch_deep_matrix(lev[l], od, H->opt.n_cycles * H->opt.n_coarse_sweeps, s);
+            if (od.rd) launch_reciprocals(lev[l], od, s);
+        }
     HIPCHK(hipHostMalloc((void **)&H->norm_host, 8 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent));
     HIPCHK(hipHostGetDevicePointer((void **)&H->norm_map, H->norm_host, 0));
     HIPCHK(hipEventCreate(&H->ev0));

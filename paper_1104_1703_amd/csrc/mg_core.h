@@ -81,6 +81,9 @@ struct OrderData {
     Seg *segs8 = nullptr;
     unsigned long long *pmask8 = nullptr;
     int nsegs8 = 0;
+    // memory of lists made after the hierarchy's creation (tuning), else null
+    char *lists = nullptr;
+    unsigned long long *masks = nullptr;
     int ntiles = 0, nsegs = 0;
     int depth = 0;  // planes per work item of segs (its masks hold depth + 4 words per item)
     bool cube = false;  // coarse levels: plain passes over 8^3 cubes loaded whole (no z march)
