@@ -34,11 +34,14 @@ __device__ __forceinline__ V bload(__amdgpu_buffer_rsrc_t r, int off) {
     else if constexpr (sizeof(V) == 4) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
     else return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0));
 }
-template <typename V>
+// AUX: cache policy bits; STREAM marks a store as non-temporal, so that its
+// lines do not push lines out of L2 that neighbouring items still read.
+constexpr int STREAM = 2;
+template <typename V, int AUX = 0>
 __device__ __forceinline__ void bstore(V v, __amdgpu_buffer_rsrc_t r, int off) {
     using U2 = unsigned __attribute__((ext_vector_type(2)));
-    if constexpr (sizeof(V) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r, off, 0, 0);
-    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, 0);
+    if constexpr (sizeof(V) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, v), r, off, 0, AUX);
+    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, AUX);
 }
 
 }  // namespace mg

@@ -38,7 +38,7 @@ using namespace rb;
 
 // Five blocks per CU (LDS); the finest float passes (16-19 KB of LDS, 62
 // registers) eight, so that the 2048 items of a 256^3 pass run in one round.
-template <typename T, bool FINE, int SEGZ, bool PRO = false>
+template <typename T, bool FINE, int SEGZ, bool PRO = false, int AUX = 0>
 __global__ __launch_bounds__(NT, FINE && sizeof(T) == 4 ? 8 : 5) void k_rbgs(
     const T *__restrict__ xin, T *__restrict__ xout, const T *__restrict__ f, const uint8_t *__restrict__ code,
     const T *__restrict__ dco, int nx, int ny, int nz, T h2, const Seg *__restrict__ segs,
@@ -47,13 +47,13 @@ __global__ __launch_bounds__(NT, FINE && sizeof(T) == 4 ? 8 : 5) void k_rbgs(
     __shared__ RbgsLds<T, FINE, PRO> lds;
     const int item = xcd_item(blockIdx.x, gridDim.x);
     if (item >= nsegs || (halt && *halt)) return;
-    rbgs_item<T, FINE, SEGZ, PRO>(lds, xin, xout, f, code, dco, nx, ny, nz, h2, segs[item],
-                                  pm + (size_t)item * (SEGZ + 4), xc, cnx, cny, cnz);
+    rbgs_item<T, FINE, SEGZ, PRO, false, AUX>(lds, xin, xout, f, code, dco, nx, ny, nz, h2, segs[item],
+                                              pm + (size_t)item * (SEGZ + 4), xc, cnx, cny, cnz);
 }
 
 // The finest pass that also forms the residual-norm partials of its input,
 // one per work item, as the residual-norm march does.
-template <int SZ>
+template <int SZ, int AUX>
 __global__ __launch_bounds__(NT, 5) void k_rbgs_norm(const double *__restrict__ xin, double *__restrict__ xout,
                                                    const double *__restrict__ f, const uint8_t *__restrict__ code,
                                                    int nx, int ny, int nz, double h2, double ih2,
@@ -63,9 +63,9 @@ __global__ __launch_bounds__(NT, 5) void k_rbgs_norm(const double *__restrict__ 
     __shared__ RbgsLds<double, true, false> lds;
     const int item = xcd_item(blockIdx.x, gridDim.x);
     if (item >= nsegs || (halt && *halt)) return;
-    const double sq = rbgs_item<double, true, SZ, false, true>(lds, xin, xout, f, code, nullptr, nx, ny, nz, h2,
-                                                               segs[item], pm + (size_t)item * (SZ + 4), nullptr, 0,
-                                                               0, 0, ih2);
+    const double sq = rbgs_item<double, true, SZ, false, true, AUX>(lds, xin, xout, f, code, nullptr, nx, ny, nz, h2,
+                                                                    segs[item], pm + (size_t)item * (SZ + 4), nullptr,
+                                                                    0, 0, 0, ih2);
     const double t = tr::block_sum(sq);
     if (threadIdx.x == 0) part[item] = t;
 }
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(NT, 5) void k_rbgs_norm(const double *__restrict__ 
 // The finest pass that also forms the residual of its result and restricts
 // it onto level 1 (smooth_res_core.h): four FP64 blocks per CU (LDS), six
 // FP32 blocks.
-template <typename T, int SEGZ>
+template <typename T, int SEGZ, int AUX>
 __global__ __launch_bounds__(NT, sizeof(T) == 8 ? 4 : 6) void k_rbgs_res(
     const T *__restrict__ xin, T *__restrict__ xout, const T *__restrict__ f, const uint8_t *__restrict__ code, int nx,
     int ny, int nz, T h2, T ih2, const Seg *__restrict__ segs, const unsigned long long *__restrict__ pm, int nsegs,
@@ -81,8 +81,8 @@ __global__ __launch_bounds__(NT, sizeof(T) == 8 ? 4 : 6) void k_rbgs_res(
     __shared__ rbr::Lds<T> lds;
     const int item = xcd_item(blockIdx.x, gridDim.x);
     if (item >= nsegs || (halt && *halt)) return;
-    rbr::rbgs_res_item<T, SEGZ>(lds, xin, xout, f, code, nx, ny, nz, h2, ih2, segs[item],
-                                          pm + (size_t)item * (SEGZ + 2 * rbr::H), cd, cnx, cny, fc);
+    rbr::rbgs_res_item<T, SEGZ, AUX>(lds, xin, xout, f, code, nx, ny, nz, h2, ih2, segs[item],
+                                     pm + (size_t)item * (SEGZ + 2 * rbr::H), cd, cnx, cny, fc);
 }
 
 // Two passes per launch (smooth2_core.h): LDS allows two FP64 blocks per CU.
@@ -225,6 +225,26 @@ void launch_rbgs_restrict32(const Level &L, const Level &C, int order, const Ord
     (void)launch_cube_restrict<float, false>(xin, xout, f, L, od, C, C.od[order].d32, fc, s);
 }
 
+// Calls launch with a finest pass's item depth and the cache policy of its
+// stores.  The result is stored non-temporally when what a pass
+// touches (x in and out, f and the code, on active cells) is more than the
+// 256 MiB last-level cache holds.  The next pass then finds nothing of it
+// there anyway, while the stored lines would push halo lines out of L2; below
+// that size it reads the result back from that cache.  Solve times, without
+// and with: FP64 192^3 porous (166 MB) 12.57 / 13.69 ms, 256^3 holes (152 MB)
+// 12.56 / 13.26, 256^3 porous (394 MB) 25.7 / 25.1, 384^3 holes (510 MB) 38.7
+// / 38.4, 512^3 holes (1.2 GB) 89.8 / 87.9; mixed precision (with the update's
+// outputs always stored so) 256^3 porous (205 MB) 20.5 / 21.6, 320^3 (400 MB)
+// 44.0 / 43.5, 512^3 (1.6 GB) 163.6 / 162.2.
+template <typename T, typename F>
+void with_fine_pass(const OrderData &od, F &&launch) {
+    const bool stream = (size_t)od.nact * (3 * sizeof(T) + 1) > ((size_t)256 << 20);
+    with_fine_depth(od.depth, [&](auto Z) {
+        if (stream) launch(Z, std::integral_constant<int, STREAM>{});
+        else launch(Z, std::integral_constant<int, 0>{});
+    });
+}
+
 template <typename T>
 hipError_t launch_fine_res(const Level &L, const OrderData &od, const T *xin, T *xout, const T *f, const Level &C,
                            const T *cd, T *fc, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
@@ -232,8 +252,8 @@ hipError_t launch_fine_res(const Level &L, const OrderData &od, const T *xin, T 
     if (od.few) return launch_cube_restrict<T, true>(xin, xout, f, L, od, C, cd, fc, s, e0, e1);
     const T h2 = (T)(L.h * L.h), ih2 = (T)(1.0 / (L.h * L.h));
     hipError_t err = hipSuccess;
-    with_fine_depth(od.depth, [&](auto Z) {
-        err = launch_k(k_rbgs_res<T, decltype(Z)::value>, grid8(od.nsegs), s, e0, e1, xin, xout, f, L.code, L.nx,
+    with_fine_pass<T>(od, [&](auto Z, auto P) {
+        err = launch_k(k_rbgs_res<T, decltype(Z)::value, decltype(P)::value>, grid8(od.nsegs), s, e0, e1, xin, xout, f, L.code, L.nx,
                        L.ny, L.nz, h2, ih2, od.segs, od.pmask3, od.nsegs, L.halt, cd, C.nx, C.ny, fc);
     });
     return err;
@@ -277,8 +297,8 @@ hipError_t launch_fine(const Level &L, const OrderData &od, const T *xin, T *xou
                        hipEvent_t e0, hipEvent_t e1) {
     if (od.few) return launch_cube<T, true>(xin, xout, f, L, od, s, e0, e1);
     hipError_t err = hipSuccess;
-    with_fine_depth(od.depth, [&](auto Z) {
-        err = launch_k(k_rbgs<T, true, decltype(Z)::value>, grid8(od.nsegs), s, e0, e1, xin, xout, f, L.code,
+    with_fine_pass<T>(od, [&](auto Z, auto P) {
+        err = launch_k(k_rbgs<T, true, decltype(Z)::value, false, decltype(P)::value>, grid8(od.nsegs), s, e0, e1, xin, xout, f, L.code,
                        (const T *)nullptr, L.nx, L.ny, L.nz, h2, od.segs, od.pmask, od.nsegs, L.halt,
                        (const T *)nullptr, 0, 0, 0);
     });
@@ -306,8 +326,8 @@ hipError_t launch_rbgs_norm(const Level &L, const OrderData &od, const double *x
                         L.nx, L.ny, L.nz, L.ntx, L.nty, L.h * L.h, 1.0 / (L.h * L.h), od.tiles, od.ntiles, od.segs,
                         od.nsegs, L.halt, part);
     hipError_t err = hipSuccess;
-    with_fine_depth(od.depth, [&](auto Z) {
-        err = launch_k(k_rbgs_norm<decltype(Z)::value>, grid8(od.nsegs), s, e0, e1, xin, xout, f, L.code, L.nx, L.ny,
+    with_fine_pass<double>(od, [&](auto Z, auto P) {
+        err = launch_k(k_rbgs_norm<decltype(Z)::value, decltype(P)::value>, grid8(od.nsegs), s, e0, e1, xin, xout, f, L.code, L.nx, L.ny,
                        L.nz, L.h * L.h, 1.0 / (L.h * L.h), od.segs, od.pmask, od.nsegs, L.halt, part);
     });
     return err;
@@ -323,8 +343,8 @@ hipError_t launch_rbgs_prolong(const Level &L, int level, const OrderData &od, c
     const double h2 = L.h * L.h;
     hipError_t err = hipSuccess;
     if (level == 0)
-        with_fine_depth(od.depth, [&](auto Z) {
-            err = launch_k(k_rbgs<double, true, decltype(Z)::value, true>, grid8(od.nsegs), s, e0, e1, xin, xout, f,
+        with_fine_pass<double>(od, [&](auto Z, auto P) {
+            err = launch_k(k_rbgs<double, true, decltype(Z)::value, true, decltype(P)::value>, grid8(od.nsegs), s, e0, e1, xin, xout, f,
                            L.code, (const double *)nullptr, L.nx, L.ny, L.nz, h2, od.segs, od.pmask, od.nsegs, L.halt,
                            xc, C.nx, C.ny, C.nz);
         });
@@ -347,8 +367,8 @@ hipError_t launch_rbgs_prolong32(const Level &L, int level, const OrderData &od,
     const float h2 = (float)(L.h * L.h);
     hipError_t err = hipSuccess;
     if (level == 0)
-        with_fine_depth(od.depth, [&](auto Z) {
-            err = launch_k(k_rbgs<float, true, decltype(Z)::value, true>, grid8(od.nsegs), s, e0, e1, xin, xout, f,
+        with_fine_pass<float>(od, [&](auto Z, auto P) {
+            err = launch_k(k_rbgs<float, true, decltype(Z)::value, true, decltype(P)::value>, grid8(od.nsegs), s, e0, e1, xin, xout, f,
                            L.code, (const float *)nullptr, L.nx, L.ny, L.nz, h2, od.segs, od.pmask, od.nsegs, L.halt,
                            xc, C.nx, C.ny, C.nz);
         });

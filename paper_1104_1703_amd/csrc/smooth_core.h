@@ -97,8 +97,13 @@ constexpr float RCP32[13] = {0.0f,      1.0f,      1.0f / 2, 1.0f / 3, 1.0f / 4,
 template <typename T>
 __device__ __forceinline__ T div_small(T a, T d, T y) {
     const T q0 = a * y;
-    const T r = -__builtin_fma(q0, d, -a);
-    return __builtin_fma(r, y, q0);
+    if constexpr (sizeof(T) == 4) {  // in float throughout (the generic builtin would convert to double)
+        const T r = -__builtin_fmaf(q0, d, -a);
+        return __builtin_fmaf(r, y, q0);
+    } else {
+        const T r = -__builtin_fma(q0, d, -a);
+        return __builtin_fma(r, y, q0);
+    }
 }
 
 // One full red-black pass over one work item (see the file comment of
@@ -114,7 +119,9 @@ __device__ __forceinline__ T div_small(T a, T d, T y) {
 // it in registers, the residual of the plane below is formed with the same
 // expression and plane order as the residual-norm march, so the block sums
 // are bit for bit the march's.
-template <typename T, bool FINE, int SEGZ, bool PRO = false, bool NORMIN = false>
+// AUX: cache policy of the stores (STREAM on large finest levels, see
+// with_fine_pass; as a run-time choice it cost the FP64 passes 3%).
+template <typename T, bool FINE, int SEGZ, bool PRO = false, bool NORMIN = false, int AUX = 0>
 __device__ __forceinline__ double rbgs_item(RbgsLds<T, FINE, PRO> &L, const T *__restrict__ xin,
                                             T *__restrict__ xout, const T *__restrict__ f,
                                             const uint8_t *__restrict__ code, const T *__restrict__ dco, int nx,
@@ -325,7 +332,7 @@ __device__ __forceinline__ double rbgs_item(RbgsLds<T, FINE, PRO> &L, const T *_
             bool act;
             if constexpr (SLIM) act = gx < nx && gy < ny;
             else act = dq[didx(u, v)] != DT(0);
-            bstore<T>(c[v * PX + u], ro, act ? (gy * nx + gx) * (int)sizeof(T) : OFF_NONE);
+            bstore<T, AUX>(c[v * PX + u], ro, act ? (gy * nx + gx) * (int)sizeof(T) : OFF_NONE);
         }
     };
 

@@ -63,8 +63,8 @@ struct Lds {
 // SEGZ + 6 mask words (planes z0-3 .. z0+SEGZ+2).  xin may be null (x = 0).
 // The item's x0, y0 and z0 are even.  Coarse cells above the item's tile
 // columns get f_c = -(1/8) sum of their children's residuals where the coarse
-// diagonal cd is non-zero, 0 elsewhere.
-template <typename T, int SEGZ>
+// diagonal cd is non-zero, 0 elsewhere.  AUX: cache policy of the stores of xout.
+template <typename T, int SEGZ, int AUX = 0>
 __device__ __forceinline__ void rbgs_res_item(Lds<T> &L, const T *__restrict__ xin, T *__restrict__ xout,
                                               const T *__restrict__ f, const uint8_t *__restrict__ code, int nx,
                                               int ny, int nz, T h2, T ih2, const Seg sg,
@@ -228,7 +228,7 @@ __device__ __forceinline__ void rbgs_res_item(Lds<T> &L, const T *__restrict__ x
             }
         }
         if (p >= 0 && p < zlen)  // inactive cells hold 0 in every iterate buffer
-            bstore<T>(xn, rsrc(xout + (size_t)(z0 + p) * plane, pbytes), cB != 0 ? ooff : OFF_NONE);
+            bstore<T, AUX>(xn, rsrc(xout + (size_t)(z0 + p) * plane, pbytes), cB != 0 ? ooff : OFF_NONE);
         xa = xb;
         xb = xn;
         nb = sn;
