@@ -57,19 +57,49 @@ __device__ __forceinline__ f32x4 mfma(const bf16x8 &a, const bf16x8 &b, const f3
 // or with HALF the last chunk when C_in = 32 q + 16) takes two taps per K step
 // of 32 (lane groups 0, 1: tap 2p; 2, 3: tap 2p + 1) instead of padding K
 // with zeros.
+//
+// The products take the weights as A and the voxels as B, so that a lane ends
+// with four channels of one voxel: one 8-byte store instead of four of two
+// bytes.  All pieces of a tile are in flight together while it is staged, the
+// weights run a tap row ahead of the products, and every LDS address is a
+// constant beyond a base per lane.  8 x 64^3 voxels, before and after: 16 -> 16
+// channels 95 -> 57 us (134 MB: 2.4 TB/s, bound by its LDS reads and the
+// staging's latency), 16 -> 48 278 -> 138 us (three channel groups share a
+// tile: 268 MB at 1.9 TB/s), 48 -> 16 (32 up-sampled) 212 -> 152 us; 8 x 32^3:
+// 96 -> 32 72 -> 58 us (750 TFLOP/s); 8 x 8^3: 128 -> 128 24 -> 20 us (bound by
+// latency: 64 blocks, a chain of four chunks).
 constexpr int TX = 16, TY = 4, TZ = 4;
 constexpr int HX = TX + 2, HY = TY + 2, HZ = TZ + 2, HV = HX * HY * HZ;
+
+// What becomes of a convolution's output besides bias and ReLU.
+struct ConvOut {
+    const bf16 *gate = nullptr;  // output zeroed where not gate > 0 (the ReLU below a gradient)
+    // split (up non-null): the output is the gradient of a concatenated input
+    // whose first cup channels were up-sampled; those are summed over the 8
+    // children of each coarse voxel into up (gated there by gate), the others
+    // go to out, cout - cup channels wide
+    bf16 *up = nullptr;
+    int cup = 0;
+};
+
+__device__ __forceinline__ bf16x8 gated(bf16x8 v, const bf16x8 &g) {
+#pragma unroll
+    for (int j = 0; j < 8; j++)
+        if (!((float)g[j] > 0.f)) v[j] = (bf16)0.0f;
+    return v;
+}
 
 template <int CK, int NTC, bool HALF = false>
 __global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina, int ca, int upa,
                                                    const bf16 *__restrict__ inb, int cb, const bf16 *__restrict__ wt,
                                                    const float *__restrict__ bias, bf16 *__restrict__ out, int cout,
                                                    int relu, int D, int H, int W, int ntx, int nty, int ntz,
-                                                   int nblk) {
+                                                   int nblk, ConvOut eo) {
     constexpr int CKP = CK + 8;
     constexpr int MT = 4;
     static_assert(MT == TY && NTH / 64 == TZ && TX == 16, "a wave owns the 16 x 4 voxels of one tile plane");
-    __shared__ __attribute__((aligned(16))) bf16 tile[HV * CKP];
+    constexpr int UP = TX * TY * TZ * NTC * 16;  // up-sampled part of a split output, on its way to the sums
+    __shared__ __attribute__((aligned(16))) bf16 tile[HV * CKP > UP ? HV * CKP : UP];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int row = lane & 15, grp = lane >> 4;
     // the 8 XCDs take contiguous runs of tiles, so neighbouring halos share an L2
@@ -85,9 +115,6 @@ __global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina,
     const int co_base = blockIdx.y * NTC * 16;
     const int cin = ca + cb;
     const int Dc = D >> 1, Hc = H >> 1, Wc = W >> 1;
-    int hb[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; mt++) hb[mt] = ((wave + 1) * HY + mt + 1) * HX + row + 1;
     f32x4 acc[MT][NTC];
 #pragma unroll
     for (int mt = 0; mt < MT; mt++)
@@ -116,36 +143,48 @@ __global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina,
         }
         rowb[src][r] = bp;
     }
-    // A fragments: LDS element offset of tap (dz, dy, dx) is toff * CKP with
-    // toff = ((dz - 1) HY + dy - 1) HX + dx - 1 >= -TMIN; bases shifted by
-    // TMIN keep every offset a non-negative constant
-    constexpr int TMIN = HY * HX + HX + 1;
-    const bf16 *tb[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; mt++) tb[mt] = tile + (hb[mt] - TMIN) * CKP;
+    // this lane's voxel of its wave's fragment 0, displaced by tap (0, 0, 0):
+    // fragment mt at tap (dz, dy, dx) lies ((dz HY + dy + mt) HX + dx) voxels on
+    const bf16 *tb = tile + (wave * HY * HX + row) * CKP;
     // weights [tap][co][ci]: a uniform per-tap base and this lane's offset
     const size_t wtap = (size_t)cout * cin;
     for (int c0 = 0; c0 < cin; c0 += CK) {
+        // Whole chunks of 32 channels: B fragments of a (dz, dy) row of taps are
+        // fetched a row ahead, the first before the staging
+        const bool full = CK == 32 && (!HALF || cin - c0 >= 32);
+        unsigned wl[NTC];  // byte offsets within a tap's weights (K entries c0 + 8 grp .. + 7)
+#pragma unroll
+        for (int nt = 0; nt < NTC; nt++) wl[nt] = (unsigned)(((co_base + nt * 16 + row) * cin + c0 + grp * 8) * 2);
+        bf16x8 bfr[2][3][NTC];
+        const auto fetch = [&](int r) {
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) {
+                const char *wb = (const char *)(wt + (r * 3 + dx) * wtap);  // uniform
+#pragma unroll
+                for (int nt = 0; nt < NTC; nt++) bfr[r & 1][dx][nt] = *(const bf16x8 *)(wb + wl[nt]);
+            }
+        };
+        if (full) fetch(0);
         __syncthreads();
         {
             const int c = c0 + sub * 8;  // this thread's 8 channels: all of a or all of b (8 | ca)
             const bool cok = c < cin, isa = c < ca;
             const int coff = isa ? c : c - ca, cs = isa ? ca : cb, sh = (isa && upa) ? 1 : 0;
             const bf16 *const *rb = rowb[isa ? 0 : 1];
-            // voxel hv = row hr (z-major over (z, y)) x HX + hx, stepped by VPT
-            constexpr int SDR = VPT / HX, SDX2 = VPT % HX;
-            int hv = hv0, hx = hv0 % HX, hr = hv0 / HX;
+            // voxel hv = row hr (z-major over (z, y)) x HX + hx, stepped by VPT.
+            // Pieces outside the box load the tensor's first one and are zeroed,
+            // so that no branch keeps the loads from being in flight together.
+            constexpr int SDR = VPT / HX, SDX2 = VPT % HX, NK = (HV + VPT - 1) / VPT;
+            int hx = hv0 % HX, hr = hv0 / HX;
+            bf16x8 v[NK];
+            bool ok[NK];
 #pragma unroll
-            for (int k = 0; k < (HV + VPT - 1) / VPT; k++) {
-                if (hv < HV) {
-                    const int gx = x0 - 1 + hx;
-                    const bf16 *bp = rb[hr];
-                    bf16x8 v = zero8();
-                    if (cok && bp && (unsigned)gx < (unsigned)W)  // x < 2^24, channels < 2^24
-                        v = *(const bf16x8 *)(bp + (__umul24((unsigned)(gx >> sh), (unsigned)cs) + coff));
-                    *(bf16x8 *)(tile + hv * CKP + sub * 8) = v;
-                }
-                hv += VPT;
+            for (int k = 0; k < NK; k++) {
+                const int gx = x0 - 1 + hx;
+                const bf16 *bp = rb[min(hr, HZ * HY - 1)];
+                ok[k] = cok && bp && (unsigned)gx < (unsigned)W;
+                // x < 2^24, channels < 2^24
+                v[k] = *(const bf16x8 *)(ok[k] ? bp + (__umul24((unsigned)(gx >> sh), (unsigned)cs) + coff) : ina);
                 hx += SDX2;
                 hr += SDR;
                 if (hx >= HX) {
@@ -153,92 +192,141 @@ __global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina,
                     hr++;
                 }
             }
+#pragma unroll
+            for (int k = 0; k < NK; k++)
+                if (hv0 + k * VPT < HV)
+                    *(bf16x8 *)(tile + (hv0 + k * VPT) * CKP + sub * 8) = ok[k] ? v[k] : zero8();
         }
         __syncthreads();
-        if (CK == 32 && (!HALF || cin - c0 >= 32)) {
-            const int cw = c0 + grp * 8;  // this lane's 8 K entries: channels cw .. cw + 7 of one tap
-            unsigned wl[NTC];  // byte offsets within a tap's weights
+        if (full) {
+            // the A fragments of a tap plane's MT + 2 rows are read once for its
+            // three dy (row mt + 1 of dy is row mt of dy + 1)
 #pragma unroll
-            for (int nt = 0; nt < NTC; nt++) wl[nt] = (unsigned)(((co_base + nt * 16 + row) * cin + cw) * 2);
-#pragma unroll 1
-            for (int tzy = 0; tzy < 9; ++tzy) {  // (dz, dy) rows of taps; the 3 dx taps unrolled
-                const int rowoff = ((tzy / 3 - 1) * HY + tzy % 3 - 1) * HX;  // uniform
-                // the row's 3 x MT A fragments and 3 x NTC B fragments are all
-                // read before its matrix products
-                bf16x8 afr[3][MT], bfr[3][NTC];
+            for (int dz = 0; dz < 3; dz++) {
+                bf16x8 afr[MT + 2][3];
 #pragma unroll
-                for (int dx = 0; dx < 3; ++dx) {
-                    const char *wb = (const char *)(wt + (tzy * 3 + dx) * wtap);  // uniform
+                for (int r = 0; r < MT + 2; r++)
 #pragma unroll
-                    for (int nt = 0; nt < NTC; nt++) bfr[dx][nt] = *(const bf16x8 *)(wb + wl[nt]);
+                    for (int dx = 0; dx < 3; ++dx)
+                        afr[r][dx] = *(const bf16x8 *)(tb + ((dz * HY + r) * HX + dx) * CKP + grp * 8);
+#pragma unroll
+                for (int dy = 0; dy < 3; dy++) {
+                    const int r = dz * 3 + dy;
+                    if (r < 8) fetch(r + 1);
+                    // keep the loads ahead of the products (with HALF the registers
+                    // that takes cost more: 153 against 171 us)
+                    if constexpr (!HALF) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                        for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+                            for (int nt = 0; nt < NTC; nt++)
+                                acc[mt][nt] = mfma(bfr[r & 1][dx][nt], afr[mt + dy][dx], acc[mt][nt]);
                 }
-#pragma unroll
-                for (int dx = 0; dx < 3; ++dx)
-#pragma unroll
-                    for (int mt = 0; mt < MT; mt++)
-                        afr[dx][mt] = *(const bf16x8 *)(tb[mt] + (rowoff + TMIN - 1 + dx) * CKP + grp * 8);
-#pragma unroll
-                for (int dx = 0; dx < 3; ++dx)
-#pragma unroll
-                    for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-                        for (int nt = 0; nt < NTC; nt++) acc[mt][nt] = mfma(afr[dx][mt], bfr[dx][nt], acc[mt][nt]);
-                // schedule: the row's weight loads, its LDS reads, then its matrix products
-                __builtin_amdgcn_sched_group_barrier(0x020, 3 * NTC, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 3 * MT, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 3 * MT * NTC, 0);
             }
         } else if constexpr (CK == 16 || HALF) {
             // 16 channels per tap: one K step of 32 covers taps 2p (lane groups 0, 1) and 2p + 1 (2, 3)
             const int half = grp >> 1, cl = (grp & 1) * 8, cw = c0 + cl;
             const bool cok = cw < cin;
-            unsigned wl[NTC];  // byte offsets within tap 2p's weights (this lane's tap is 2p + half)
+            unsigned wp[NTC];  // byte offsets within tap 2p's weights (this lane's tap is 2p + half)
 #pragma unroll
             for (int nt = 0; nt < NTC; nt++)
-                wl[nt] = (unsigned)((half * (int)wtap + (co_base + nt * 16 + row) * cin + cw) * 2);
-            const bf16 *tc[MT];
+                wp[nt] = (unsigned)((half * (int)wtap + (co_base + nt * 16 + row) * cin + cw) * 2);
+            // tap 2p + 1 lies one voxel, one row less two or one plane less two
+            // rows and two voxels beyond tap 2p: one base for each, so that all
+            // fragment addresses are constants beyond it
+            const bf16 *t1 = tb + cl + half * CKP, *t2 = tb + cl + half * (HX - 2) * CKP,
+                       *t3 = tb + cl + half * ((HY - 2) * HX - 2) * CKP;
 #pragma unroll
-            for (int mt = 0; mt < MT; mt++) tc[mt] = tb[mt] + TMIN * CKP + cl;
-#pragma unroll 2
             for (int p = 0; p < 14; ++p) {
-                const int t0 = 2 * p, t1 = 2 * p + 1;  // uniform; this lane's tap is t0 + half
-                const int o0 = ((t0 / 9 - 1) * HY + (t0 / 3) % 3 - 1) * HX + t0 % 3 - 1;
-                const int o1 = t1 < 27 ? ((t1 / 9 - 1) * HY + (t1 / 3) % 3 - 1) * HX + t1 % 3 - 1 : 0;
-                const bool tok = cok && (t1 < 27 || !half);
-                const int toff = (half ? o1 : o0) * CKP;
-                const char *wb = (const char *)(wt + t0 * wtap);  // uniform
-                bf16x8 bfr[NTC];
+                const int ta = 2 * p;  // its second tap, 27, does not exist for p = 13: zeros
+                const bf16 *base = ta % 3 < 2 ? t1 : ta % 9 < 8 ? t2 : t3;
+                const int off = ((ta / 9 * HY + ta / 3 % 3) * HX + ta % 3) * CKP;
+                const bool tok = cok && (p < 13 || !half);
+                const char *wb = (const char *)(wt + ta * wtap);  // uniform
+                bf16x8 bp[NTC];
 #pragma unroll
-                for (int nt = 0; nt < NTC; nt++) bfr[nt] = tok ? *(const bf16x8 *)(wb + wl[nt]) : zero8();
+                for (int nt = 0; nt < NTC; nt++) bp[nt] = tok ? *(const bf16x8 *)(wb + wp[nt]) : zero8();
 #pragma unroll
                 for (int mt = 0; mt < MT; mt++) {
-                    const bf16x8 afr = tok ? *(const bf16x8 *)(tc[mt] + toff) : zero8();
+                    bf16x8 afr = *(const bf16x8 *)((p < 13 ? base : tb + cl) + off + mt * HX * CKP);
+                    if (p == 13 && half) afr = zero8();
 #pragma unroll
-                    for (int nt = 0; nt < NTC; nt++) acc[mt][nt] = mfma(afr, bfr[nt], acc[mt][nt]);
+                    for (int nt = 0; nt < NTC; nt++) acc[mt][nt] = mfma(bp[nt], afr, acc[mt][nt]);
                 }
             }
         }
     }
-    // lane l holds D[4 (l div 16) + r][l mod 16]: voxel x = 4 grp + r of row y = mt, channel row
-    const int z = z0 + wave;
-    // this lane's first output (x0 + 4 grp, y0, z, channel co_base + row)
-    bf16 *ob = out + ((((size_t)n * D + z) * H + y0) * W + x0 + grp * 4) * cout + co_base + row;
+    // lane l holds D[4 (l div 16) + r][l mod 16]: channel 4 grp + r of voxel x = row of row y = mt
+    const int x = x0 + row, z = z0 + wave;
+    const bool zx = z < D && x < W;
+    const int cskip = cout - eo.cup;  // channels of out (eo.cup = 0 without a split)
+    const bool vec = ((uintptr_t)out & 7) == 0;
+    typedef __bf16 bf16x4v __attribute__((ext_vector_type(4)));
+    if (eo.up) __syncthreads();  // the input tile becomes the up-sampled part
 #pragma unroll
-    for (int mt = 0; mt < MT; mt++)
+    for (int nt = 0; nt < NTC; nt++) {
+        const int co = co_base + nt * 16 + grp * 4;
+        float bv[4];
 #pragma unroll
-        for (int nt = 0; nt < NTC; nt++) {
-            const int co = co_base + nt * 16 + row;
-            const float bv = bias ? bias[co] : 0.f;
+        for (int r = 0; r < 4; r++) bv[r] = bias ? bias[co + r] : 0.f;
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++) {
+            const int y = y0 + mt;
+            bf16x4v v;
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                const int x = x0 + grp * 4 + r, y = y0 + mt;
-                if (x < W && y < H && z < D) {
-                    float val = acc[mt][nt][r] + bv;
-                    if (relu) val = fmaxf(val, 0.f);
-                    ob[(size_t)(mt * W + r) * cout + nt * 16] = (bf16)val;
-                }
+                float val = acc[mt][nt][r] + bv[r];
+                if (relu) val = fmaxf(val, 0.f);
+                v[r] = (bf16)val;
+            }
+            if (co < eo.cup) {  // uniform: cup is a multiple of 16
+                *(bf16x4v *)(tile + ((wave * TY + mt) * TX + row) * (NTC * 16) + nt * 16 + grp * 4) = v;
+                continue;
+            }
+            if (!(zx && y < H)) continue;
+            const size_t o = ((((size_t)n * D + z) * H + y) * W + x) * cskip + (co - eo.cup);
+            if (eo.gate && !eo.up) {
+                const bf16x4v g = *(const bf16x4v *)(eo.gate + o);
+#pragma unroll
+                for (int r = 0; r < 4; r++)
+                    if (!((float)g[r] > 0.f)) v[r] = (bf16)0.0f;
+            }
+            if (vec) {
+                *(bf16x4v *)(out + o) = v;
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; r++) out[o + r] = v[r];
             }
         }
+    }
+    if (!eo.up || co_base >= eo.cup) return;
+    __syncthreads();
+    // coarse voxels of the tile (8 x 2 x 2), 8 channels a thread; children summed z, y, x-major
+    const int nc8 = min(NTC * 16, eo.cup - co_base) >> 3;
+    for (int e = threadIdx.x; e < (TX / 2) * (TY / 2) * (TZ / 2) * nc8; e += NTH) {
+        const int c8 = e % nc8, q = e / nc8;
+        const int cx = q % (TX / 2), cy = q / (TX / 2) % (TY / 2), cz = q / (TX / 2 * (TY / 2));
+        const int X = (x0 >> 1) + cx, Y = (y0 >> 1) + cy, Z = (z0 >> 1) + cz;
+        if (X >= Wc || Y >= Hc || Z >= Dc) continue;
+        float sum[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) sum[j] = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const int vox = ((2 * cz + (k >> 2)) * TY + 2 * cy + ((k >> 1) & 1)) * TX + 2 * cx + (k & 1);
+            const bf16x8 v = *(const bf16x8 *)(tile + vox * (NTC * 16) + c8 * 8);
+#pragma unroll
+            for (int j = 0; j < 8; j++) sum[j] += (float)v[j];
+        }
+        bf16x8 v;
+#pragma unroll
+        for (int j = 0; j < 8; j++) v[j] = (bf16)sum[j];
+        const size_t o = ((((size_t)n * Dc + Z) * Hc + Y) * Wc + X) * eo.cup + co_base + c8 * 8;
+        if (eo.gate) v = gated(v, *(const bf16x8 *)(eo.gate + o));
+        *(bf16x8 *)(eo.up + o) = v;
+    }
 }
 
 // -------------------------------------------------------------- conv bwd W
@@ -494,14 +582,17 @@ __global__ void k_pool(const bf16 *__restrict__ in, bf16 *__restrict__ out, int 
     }
 }
 
-// Gradient of the pooling: din[fine] += dout[parent] / 8.
-__global__ void k_pool_bwd(const bf16 *__restrict__ dout, bf16 *__restrict__ din, int C, int N, int D, int H,
-                           int W) {
-    const int Dc = D >> 1, Hc = H >> 1, Wc = W >> 1;
-    const long long n = (long long)N * D * H * W * C;
+// Gradient of the pooling: din[fine] += dout[parent] / 8; with a gate, din is
+// then zeroed where not gate > 0.  VEC channels of a voxel per thread.
+template <int VEC>
+__global__ void k_pool_bwd(const bf16 *__restrict__ dout, bf16 *__restrict__ din, const bf16 *__restrict__ gate, int C,
+                           int N, int D, int H, int W) {
+    typedef __bf16 vec __attribute__((ext_vector_type(VEC)));
+    const int Dc = D >> 1, Hc = H >> 1, Wc = W >> 1, G = C / VEC;
+    const long long n = (long long)N * D * H * W * G;
     for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
-        const int c = (int)(e % C);
-        long long t = e / C;
+        const int c = (int)(e % G) * VEC;
+        long long t = e / G;
         const int x = (int)(t % W);
         t /= W;
         const int y = (int)(t % H);
@@ -509,15 +600,26 @@ __global__ void k_pool_bwd(const bf16 *__restrict__ dout, bf16 *__restrict__ din
         const int z = (int)(t % D);
         const int b = (int)(t / D);
         const size_t p = (((size_t)b * Dc + (z >> 1)) * Hc + (y >> 1)) * Wc + (x >> 1);
-        din[e] = (bf16)((float)din[e] + 0.125f * (float)dout[p * C + c]);
+        vec v = *(vec *)(din + e * VEC);
+        const vec g = *(const vec *)(dout + p * C + c);
+#pragma unroll
+        for (int j = 0; j < VEC; j++) v[j] = (bf16)((float)v[j] + 0.125f * (float)g[j]);
+        if (gate) {
+            const vec q = *(const vec *)(gate + e * VEC);
+#pragma unroll
+            for (int j = 0; j < VEC; j++)
+                if (!((float)q[j] > 0.f)) v[j] = (bf16)0.0f;
+        }
+        *(vec *)(din + e * VEC) = v;
     }
 }
 
 // Split the gradient of a concatenated, partly upsampled input:
 // dup[coarse][c] = sum over its 8 fine children of dx[fine][c] (c < ca), and
 // dskip[fine][c - ca] = dx[fine][c] (c >= ca; the pooling path adds its share later).
+// gate (may be null): dup is zeroed where not gate > 0.
 __global__ void k_split_grad(const bf16 *__restrict__ dx, int ca, int cb, bf16 *__restrict__ dup,
-                             bf16 *__restrict__ dskip, int N, int D, int H, int W) {
+                             bf16 *__restrict__ dskip, const bf16 *__restrict__ gate, int N, int D, int H, int W) {
     const int cin = ca + cb;
     const int Dc = D >> 1, Hc = H >> 1, Wc = W >> 1;
     const long long nc = (long long)N * Dc * Hc * Wc * ca;
@@ -536,7 +638,7 @@ __global__ void k_split_grad(const bf16 *__restrict__ dx, int ca, int cb, bf16 *
             const size_t vox = (((size_t)b * D + 2 * z + (q >> 2)) * H + 2 * y + ((q >> 1) & 1)) * W + 2 * x + (q & 1);
             s += (float)dx[vox * cin + c];
         }
-        dup[e] = (bf16)s;
+        dup[e] = !gate || (float)gate[e] > 0.f ? (bf16)s : (bf16)0.0f;
     }
     if (!dskip) return;
     const long long nf = (long long)N * D * H * W * cb;
@@ -710,7 +812,8 @@ __global__ void k_coarsen(const double *__restrict__ rho, const int8_t *__restri
 }
 
 // Loss = mean over the active cells of the batch of (y - t)^2, with y the
-// head output and t = 256 target / s_n.  Writes dx (bf16), accumulates the
+// head output and t = 256 target / s_n.  Writes dx (bf16; zero where x, a
+// ReLU's output, is not positive), accumulates the
 // head's weight and bias gradients and the loss.
 __global__ void k_head_loss(const bf16 *__restrict__ x, const float *__restrict__ w, const float *__restrict__ b,
                             const int8_t *__restrict__ mask, const double *__restrict__ target,
@@ -744,8 +847,8 @@ __global__ void k_head_loss(const bf16 *__restrict__ x, const float *__restrict_
         bf16x8 lo, hi;
 #pragma unroll
         for (int c = 0; c < 8; c++) {
-            lo[c] = (bf16)(g * w[c]);
-            hi[c] = (bf16)(g * w[c + 8]);
+            lo[c] = xv[c] > 0.f ? (bf16)(g * w[c]) : (bf16)0.0f;
+            hi[c] = xv[c + 8] > 0.f ? (bf16)(g * w[c + 8]) : (bf16)0.0f;
         }
         *(bf16x8 *)(dx + v * 16) = lo;
         *(bf16x8 *)(dx + v * 16 + 8) = hi;
@@ -859,36 +962,37 @@ static bool dims_ok(int n, int d, int h, int w) { return n > 0 && d > 0 && h > 0
 
 template <int CK, int NTC>
 void launch_tile(const bf16 *ina, int ca, int upa, const bf16 *inb, int cb, const bf16 *w, const float *bias, bf16 *out,
-                 int cout, int relu, int n, int D, int H, int W, hipStream_t s) {
+                 int cout, int relu, const ConvOut &eo, int n, int D, int H, int W, hipStream_t s) {
     const int ntx = (W + TX - 1) / TX, nty = (H + TY - 1) / TY, ntz = (D + TZ - 1) / TZ;
     const int nblk = n * ntx * nty * ntz;
     dim3 grid((unsigned)nblk, (unsigned)(cout / (16 * NTC)));
     if constexpr (CK == 32) {
         if ((ca + cb) % 32 == 16) {
             k_conv_tile<CK, NTC, true><<<grid, NTH, 0, s>>>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, D, H, W,
-                                                            ntx, nty, ntz, nblk);
+                                                            ntx, nty, ntz, nblk, eo);
             return;
         }
     }
     k_conv_tile<CK, NTC><<<grid, NTH, 0, s>>>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, D, H, W, ntx, nty, ntz,
-                                              nblk);
+                                              nblk, eo);
 }
 
 template <int CK>
 void launch_tile_ck(const bf16 *ina, int ca, int upa, const bf16 *inb, int cb, const bf16 *w, const float *bias,
-                    bf16 *out, int cout, int relu, int n, int D, int H, int W, hipStream_t s) {
+                    bf16 *out, int cout, int relu, const ConvOut &eo, int n, int D, int H, int W, hipStream_t s) {
     // widest output tiling that still gives about 1024 blocks
     const long long nblk = (long long)n * ((W + TX - 1) / TX) * ((H + TY - 1) / TY) * ((D + TZ - 1) / TZ);
     const int tiles = cout / 16;
-    int ntc = tiles % 4 == 0 ? 4 : tiles % 2 == 0 ? 2 : 1;
-    while (ntc > 1 && nblk * (tiles / ntc) < 1024) ntc /= 2;
-    if (ntc == 4) launch_tile<CK, 4>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, n, D, H, W, s);
-    else if (ntc == 2) launch_tile<CK, 2>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, n, D, H, W, s);
-    else launch_tile<CK, 1>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, n, D, H, W, s);
+    int ntc = 4;
+    while (ntc > 1 && (tiles % ntc || nblk * (tiles / ntc) < 1024)) ntc--;
+    if (ntc == 4) launch_tile<CK, 4>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, eo, n, D, H, W, s);
+    else if (ntc == 3) launch_tile<CK, 3>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, eo, n, D, H, W, s);
+    else if (ntc == 2) launch_tile<CK, 2>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, eo, n, D, H, W, s);
+    else launch_tile<CK, 1>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, eo, n, D, H, W, s);
 }
 
-bool conv_fwd(const void *in_a, int ca, int up_a, const void *in_b, int cb, const void *w, const float *bias,
-              void *out, int cout, int relu, int n, int d, int h, int wd, hipStream_t s) {
+static bool conv_run(const void *in_a, int ca, int up_a, const void *in_b, int cb, const void *w, const float *bias,
+                     void *out, int cout, int relu, const ConvOut &eo, int n, int d, int h, int wd, hipStream_t s) {
     if (!in_a || !w || !out || ca <= 0 || cb < 0 || (cb > 0 && !in_b) || ca % 8 || cb % 8 || cout <= 0 ||
         cout % 16 || !dims_ok(n, d, h, wd) || (up_a && (d % 2 || h % 2 || wd % 2))) {
         set_error("conv3d: invalid arguments (input channels multiples of 8, output channels of 16)");
@@ -896,9 +1000,34 @@ bool conv_fwd(const void *in_a, int ca, int up_a, const void *in_b, int cb, cons
     }
     const bf16 *A = (const bf16 *)in_a, *B = (const bf16 *)in_b, *W = (const bf16 *)w;
     bf16 *O = (bf16 *)out;
-    if (ca + cb <= 16) launch_tile_ck<16>(A, ca, up_a, B, cb, W, bias, O, cout, relu, n, d, h, wd, s);
-    else launch_tile_ck<32>(A, ca, up_a, B, cb, W, bias, O, cout, relu, n, d, h, wd, s);
+    if (ca + cb <= 16) launch_tile_ck<16>(A, ca, up_a, B, cb, W, bias, O, cout, relu, eo, n, d, h, wd, s);
+    else launch_tile_ck<32>(A, ca, up_a, B, cb, W, bias, O, cout, relu, eo, n, d, h, wd, s);
     return hip_ok(hipGetLastError(), "conv3d launch");
+}
+
+bool conv_fwd(const void *in_a, int ca, int up_a, const void *in_b, int cb, const void *w, const float *bias,
+              void *out, int cout, int relu, int n, int d, int h, int wd, hipStream_t s) {
+    return conv_run(in_a, ca, up_a, in_b, cb, w, bias, out, cout, relu, ConvOut{}, n, d, h, wd, s);
+}
+
+bool conv_grad(const void *dout, int cout, const void *wf, const void *gate, void *dx, int cin, int n, int d, int h,
+               int wd, hipStream_t s) {
+    ConvOut eo;
+    eo.gate = (const bf16 *)gate;
+    return conv_run(dout, cout, 0, nullptr, 0, wf, nullptr, dx, cin, 0, eo, n, d, h, wd, s);
+}
+
+bool conv_grad_split(const void *dout, int cout, const void *wf, int ca, int cb, const void *gate, void *dup,
+                     void *dskip, int n, int d, int h, int wd, hipStream_t s) {
+    if (!dup || !dskip || ca % 16 || cb % 16 || d % 2 || h % 2 || wd % 2) {
+        set_error("conv3d split gradient: invalid arguments");
+        return false;
+    }
+    ConvOut eo;
+    eo.gate = (const bf16 *)gate;
+    eo.up = (bf16 *)dup;
+    eo.cup = ca;
+    return conv_run(dout, cout, 0, nullptr, 0, wf, nullptr, dskip, ca + cb, 0, eo, n, d, h, wd, s);
 }
 
 bool conv_bwd_weight(const void *dout, int cout, const void *in_a, int ca, int up_a, const void *in_b, int cb,
@@ -935,15 +1064,26 @@ bool pool2(const void *in, void *out, int c, int n, int d, int h, int wd, hipStr
     return hip_ok(hipGetLastError(), "pool launch");
 }
 
-bool pool2_bwd(const void *dout, void *din, int c, int n, int d, int h, int wd, hipStream_t s) {
+bool pool2_bwd(const void *dout, void *din, const void *gate, int c, int n, int d, int h, int wd, hipStream_t s) {
     const long long cnt = (long long)n * d * h * wd * c;
-    k_pool_bwd<<<blocks_for(cnt), 256, 0, s>>>((const bf16 *)dout, (bf16 *)din, c, n, d, h, wd);
+    // 16-byte accesses where every voxel's channels allow them: at 8 x 64^3 x 16
+    // 102 us with one channel a thread (the index divisions) plus 50 us for the
+    // gate as a pass of its own, 32 us with both
+    const bool vec = c % 8 == 0 && (((uintptr_t)dout | (uintptr_t)din | (uintptr_t)gate) & 15) == 0;
+    if (vec)
+        k_pool_bwd<8><<<blocks_for(cnt / 8), 256, 0, s>>>((const bf16 *)dout, (bf16 *)din, (const bf16 *)gate, c, n, d,
+                                                          h, wd);
+    else
+        k_pool_bwd<1><<<blocks_for(cnt), 256, 0, s>>>((const bf16 *)dout, (bf16 *)din, (const bf16 *)gate, c, n, d, h,
+                                                      wd);
     return hip_ok(hipGetLastError(), "pool backward launch");
 }
 
-bool split_grad(const void *dx, int ca, int cb, void *dup, void *dskip, int n, int d, int h, int wd, hipStream_t s) {
+bool split_grad(const void *dx, int ca, int cb, void *dup, void *dskip, const void *gate, int n, int d, int h, int wd,
+                hipStream_t s) {
     const long long cnt = (long long)n * d * h * wd * (ca > cb ? ca : cb);
-    k_split_grad<<<blocks_for(cnt), 256, 0, s>>>((const bf16 *)dx, ca, cb, (bf16 *)dup, (bf16 *)dskip, n, d, h, wd);
+    k_split_grad<<<blocks_for(cnt), 256, 0, s>>>((const bf16 *)dx, ca, cb, (bf16 *)dup, (bf16 *)dskip,
+                                                (const bf16 *)gate, n, d, h, wd);
     return hip_ok(hipGetLastError(), "split gradient launch");
 }
 
@@ -1066,7 +1206,7 @@ mg_status mg_nn_pool2_bwd(const void *dout, void *din, int32_t c, int32_t n, int
         set_error("mg_nn_pool2_bwd: invalid arguments");
         return MG_ERR_ARG;
     }
-    NN_RET(nn::pool2_bwd(dout, din, c, n, d, h, wd, (hipStream_t)stream));
+    NN_RET(nn::pool2_bwd(dout, din, nullptr, c, n, d, h, wd, (hipStream_t)stream));
 }
 
 mg_status mg_nn_split_grad(const void *dx, int32_t ca, int32_t cb, void *dup, void *dskip, int32_t n, int32_t d,
@@ -1076,7 +1216,7 @@ mg_status mg_nn_split_grad(const void *dx, int32_t ca, int32_t cb, void *dup, vo
         set_error("mg_nn_split_grad: invalid arguments");
         return MG_ERR_ARG;
     }
-    NN_RET(nn::split_grad(dx, ca, cb, dup, dskip, n, d, h, wd, (hipStream_t)stream));
+    NN_RET(nn::split_grad(dx, ca, cb, dup, dskip, nullptr, n, d, h, wd, (hipStream_t)stream));
 }
 
 mg_status mg_nn_adamw(float *param, void *param_bf16, const float *grad, float *m, float *v, int64_t count, float lr,

@@ -11,6 +11,16 @@ namespace nn {
 // out = [ReLU](conv3x3x3(concat(up2?(in_a), in_b)) + bias); weights [27][cout][cin].
 bool conv_fwd(const void *in_a, int ca, int up_a, const void *in_b, int cb, const void *w, const float *bias,
               void *out, int cout, int relu, int n, int d, int h, int wd, hipStream_t s);
+// Input gradient of a layer, dout convolved with its flipped weights wf; gate
+// (may be null): the activation whose ReLU lies below, dx zeroed where it is
+// not positive.
+bool conv_grad(const void *dout, int cout, const void *wf, const void *gate, void *dx, int cin, int n, int d, int h,
+               int wd, hipStream_t s);
+// ... of a layer whose input was the concatenation of ca up-sampled and cb
+// full-resolution channels (multiples of 16): conv_grad and split_grad in one,
+// the first ca channels summed onto the coarse grid (gated there).
+bool conv_grad_split(const void *dout, int cout, const void *wf, int ca, int cb, const void *gate, void *dup,
+                     void *dskip, int n, int d, int h, int wd, hipStream_t s);
 // dw[27][cout][cin] += weight gradient, dbias[cout] += bias gradient (FP32, atomics).
 bool conv_bwd_weight(const void *dout, int cout, const void *in_a, int ca, int up_a, const void *in_b, int cb,
                      float *dw, float *dbias, int n, int d, int h, int wd, hipStream_t s);
@@ -18,8 +28,9 @@ bool conv_bwd_weight(const void *dout, int cout, const void *in_a, int ca, int u
 bool weight_flip(const void *w, int cout, int cin, void *wt, hipStream_t s);
 bool relu_bwd(void *dy, const void *y, long long count, hipStream_t s);
 bool pool2(const void *in, void *out, int c, int n, int d, int h, int wd, hipStream_t s);
-bool pool2_bwd(const void *dout, void *din, int c, int n, int d, int h, int wd, hipStream_t s);
-bool split_grad(const void *dx, int ca, int cb, void *dup, void *dskip, int n, int d, int h, int wd, hipStream_t s);
+bool pool2_bwd(const void *dout, void *din, const void *gate, int c, int n, int d, int h, int wd, hipStream_t s);
+bool split_grad(const void *dx, int ca, int cb, void *dup, void *dskip, const void *gate, int n, int d, int h, int wd,
+                hipStream_t s);
 // st[2n] = sum of rho^2 over active cells of sample n, st[2n+1] = their count (FP64)
 bool stats(const double *rho, const int8_t *mask, long long vs, int n, double *st, hipStream_t s);
 bool pack(const double *rho, const int8_t *mask, const double *B, const double *st, int S, int n, int dc, int hc,

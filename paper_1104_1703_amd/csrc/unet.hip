@@ -139,10 +139,7 @@ bool ensure_workspace(mg_unet *U, int n, int d, int h, int w, bool train) {
         ok &= (U->gpool[0] = get(16 * vox(2))) != nullptr;
         ok &= (U->gpool[1] = get(32 * vox(3))) != nullptr;
         ok &= (U->gpool[2] = get(64 * vox(4))) != nullptr;
-        long long cat = 48 * vox(1);
-        if (96 * vox(2) > cat) cat = 96 * vox(2);
-        if (192 * vox(3) > cat) cat = 192 * vox(3);
-        ok &= (U->gcat = get(cat)) != nullptr;
+        ok &= (U->gcat = get((kLayers[D3A].ca + kLayers[D3A].cb) * vox(kLayers[D3A].level))) != nullptr;
     }
     if (!ok) {
         free_workspace(U);
@@ -218,43 +215,56 @@ bool backward(mg_unet *U) {
     auto dims = [&](int level, int &d, int &h, int &w) {
         d = U->wd >> (level - 1), h = U->wh >> (level - 1), w = U->ww >> (level - 1);
     };
-    // ReLU backward, weight and bias gradients, and (if dx) the gradient of
-    // the layer's (concatenated) input written to dx.
-    auto back = [&](int l, const void *a, int up, const void *b, void *dx) {
+    // Every gact[l] is written with the ReLU of act[l] already applied, by the
+    // kernel that writes it last.  Weight and bias gradients of layer l:
+    auto weights = [&](int l, const void *a, int up, const void *b) {
         const LayerDef &L = kLayers[l];
         int d, h, w;
         dims(L.level, d, h, w);
-        const long long cnt = (long long)n * d * h * w * L.cout;
-        const int ca = up ? L.ca : L.cb, cb = up ? L.cb : 0;
-        if (!mg::nn::relu_bwd(U->gact[l], U->act[l], cnt, s)) return false;
-        if (!mg::nn::conv_bwd_weight(U->gact[l], L.cout, a, ca, up, b, cb, U->g + U->woff[l], U->g + U->boff[l], n, d,
-                                     h, w, s))
-            return false;
-        if (!dx) return true;
-        return mg::nn::conv_fwd(U->gact[l], L.cout, 0, nullptr, 0, U->pf + U->woff[l], nullptr, dx, L.ca + L.cb, 0, n,
-                                d, h, w, s);
+        return mg::nn::conv_bwd_weight(U->gact[l], L.cout, a, up ? L.ca : L.cb, up, b, up ? L.cb : 0,
+                                       U->g + U->woff[l], U->g + U->boff[l], n, d, h, w, s);
     };
-    auto split = [&](int level, int ca, int cb, void *dup, void *dskip) {
+    // ... and the gradient of the layer's input, gated by `gate` if it was a layer's output
+    auto back = [&](int l, const void *a, int up, const void *b, const void *gate, void *dx) {
+        const LayerDef &L = kLayers[l];
         int d, h, w;
-        dims(level, d, h, w);
-        return mg::nn::split_grad(U->gcat, ca, cb, dup, dskip, n, d, h, w, s);
+        dims(L.level, d, h, w);
+        return weights(l, a, up, b) && mg::nn::conv_grad(U->gact[l], L.cout, U->pf + U->woff[l], gate, dx, L.ca + L.cb,
+                                                         n, d, h, w, s);
     };
-    auto pool_back = [&](void *gp, void *gfine, int c, int level) {
+    // ... split into the up-sampled layer's and the skip's (the pooling path adds its share later)
+    auto back_split = [&](int l, const void *a, const void *b, const void *gate, void *dup, void *dskip) {
+        const LayerDef &L = kLayers[l];
         int d, h, w;
-        dims(level, d, h, w);
-        return mg::nn::pool2_bwd(gp, gfine, c, n, d, h, w, s);
+        dims(L.level, d, h, w);
+        return weights(l, a, 1, b) && mg::nn::conv_grad_split(U->gact[l], L.cout, U->pf + U->woff[l], L.ca, L.cb, gate,
+                                                              dup, dskip, n, d, h, w, s);
+    };
+    auto split = [&](int l, const void *gate, void *dup, void *dskip) {
+        const LayerDef &L = kLayers[l];
+        int d, h, w;
+        dims(L.level, d, h, w);
+        return mg::nn::split_grad(U->gcat, L.ca, L.cb, dup, dskip, gate, n, d, h, w, s);
+    };
+    auto pool_back = [&](void *gp, int l) {
+        int d, h, w;
+        dims(kLayers[l].level, d, h, w);
+        return mg::nn::pool2_bwd(gp, U->gact[l], U->act[l], kLayers[l].cout, n, d, h, w, s);
     };
     void **A = U->act, **G = U->gact;
-    return back(D1B, A[D1A], 0, nullptr, G[D1A]) && back(D1A, A[D2B], 1, A[E1B], U->gcat) &&
-           split(1, 32, 16, G[D2B], G[E1B]) && back(D2B, A[D2A], 0, nullptr, G[D2A]) &&
-           back(D2A, A[D3B], 1, A[E2B], U->gcat) && split(2, 64, 32, G[D3B], G[E2B]) &&
-           back(D3B, A[D3A], 0, nullptr, G[D3A]) && back(D3A, A[M4B], 1, A[E3B], U->gcat) &&
-           split(3, 128, 64, G[M4B], G[E3B]) && back(M4B, A[M4A], 0, nullptr, G[M4A]) &&
-           back(M4A, U->pool[2], 0, nullptr, U->gpool[2]) && pool_back(U->gpool[2], G[E3B], 64, 3) &&
-           back(E3B, A[E3A], 0, nullptr, G[E3A]) && back(E3A, U->pool[1], 0, nullptr, U->gpool[1]) &&
-           pool_back(U->gpool[1], G[E2B], 32, 2) && back(E2B, A[E2A], 0, nullptr, G[E2A]) &&
-           back(E2A, U->pool[0], 0, nullptr, U->gpool[0]) && pool_back(U->gpool[0], G[E1B], 16, 1) &&
-           back(E1B, A[E1A], 0, nullptr, G[E1A]) && back(E1A, U->x0, 0, nullptr, nullptr);
+    // (dec3a's concatenated gradient is kept whole: MG_UNET_CAT_GRAD)
+    return back(D1B, A[D1A], 0, nullptr, A[D1A], G[D1A]) &&
+           back_split(D1A, A[D2B], A[E1B], A[D2B], G[D2B], G[E1B]) &&
+           back(D2B, A[D2A], 0, nullptr, A[D2A], G[D2A]) &&
+           back_split(D2A, A[D3B], A[E2B], A[D3B], G[D3B], G[E2B]) &&
+           back(D3B, A[D3A], 0, nullptr, A[D3A], G[D3A]) && back(D3A, A[M4B], 1, A[E3B], nullptr, U->gcat) &&
+           split(D3A, A[M4B], G[M4B], G[E3B]) && back(M4B, A[M4A], 0, nullptr, A[M4A], G[M4A]) &&
+           back(M4A, U->pool[2], 0, nullptr, nullptr, U->gpool[2]) && pool_back(U->gpool[2], E3B) &&
+           back(E3B, A[E3A], 0, nullptr, A[E3A], G[E3A]) &&
+           back(E3A, U->pool[1], 0, nullptr, nullptr, U->gpool[1]) && pool_back(U->gpool[1], E2B) &&
+           back(E2B, A[E2A], 0, nullptr, A[E2A], G[E2A]) &&
+           back(E2A, U->pool[0], 0, nullptr, nullptr, U->gpool[0]) && pool_back(U->gpool[0], E1B) &&
+           back(E1B, A[E1A], 0, nullptr, A[E1A], G[E1A]) && weights(E1A, U->x0, 0, nullptr);
 }
 
 bool shape_ok(int n, int nx, int ny, int nz, int stride) {
