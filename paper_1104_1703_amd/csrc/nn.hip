@@ -559,26 +559,36 @@ __global__ void k_relu_bwd(bf16 *__restrict__ dy, const bf16 *__restrict__ y, lo
         if (!((float)y[e] > 0.f)) dy[e] = (bf16)0.0f;
 }
 
-// 2x average pooling of a (N, D, H, W, C) tensor into (N, D/2, H/2, W/2, C).
+// 2x average pooling of a (N, D, H, W, C) tensor into (N, D/2, H/2, W/2, C),
+// VEC channels of a voxel per thread.
+template <int VEC>
 __global__ void k_pool(const bf16 *__restrict__ in, bf16 *__restrict__ out, int C, int N, int D, int H, int W) {
-    const int Dc = D >> 1, Hc = H >> 1, Wc = W >> 1;
-    const long long n = (long long)N * Dc * Hc * Wc * C;
+    typedef __bf16 vec __attribute__((ext_vector_type(VEC)));
+    const int Dc = D >> 1, Hc = H >> 1, Wc = W >> 1, G = C / VEC;
+    const long long n = (long long)N * Dc * Hc * Wc * G;
     for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
-        const int c = (int)(e % C);
-        long long t = e / C;
+        const int c = (int)(e % G) * VEC;
+        long long t = e / G;
         const int x = (int)(t % Wc);
         t /= Wc;
         const int y = (int)(t % Hc);
         t /= Hc;
         const int z = (int)(t % Dc);
         const int b = (int)(t / Dc);
-        float s = 0.f;
+        float s[VEC];
+#pragma unroll
+        for (int j = 0; j < VEC; j++) s[j] = 0.f;
 #pragma unroll
         for (int q = 0; q < 8; q++) {
             const size_t vox = (((size_t)b * D + 2 * z + (q >> 2)) * H + 2 * y + ((q >> 1) & 1)) * W + 2 * x + (q & 1);
-            s += (float)in[vox * C + c];
+            const vec v = *(const vec *)(in + vox * C + c);
+#pragma unroll
+            for (int j = 0; j < VEC; j++) s[j] += (float)v[j];
         }
-        out[e] = (bf16)(0.125f * s);
+        vec o;
+#pragma unroll
+        for (int j = 0; j < VEC; j++) o[j] = (bf16)(0.125f * s[j]);
+        *(vec *)(out + e * VEC) = o;
     }
 }
 
@@ -690,42 +700,160 @@ __device__ __forceinline__ double sample_scale(const double *stats, int n) {
     return s > 0.0 ? s : 1.0;
 }
 
-// Network input at 1/S resolution, 16 channels per voxel: mean of rho over
-// the active fine cells of the block / s, +1 if more than half of the block
-// is active (else -1), mean of B over the block / s, zeros.
+// Network input, 16 channels per voxel: rho on active cells / s, the mask, B / s, zeros.
 __global__ void k_pack(const double *__restrict__ rho, const int8_t *__restrict__ mask, const double *__restrict__ B,
-                       const double *__restrict__ stats, int S, int N, int Dc, int Hc, int Wc, bf16 *__restrict__ x) {
-    const long long Vc = (long long)Dc * Hc * Wc;
-    const long long total = (long long)N * Vc;
-    const int W = Wc * S, H = Hc * S, D = Dc * S;
+                       const double *__restrict__ stats, long long vs, long long total, bf16 *__restrict__ x) {
     for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total; e += (long long)gridDim.x * blockDim.x) {
-        const int n = (int)(e / Vc);
-        long long t = e - n * Vc;
-        const int cx = (int)(t % Wc);
-        t /= Wc;
-        const int cy = (int)(t % Hc);
-        const int cz = (int)(t / Hc);
-        const double is = 1.0 / sample_scale(stats, n);
-        double rs = 0.0, bs = 0.0;
-        int cnt = 0;
-        for (int dz = 0; dz < S; dz++)
-            for (int dy = 0; dy < S; dy++)
-                for (int dx = 0; dx < S; dx++) {
-                    const size_t f = (((size_t)n * D + cz * S + dz) * H + cy * S + dy) * W + cx * S + dx;
-                    if (mask[f] == 1) {
-                        rs += rho[f];
-                        cnt++;
-                    }
-                    if (B) bs += B[f];
-                }
-        const int S3 = S * S * S;
+        const double is = 1.0 / sample_scale(stats, (int)(e / vs));
+        const bool act = mask[e] == 1;
         bf16x8 a = zero8(), b = zero8();
-        a[0] = (bf16)(float)(cnt > 0 ? rs / cnt * is : 0.0);
-        a[1] = (bf16)(2 * cnt > S3 ? 1.0f : -1.0f);
-        a[2] = (bf16)(float)(bs / S3 * is);
+        a[0] = (bf16)(float)(act ? (0.0 + rho[e]) * is : 0.0);  // sums of one term: -0 becomes 0
+        a[1] = (bf16)(act ? 1.0f : -1.0f);
+        a[2] = (bf16)(float)((B ? 0.0 + B[e] : 0.0) * is);
         *(bf16x8 *)(x + e * 16) = a;
         *(bf16x8 *)(x + e * 16 + 8) = b;
     }
+}
+
+// Network input at 1/S resolution: mean of rho over the active fine cells of
+// the block / s, +1 if more than half of the block is active (else -1), mean
+// of B over the block / s, zeros.
+// One sample, in one pass over the fine fields: each
+// thread forms its coarse cell's sums, which wait in
+// `sums` (3 per cell: of rho, of B, the active count) for the scale, and each
+// block its share of k_stats' sums.  Reading rho twice and 8192 atomics on one
+// line of memory took 107 + 38 us at 256^3 and S = 4; this 17 + 9 us
+// (17 MB of mask and the active third of 134 MB of rho).  VEC: rows of a cell are read as 16-byte pieces and
+// mask words (alignment permitting); a row with no active cell reads rho's
+// first piece instead of its own.
+template <int S, bool VEC>
+__global__ __launch_bounds__(NTH) void k_pack_sums(const double *__restrict__ rho, const int8_t *__restrict__ mask,
+                                                   const double *__restrict__ B, int Dc, int Hc, int Wc,
+                                                   double *__restrict__ sums, double *__restrict__ part) {
+    __shared__ double s_a[NTH / 64], s_c[NTH / 64];
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    constexpr int P = S < 4 ? 2 : 4;  // cells of a mask word
+    using word = typename std::conditional<P == 2, uint16_t, uint32_t>::type;
+    const int V = Dc * Hc * Wc;
+    const size_t W = (size_t)Wc * S, H = (size_t)Hc * S;
+    double a = 0.0, c = 0.0;
+    const int e = blockIdx.x * NTH + threadIdx.x;
+    if (e < V) {
+        const int cx = e % Wc, cy = e / Wc % Hc, cz = e / Wc / Hc;
+        double rs = 0.0, bs = 0.0;
+        int cnt = 0;
+#pragma unroll 1
+        for (int dz = 0; dz < S; dz++) {
+            const size_t f0 = ((size_t)(cz * S + dz) * H + (size_t)cy * S) * W + (size_t)cx * S;
+            double r[S][S];
+            bool m[S][S];
+            if constexpr (VEC) {
+                word mw[S][S / P];
+#pragma unroll
+                for (int dy = 0; dy < S; dy++)
+#pragma unroll
+                    for (int q = 0; q < S / P; q++) mw[dy][q] = *(const word *)(mask + f0 + dy * W + q * P);
+#pragma unroll
+                for (int dy = 0; dy < S; dy++) {
+                    bool any = false;
+#pragma unroll
+                    for (int dx = 0; dx < S; dx++) any |= (m[dy][dx] = ((mw[dy][dx / P] >> (8 * (dx % P))) & 255) == 1);
+#pragma unroll
+                    for (int q = 0; q < S / 2; q++) {
+                        const d2 v = *(const d2 *)(any ? rho + f0 + dy * W + 2 * q : rho);
+                        r[dy][2 * q] = v[0];
+                        r[dy][2 * q + 1] = v[1];
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int dy = 0; dy < S; dy++)
+#pragma unroll
+                    for (int dx = 0; dx < S; dx++) {
+                        m[dy][dx] = mask[f0 + dy * W + dx] == 1;
+                        r[dy][dx] = rho[f0 + dy * W + dx];
+                    }
+            }
+#pragma unroll
+            for (int dy = 0; dy < S; dy++)
+#pragma unroll
+                for (int dx = 0; dx < S; dx++)
+                    if (m[dy][dx]) {
+                        rs += r[dy][dx];
+                        a += r[dy][dx] * r[dy][dx];
+                        cnt++;
+                    }
+            if (B)
+#pragma unroll
+                for (int dy = 0; dy < S; dy++)
+#pragma unroll
+                    for (int dx = 0; dx < S; dx++) bs += B[f0 + dy * W + dx];
+        }
+        sums[e] = rs;
+        sums[(size_t)V + e] = bs;
+        sums[2 * (size_t)V + e] = (double)cnt;
+        c = (double)cnt;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o);
+        c += __shfl_xor(c, o);
+    }
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    if (lane == 0) {
+        s_a[wv] = a;
+        s_c[wv] = c;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < NTH / 64; q++) {
+            a += s_a[q];
+            c += s_c[q];
+        }
+        part[2 * blockIdx.x] = a;
+        part[2 * blockIdx.x + 1] = c;
+    }
+}
+
+// One block: stats[0], stats[1] from the np partial sums, in a fixed order.
+__global__ __launch_bounds__(1024) void k_stats_sum(const double *__restrict__ part, int np,
+                                                    double *__restrict__ stats) {
+    __shared__ double sa[16], sc[16];
+    double a = 0.0, c = 0.0;
+    for (int q = threadIdx.x; q < np; q += 1024) {
+        a += part[2 * q];
+        c += part[2 * q + 1];
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o);
+        c += __shfl_xor(c, o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sa[threadIdx.x >> 6] = a;
+        sc[threadIdx.x >> 6] = c;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < 16; q++) {
+            a += sa[q];
+            c += sc[q];
+        }
+        stats[0] = a;
+        stats[1] = c;
+    }
+}
+
+__global__ __launch_bounds__(NTH) void k_pack_scale(const double *__restrict__ sums, const double *__restrict__ stats,
+                                                    int S3, int V, bf16 *__restrict__ x) {
+    const int e = blockIdx.x * NTH + threadIdx.x;
+    if (e >= V) return;
+    const double is = 1.0 / sample_scale(stats, 0), rs = sums[e], bs = sums[(size_t)V + e];
+    const int cnt = (int)sums[2 * (size_t)V + e];
+    bf16x8 a = zero8(), b = zero8();
+    a[0] = (bf16)(float)(cnt > 0 ? rs / cnt * is : 0.0);
+    a[1] = (bf16)(2 * cnt > S3 ? 1.0f : -1.0f);
+    a[2] = (bf16)(float)(bs / S3 * is);
+    *(bf16x8 *)(x + (size_t)e * 16) = a;
+    *(bf16x8 *)(x + (size_t)e * 16 + 8) = b;
 }
 
 // Head: phi[v] = s_n / 256 * (sum_c w[c] x[v][c] + b), zero where a mask is
@@ -746,33 +874,62 @@ __global__ void k_head(const bf16 *__restrict__ x, const float *__restrict__ w, 
 // Linear up-sampling of a cell-centred field by 2 per axis: 3/4 of the
 // parent plus 1/4 of the next coarse cell on the child's side (the edge cell
 // repeated past the array end); zero on inactive cells when a mask is given.
-__global__ void k_up2(const double *__restrict__ c, double *__restrict__ f, int N, int Dc, int Hc, int Wc,
-                      const int8_t *__restrict__ mask) {
-    const int D = 2 * Dc, H = 2 * Hc, W = 2 * Wc;
-    const long long total = (long long)N * D * H * W;
-    for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total; e += (long long)gridDim.x * blockDim.x) {
-        long long t = e;
-        const int x = (int)(t % W);
-        t /= W;
-        const int y = (int)(t % H);
-        t /= H;
-        const int z = (int)(t % D);
-        const int n = (int)(t / D);
-        if (mask && mask[e] != 1) {
-            f[e] = 0.0;
-            continue;
+// A thread forms the two z and y children and one x pair of a coarse cell from
+// its 27 neighbours and stores pairs (16 bytes with VEC): one thread per child,
+// with 64-bit index divisions and 8 loads for one store, took 66 us for
+// 128^3 -> 256^3, this 40 us (168 MB).
+template <bool VEC>
+__global__ __launch_bounds__(NTH) void k_up2(const double *__restrict__ c, double *__restrict__ f, int Dc, int Hc,
+                                             int Wc, const int8_t *__restrict__ mask) {
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    const int e = blockIdx.x * NTH + threadIdx.x;  // row (y) and x of a coarse plane
+    if (e >= Hc * Wc) return;
+    const int pz = blockIdx.y, py = e / Wc, px = e - py * Wc;
+    const size_t base = (size_t)blockIdx.z * Dc * Hc * Wc, cpl = (size_t)Hc * Wc;
+    const size_t H = 2 * (size_t)Hc, W = 2 * (size_t)Wc;
+    const size_t f0 = (((size_t)blockIdx.z * 2 * Dc + 2 * pz) * H + 2 * py) * W + 2 * px;
+    bool act[2][2][2];
+    bool any = false;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const size_t o = f0 + ((q >> 1) * H + (q & 1)) * W;
+#pragma unroll
+        for (int dx = 0; dx < 2; dx++) any |= (act[q >> 1][q & 1][dx] = !mask || mask[o + dx] == 1);
+    }
+    const auto mix = [](double near, double far) { return __builtin_fma(0.75, near, 0.25 * far); };
+    const auto put = [&](int dz, int dy, double v0, double v1) {
+        const size_t o = f0 + (dz * H + dy) * W;
+        v0 = act[dz][dy][0] ? v0 : 0.0;
+        v1 = act[dz][dy][1] ? v1 : 0.0;
+        if constexpr (VEC) {
+            *(d2 *)(f + o) = d2{v0, v1};
+        } else {
+            f[o] = v0;
+            f[o + 1] = v1;
         }
-        const int px = x >> 1, py = y >> 1, pz = z >> 1;
-        const int qx = min(max((x & 1) ? px + 1 : px - 1, 0), Wc - 1);
-        const int qy = min(max((y & 1) ? py + 1 : py - 1, 0), Hc - 1);
-        const int qz = min(max((z & 1) ? pz + 1 : pz - 1, 0), Dc - 1);
-        const size_t base = (size_t)n * Dc * Hc * Wc;
-        auto at = [&](int zz, int yy, int xx) { return c[base + ((size_t)zz * Hc + yy) * Wc + xx]; };
-        const double z0 = 0.75 * (0.75 * at(pz, py, px) + 0.25 * at(pz, py, qx)) +
-                          0.25 * (0.75 * at(pz, qy, px) + 0.25 * at(pz, qy, qx));
-        const double z1 = 0.75 * (0.75 * at(qz, py, px) + 0.25 * at(qz, py, qx)) +
-                          0.25 * (0.75 * at(qz, qy, px) + 0.25 * at(qz, qy, qx));
-        f[e] = 0.75 * z0 + 0.25 * z1;
+    };
+    if (!any) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) put(q >> 1, q & 1, 0.0, 0.0);
+        return;
+    }
+    double v[3][3][3];
+#pragma unroll
+    for (int k = 0; k < 27; k++) {
+        const int z = min(max(pz + k / 9 - 1, 0), Dc - 1), y = min(max(py + k / 3 % 3 - 1, 0), Hc - 1),
+                  x = min(max(px + k % 3 - 1, 0), Wc - 1);
+        v[k / 9][k / 3 % 3][k % 3] = c[base + z * cpl + (size_t)y * Wc + x];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        double r[2];
+#pragma unroll
+        for (int dx = 0; dx < 2; dx++) {
+            const int qz = (q >> 1) ? 2 : 0, qy = (q & 1) ? 2 : 0, qx = dx ? 2 : 0;
+            r[dx] = mix(mix(mix(v[1][1][1], v[1][1][qx]), mix(v[1][qy][1], v[1][qy][qx])),
+                        mix(mix(v[qz][1][1], v[qz][1][qx]), mix(v[qz][qy][1], v[qz][qy][qx])));
+        }
+        put(q >> 1, q & 1, r[0], r[1]);
     }
 }
 
@@ -815,12 +972,16 @@ __global__ void k_coarsen(const double *__restrict__ rho, const int8_t *__restri
 // head output and t = 256 target / s_n.  Writes dx (bf16; zero where x, a
 // ReLU's output, is not positive), accumulates the
 // head's weight and bias gradients and the loss.
-__global__ void k_head_loss(const bf16 *__restrict__ x, const float *__restrict__ w, const float *__restrict__ b,
+// One block of 1024 threads per CU: the 18 sums take an atomic per block on one
+// line of memory, and with 1024 blocks of 256 those took half of the launch
+// (8 x 64^3: 50 us, now 43, for 153 MB).
+constexpr int HL_NT = 1024;
+__global__ __launch_bounds__(HL_NT) void k_head_loss(const bf16 *__restrict__ x, const float *__restrict__ w, const float *__restrict__ b,
                             const int8_t *__restrict__ mask, const double *__restrict__ target,
                             const double *__restrict__ stats, int N, long long vs, bf16 *__restrict__ dx,
                             float *__restrict__ dw, float *__restrict__ db, double *__restrict__ loss) {
-    __shared__ float s_dw[NTH / 64][17];
-    __shared__ double s_l[NTH / 64];
+    __shared__ float s_dw[HL_NT / 64][17];
+    __shared__ double s_l[HL_NT / 64];
     double count = 0.0;
     for (int n = 0; n < N; n++) count += stats[2 * n + 1];
     const double inv_count = count > 0.0 ? 1.0 / count : 0.0;
@@ -869,13 +1030,13 @@ __global__ void k_head_loss(const bf16 *__restrict__ x, const float *__restrict_
     __syncthreads();
     if (threadIdx.x < 17) {
         float t = 0.f;
-        for (int q = 0; q < NTH / 64; q++) t += s_dw[q][threadIdx.x];
+        for (int q = 0; q < HL_NT / 64; q++) t += s_dw[q][threadIdx.x];
         if (threadIdx.x < 16) atomicAdd(&dw[threadIdx.x], t);
         else atomicAdd(db, t);
     }
     if (threadIdx.x == 0) {
         double t = 0.0;
-        for (int q = 0; q < NTH / 64; q++) t += s_l[q];
+        for (int q = 0; q < HL_NT / 64; q++) t += s_l[q];
         atomicAdd(loss, t * inv_count);
     }
 }
@@ -1060,7 +1221,11 @@ bool relu_bwd(void *dy, const void *y, long long count, hipStream_t s) {
 
 bool pool2(const void *in, void *out, int c, int n, int d, int h, int wd, hipStream_t s) {
     const long long cnt = (long long)n * (d / 2) * (h / 2) * (wd / 2) * c;
-    k_pool<<<blocks_for(cnt), 256, 0, s>>>((const bf16 *)in, (bf16 *)out, c, n, d, h, wd);
+    // 16-byte accesses where every voxel's channels allow them (8 x 64^3 x 16: 22 -> 14 us)
+    if (c % 8 == 0 && (((uintptr_t)in | (uintptr_t)out) & 15) == 0)
+        k_pool<8><<<blocks_for(cnt / 8), 256, 0, s>>>((const bf16 *)in, (bf16 *)out, c, n, d, h, wd);
+    else
+        k_pool<1><<<blocks_for(cnt), 256, 0, s>>>((const bf16 *)in, (bf16 *)out, c, n, d, h, wd);
     return hip_ok(hipGetLastError(), "pool launch");
 }
 
@@ -1089,15 +1254,42 @@ bool split_grad(const void *dx, int ca, int cb, void *dup, void *dskip, const vo
 
 bool stats(const double *rho, const int8_t *mask, long long vs, int n, double *st, hipStream_t s) {
     k_fill_f64<<<1, 64, 0, s>>>(st, 2LL * n);
-    dim3 grid(blocks_for(vs, 4096), (unsigned)n);
+    // two atomics a block on one line of memory (about 10 ns each)
+    dim3 grid(std::min(blocks_for(vs, 4096), 1024u), (unsigned)n);
     k_stats<<<grid, NTH, 0, s>>>(rho, mask, vs, st);
     return hip_ok(hipGetLastError(), "stats launch");
 }
 
-bool pack(const double *rho, const int8_t *mask, const double *B, const double *st, int S, int n, int dc, int hc,
-          int wc, void *x, hipStream_t s) {
-    const long long total = (long long)n * dc * hc * wc;
-    k_pack<<<blocks_for(total), 256, 0, s>>>(rho, mask, B, st, S, n, dc, hc, wc, (bf16 *)x);
+bool pack(const double *rho, const int8_t *mask, const double *B, const double *st, int n, long long vs, void *x,
+          hipStream_t s) {
+    k_pack<<<blocks_for(vs * n), 256, 0, s>>>(rho, mask, B, st, vs, vs * n, (bf16 *)x);
+    return hip_ok(hipGetLastError(), "pack launch");
+}
+
+template <int S>
+static void launch_pack_sums(const double *rho, const int8_t *mask, const double *B, int dc, int hc, int wc,
+                             double *sums, double *part, unsigned g, hipStream_t s) {
+    if (((uintptr_t)rho & 15) == 0 && ((uintptr_t)mask & 3) == 0)
+        k_pack_sums<S, true><<<g, NTH, 0, s>>>(rho, mask, B, dc, hc, wc, sums, part);
+    else
+        k_pack_sums<S, false><<<g, NTH, 0, s>>>(rho, mask, B, dc, hc, wc, sums, part);
+}
+
+long long pack_coarse_words(int dc, int hc, int wc) {
+    const long long v = (long long)dc * hc * wc;
+    return 3 * v + 2 * ((v + NTH - 1) / NTH);
+}
+
+bool pack_coarse(const double *rho, const int8_t *mask, const double *B, double *st, int S, int dc, int hc, int wc,
+                 double *work, void *x, hipStream_t s) {
+    const long long v = (long long)dc * hc * wc;
+    const unsigned g = (unsigned)((v + NTH - 1) / NTH);
+    double *part = work + 3 * v;
+    if (S == 2) launch_pack_sums<2>(rho, mask, B, dc, hc, wc, work, part, g, s);
+    else if (S == 4) launch_pack_sums<4>(rho, mask, B, dc, hc, wc, work, part, g, s);
+    else launch_pack_sums<8>(rho, mask, B, dc, hc, wc, work, part, g, s);
+    k_stats_sum<<<1, 1024, 0, s>>>(part, (int)g, st);
+    k_pack_scale<<<g, NTH, 0, s>>>(work, st, S * S * S, (int)v, (bf16 *)x);
     return hip_ok(hipGetLastError(), "pack launch");
 }
 
@@ -1108,7 +1300,9 @@ bool head(const void *x, const float *w, const float *b, const double *st, const
 }
 
 bool up2(const double *c, double *f, int n, int dc, int hc, int wc, const int8_t *mask, hipStream_t s) {
-    k_up2<<<blocks_for(8LL * n * dc * hc * wc), 256, 0, s>>>(c, f, n, dc, hc, wc, mask);
+    const dim3 grid((unsigned)(((long long)hc * wc + NTH - 1) / NTH), (unsigned)dc, (unsigned)n);
+    if (((uintptr_t)f & 15) == 0) k_up2<true><<<grid, NTH, 0, s>>>(c, f, dc, hc, wc, mask);
+    else k_up2<false><<<grid, NTH, 0, s>>>(c, f, dc, hc, wc, mask);
     return hip_ok(hipGetLastError(), "up-sampling launch");
 }
 
@@ -1120,7 +1314,7 @@ bool coarsen(const double *rho, const int8_t *mask, const double *B, int S, int 
 
 bool head_loss(const void *x, const float *w, const float *b, const int8_t *mask, const double *target,
                const double *st, int n, long long vs, void *dx, float *dw, float *db, double *loss, hipStream_t s) {
-    k_head_loss<<<blocks_for(vs * n, 1024), NTH, 0, s>>>((const bf16 *)x, w, b, mask, target, st, n, vs, (bf16 *)dx,
+    k_head_loss<<<std::min(blocks_for(vs * n, HL_NT), 256u), HL_NT, 0, s>>>((const bf16 *)x, w, b, mask, target, st, n, vs, (bf16 *)dx,
                                                          dw, db, loss);
     return hip_ok(hipGetLastError(), "loss launch");
 }

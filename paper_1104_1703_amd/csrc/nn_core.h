@@ -33,8 +33,13 @@ bool split_grad(const void *dx, int ca, int cb, void *dup, void *dskip, const vo
                 hipStream_t s);
 // st[2n] = sum of rho^2 over active cells of sample n, st[2n+1] = their count (FP64)
 bool stats(const double *rho, const int8_t *mask, long long vs, int n, double *st, hipStream_t s);
-bool pack(const double *rho, const int8_t *mask, const double *B, const double *st, int S, int n, int dc, int hc,
-          int wc, void *x, hipStream_t s);
+bool pack(const double *rho, const int8_t *mask, const double *B, const double *st, int n, long long vs, void *x,
+          hipStream_t s);
+// One sample at 1/S resolution (S = 2, 4 or 8): st and the packed input in one
+// pass; work: pack_coarse_words doubles.
+long long pack_coarse_words(int dc, int hc, int wc);
+bool pack_coarse(const double *rho, const int8_t *mask, const double *B, double *st, int S, int dc, int hc, int wc,
+                 double *work, void *x, hipStream_t s);
 bool head(const void *x, const float *w, const float *b, const double *st, const int8_t *mask, double *phi,
           long long vs, int n, hipStream_t s);
 bool up2(const double *c, double *f, int n, int dc, int hc, int wc, const int8_t *mask, hipStream_t s);

@@ -81,8 +81,8 @@ struct mg_unet {
     std::vector<void *> ws;
     void *x0 = nullptr, *act[NLAYER] = {}, *pool[3] = {};
     void *gact[NLAYER] = {}, *gpool[3] = {}, *gcat = nullptr;
-    double *yc = nullptr, *up_tmp[2] = {};
-    long long yc_len = 0, up_len[2] = {0, 0};
+    double *yc = nullptr, *up_tmp[2] = {}, *pack_tmp = nullptr;
+    long long yc_len = 0, up_len[2] = {0, 0}, pack_len = 0;
 };
 
 namespace {
@@ -284,7 +284,7 @@ mg_status loss_grad(mg_unet *U, int32_t n, const double *rho, const int8_t *mask
     const long long vs = (long long)nx * ny * nz;
     hipStream_t s = U->stream;
     bool ok = mg::nn::stats(rho, mask, vs, n, U->st, s) &&
-              mg::nn::pack(rho, mask, dirichlet, U->st, 1, n, nz, ny, nx, U->x0, s) && forward(U) &&
+              mg::nn::pack(rho, mask, dirichlet, U->st, n, vs, U->x0, s) && forward(U) &&
               mg::nn::fill_f32(U->g, U->np, s) && mg::nn::fill_f64(U->loss_dev, 1, s) &&
               mg::nn::head_loss(U->act[D1B], U->p + U->head_w, U->p + U->head_b, mask, target, U->st, n, vs,
                                 U->gact[D1B], U->g + U->head_w, U->g + U->head_b, U->loss_dev, s) &&
@@ -411,6 +411,7 @@ void mg_unet_destroy(mg_unet *U) {
     for (void *p : U->fixed) raw_free(U, p);
     raw_free(U, U->st);
     raw_free(U, U->yc);
+    raw_free(U, U->pack_tmp);
     raw_free(U, U->up_tmp[0]);
     raw_free(U, U->up_tmp[1]);
     if (U->loss_host) (void)hipHostFree(U->loss_host);
@@ -526,9 +527,13 @@ mg_status mg_unet_infer(mg_unet *U, const double *rho, const int8_t *mask, const
     if (!ensure_workspace(U, 1, cz, cy, cx, false) || !ensure_stats(U, 1)) return MG_ERR_ALLOC;
     hipStream_t s = U->stream;
     const long long vc = (long long)cx * cy * cz;
-    if (!mg::nn::stats(rho, mask, (long long)nx * ny * nz, 1, U->st, s) ||
-        !mg::nn::pack(rho, mask, dirichlet, U->st, stride, 1, cz, cy, cx, U->x0, s) || !forward(U))
-        return MG_ERR_HIP;
+    if (stride > 1 && !ensure_f64(U, U->pack_tmp, U->pack_len, mg::nn::pack_coarse_words(cz, cy, cx)))
+        return MG_ERR_ALLOC;
+    const bool packed =
+        stride == 1 ? mg::nn::stats(rho, mask, vc, 1, U->st, s) &&
+                          mg::nn::pack(rho, mask, dirichlet, U->st, 1, vc, U->x0, s)
+                    : mg::nn::pack_coarse(rho, mask, dirichlet, U->st, stride, cz, cy, cx, U->pack_tmp, U->x0, s);
+    if (!packed || !forward(U)) return MG_ERR_HIP;
     if (stride == 1) {
         return mg::nn::head(U->act[D1B], U->p + U->head_w, U->p + U->head_b, U->st, mask, phi0, vc, 1, s)
                    ? MG_OK
