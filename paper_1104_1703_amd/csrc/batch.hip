@@ -39,6 +39,7 @@
 #include <new>
 
 #include "coarse_core.h"
+#include "cube_core.h"
 #include "march_core.h"
 
 namespace mg {
@@ -108,13 +109,17 @@ __device__ __forceinline__ bool take(const BRef *__restrict__ refs, const int *_
 // follow the other boundary order, their blocks only read their state word and
 // leave, yet a finest launch of dead blocks still took 15-22 us of its 58 (96
 // patches).  Each span copies the positions of one patch's items of one launch
-// into that launch's map, so that its grid holds live items only.
+// into that launch's map, so that its grid holds live items only; with
+// lev >= 0 it lists the patch level's cubes instead (src: their selector).
 struct Span {
-    int src, dst, n;
+    int src, dst, n, lev;
 };
-__global__ void kb_spans(const Span *__restrict__ spans, int *__restrict__ map) {
+__global__ void kb_spans(const Span *__restrict__ spans, int *__restrict__ map, BRef *__restrict__ cubes) {
     const Span s = spans[blockIdx.x];
-    for (int i = threadIdx.x; i < s.n; i += blockDim.x) map[s.dst + i] = s.src + i;
+    if (s.lev < 0)
+        for (int i = threadIdx.x; i < s.n; i += blockDim.x) map[s.dst + i] = s.src + i;
+    else
+        for (int i = threadIdx.x; i < s.n; i += blockDim.x) cubes[s.dst + i] = BRef{s.lev, s.src | i};
 }
 
 // NORMIN: the pass also writes its item's partial of the residual norm of
@@ -136,6 +141,101 @@ __global__ __launch_bounds__(rb::NT, NORMIN ? 4 : 5) void kb_smooth(const BRef *
         const double t = tr::block_sum(sq);
         if (threadIdx.x == 0) part[poff + w] = t;
     }
+}
+
+// ---- launches of few live items: passes over whole 8^3 cubes (cube_core.h) ----
+// The marches of a launch that cannot fill the chip take their 8 to 20 dependent
+// plane steps whatever their number; a cube is loaded whole and leaves after
+// one memory latency and its two half-sweeps.  Bit for bit the marches.
+// Whole solves of 4 to 32 patches of up to 128^3: 1.2 to 1.7 times as fast (8
+// patches of 24 to 64 cells an edge 3.38 -> 2.06 ms, 4 of 32 to 128 9.03 ->
+// 5.75); 96 patches of up to 96 cells, most of whose cycles have few live
+// patches left, 18.2 -> 16.5.
+// The lines: a finest launch of up to 8192 live cubes (6 to 8 blocks per CU, 4
+// to 5 rounds) and a coarse one of up to 16384 (its marches are shorter but
+// thinner) runs over cubes.  Half and twice these sizes: within 3% on every
+// batch tried, 128 patches of 32 to 128 cells 33.7 ms at 8192 on both, 32.9 so.
+constexpr int LIVE_CUBES_FINE = 8192, LIVE_CUBES_COARSE = 16384;
+
+// Item of the list `cubes`; false for grid padding and patches not served.
+__device__ __forceinline__ bool take_cube(const BRef *__restrict__ cubes, int b, int nb, int count,
+                                          const BLev *__restrict__ lev, const int *__restrict__ state, int order,
+                                          BRef &r, int &x0, int &y0, int &z0) {
+    const int w = rb::xcd_item(b, nb);
+    if (w >= count) return false;
+    r = cubes[w];
+    if (state[r.lev / MAXL] != order) return false;
+    const BLev &L = lev[r.lev];
+    const int idx = r.w & IDX_MASK, tile = L.tiles[idx >> 2];
+    x0 = (tile % L.ntx) * TX + (idx & 3) * cube::C;
+    y0 = (tile / L.ntx) % L.nty * TY;
+    z0 = tile / (L.ntx * L.nty) * TZ;
+    return x0 < L.nx;
+}
+
+template <bool FINE>
+__device__ __forceinline__ auto cube_diag(const BLev &L) {
+    if constexpr (FINE) return L.code;
+    else return L.d;
+}
+
+template <bool FINE, bool PRO>
+__global__ __launch_bounds__(cube::NT) void kb_cube(const BRef *__restrict__ cubes, int count,
+                                                    const BLev *__restrict__ lev, const int *__restrict__ state,
+                                                    int order) {
+    __shared__ cube::Lds<double, FINE, PRO> lds;
+    BRef r;
+    int x0, y0, z0;
+    if (!take_cube(cubes, blockIdx.x, gridDim.x, count, lev, state, order, r, x0, y0, z0)) return;
+    const BLev &L = lev[r.lev];
+    const int sel = r.w >> WBITS, a = sel & 1;
+    cube::rbgs_cube<double, FINE, PRO>(lds, (sel & 2) ? nullptr : L.x[a], L.x[a ^ 1], L.f, cube_diag<FINE>(L), L.nx,
+                                       L.ny, L.nz, L.h2, x0, y0, z0, PRO ? L.cx[(sel >> 2) & 1] : nullptr, L.cnx,
+                                       L.cny, L.cnz);
+}
+
+// The last pre-smoothing pass, its residual and R1.
+template <bool FINE>
+__global__ __launch_bounds__(cube::NT) void kb_cube_restrict(const BRef *__restrict__ cubes, int count,
+                                                             const BLev *__restrict__ lev,
+                                                             const int *__restrict__ state, int order) {
+    __shared__ cube::LdsRes<double, FINE> lds;
+    BRef r;
+    int x0, y0, z0;
+    if (!take_cube(cubes, blockIdx.x, gridDim.x, count, lev, state, order, r, x0, y0, z0)) return;
+    const BLev &L = lev[r.lev];
+    const int sel = r.w >> WBITS, a = sel & 1;
+    cube::rbgs_cube_restrict<double, FINE>(lds, (sel & 2) ? nullptr : L.x[a], L.x[a ^ 1], L.f, cube_diag<FINE>(L),
+                                           L.nx, L.ny, L.nz, L.h2, L.ih2, x0, y0, z0, L.cd, L.cf, L.cnx, L.cny,
+                                           L.cnz);
+}
+
+// The first finest pass of a cycle: the first nitems blocks (a multiple of 8)
+// take the residual-norm partial of one smoother item each, the others a cube.
+__global__ __launch_bounds__(cube::NT) void kb_cube_norm(const BRef *__restrict__ refs, const int *__restrict__ map,
+                                                         int count, int nitems, const BRef *__restrict__ cubes,
+                                                         int ncubes, const BLev *__restrict__ lev,
+                                                         const int *__restrict__ state, int order,
+                                                         double *__restrict__ part, int poff) {
+    __shared__ cube::Lds<double, true, false> lds;
+    BRef r;
+    const int b = blockIdx.x;
+    if (b < nitems) {  // uniform per block
+        if (b >= count) return;
+        const int w = map ? map[b] : b;
+        r = refs[w];
+        if (state[r.lev / MAXL] != order) return;
+        const BLev &L = lev[r.lev];
+        const double t = tr::block_sum(tr::item_norm(L.segs[r.w & IDX_MASK], L.x[(r.w >> WBITS) & 1], L.f, L.code,
+                                                     L.nx, L.ny, L.nz, L.ih2));
+        if (threadIdx.x == 0) part[poff + w] = t;
+        return;
+    }
+    int x0, y0, z0;
+    if (!take_cube(cubes, b - nitems, gridDim.x - nitems, ncubes, lev, state, order, r, x0, y0, z0)) return;
+    const BLev &L = lev[r.lev];
+    const int a = (r.w >> WBITS) & 1;
+    cube::rbgs_cube<double, true, false>(lds, L.x[a], L.x[a ^ 1], L.f, L.code, L.nx, L.ny, L.nz, L.h2, x0, y0, z0);
 }
 
 template <int MODE>
@@ -513,11 +613,15 @@ struct mg_batch {
         // launches' maps hold now (empty: none) and their live items
         struct Range {
             int launch, patch, first, n;
+            int lev, sel, cubes;  // the items' level and selector; smoother launches: the level's cubes
         };
         std::vector<Range> ranges;
         std::vector<char> mapped;
-        std::vector<int> live;
-        mg::Span *spans = nullptr, *pin_spans = nullptr;  // device, pinned: one per range
+        std::vector<int> live, live_cubes;  // live_cubes: -1 where a launch runs its items
+        std::vector<int> cube_max, cube_at;  // per launch: most live cubes it runs over (0: its items always), their place
+        std::vector<char> fused;             // a smoother launch and the restriction after it serve the same patches
+        mg::Span *spans = nullptr, *pin_spans = nullptr;  // device, pinned: two per range
+        mg::BRef *cubes = nullptr;                        // device: the launches' live cubes
     };
     Prog begin, end, pre, cycle[3];
     mg::BRef *refs = nullptr;                    // device, all programs' work items
@@ -972,13 +1076,42 @@ bool build_programs(mg_batch *B) {
             const Launch &k = g->k[i];
             if (k.kind == K_FIN) continue;
             for (int j = 0; j < k.count;) {  // a launch lists its patches one after the other
-                const int p = refs[k.first + j].lev / MAXL, j0 = j;
+                const BRef r0 = refs[k.first + j];
+                const int p = r0.lev / MAXL, l = r0.lev % MAXL, j0 = j;
                 while (j < k.count && refs[k.first + j].lev / MAXL == p) j++;
-                g->ranges.push_back({(int)i, p, j0, j - j0});
+                const int o = g == &B->cycle[1] ? 1 : 2;
+                g->ranges.push_back({(int)i, p, j0, j - j0, r0.lev, r0.w & ~IDX_MASK,
+                                     4 * B->patches[p]->lev[l].od[l == 0 ? 2 : o].ntiles});
             }
         }
-        g->spans = balloc<Span>(B, g->ranges.size());
-        BHIP(hipHostMalloc((void **)&g->pin_spans, std::max<size_t>(1, g->ranges.size()) * sizeof(Span),
+        const auto of = [&](size_t i) {  // patches and levels of launch i
+            std::vector<int> v;
+            for (const auto &r : g->ranges)
+                if (r.launch == (int)i) v.push_back(r.lev);
+            return v;
+        };
+        g->cube_max.assign(g->k.size(), 0);
+        g->cube_at.assign(g->k.size(), 0);
+        int ncubes = 0;
+        g->fused.assign(g->k.size(), 0);
+        for (size_t i = 0; i < g->k.size() && !B->opt.fuse_passes; i++) {
+            const int kind = g->k[i].kind;
+            if (kind <= K_SM2P || kind == K_SM0N) {
+                int all = 0;
+                for (const auto &r : g->ranges)
+                    if (r.launch == (int)i) all += r.cubes;
+                const bool fine = kind == K_SM0 || kind == K_SM0P || kind == K_SM0N;
+                g->cube_max[i] = std::min(all, fine ? LIVE_CUBES_FINE : LIVE_CUBES_COARSE);
+                g->cube_at[i] = ncubes;
+                ncubes += g->cube_max[i];
+            }
+            const bool plain = kind == K_SM0 || kind == K_SM1 || kind == K_SM2;
+            g->fused[i] = plain && i + 1 < g->k.size() && g->k[i + 1].kind == (kind == K_SM0 ? K_RES0 : K_RESC) &&
+                          of(i) == of(i + 1);
+        }
+        g->spans = balloc<Span>(B, 2 * g->ranges.size());
+        g->cubes = balloc<BRef>(B, ncubes);
+        BHIP(hipHostMalloc((void **)&g->pin_spans, std::max<size_t>(1, 2 * g->ranges.size()) * sizeof(Span),
                            hipHostMallocDefault));
     }
     B->nfirst = upload(B, first);
@@ -1116,28 +1249,79 @@ void launch(mg_batch *B, const Launch &k, int order, const int *state, hipStream
     }
 }
 
+// A smoother launch of g over its live cubes; fused: with the restriction.
+void launch_cubes(mg_batch *B, const mg_batch::Prog &g, size_t i, bool fused, int order, const int *state,
+                  hipStream_t s) {
+    const Launch &k = g.k[i];
+    const BRef *c = g.cubes + g.cube_at[i];
+    const int n = g.live_cubes[i];
+    const BLev *lev = B->lev[order];
+    const unsigned gr = grid8(n);
+    constexpr int NT = cube::NT;
+    switch (k.kind) {
+        case K_SM0:
+            if (fused) kb_cube_restrict<true><<<gr, NT, 0, s>>>(c, n, lev, state, order);
+            else kb_cube<true, false><<<gr, NT, 0, s>>>(c, n, lev, state, order);
+            break;
+        case K_SM0P: kb_cube<true, true><<<gr, NT, 0, s>>>(c, n, lev, state, order); break;
+        case K_SM1:
+        case K_SM2:
+            if (fused) kb_cube_restrict<false><<<gr, NT, 0, s>>>(c, n, lev, state, order);
+            else kb_cube<false, false><<<gr, NT, 0, s>>>(c, n, lev, state, order);
+            break;
+        case K_SM1P:
+        case K_SM2P: kb_cube<false, true><<<gr, NT, 0, s>>>(c, n, lev, state, order); break;
+        case K_SM0N: {
+            const bool whole = g.live[i] == k.count;
+            const unsigned gi = grid8(g.live[i]);
+            kb_cube_norm<<<gi + gr, NT, 0, s>>>(B->refs + k.first, whole ? nullptr : B->map + k.first, g.live[i],
+                                                (int)gi, c, n, lev, state, order, B->part, k.poff);
+            break;
+        }
+        default: break;
+    }
+}
+
 // The program for the patches marked in `on` (the ones `state` gives to
-// `order`): launches of live items only.
+// `order`): launches of live items only; smoother launches of few
+// live cubes run over those instead of their items.
 void run_live(mg_batch *B, mg_batch::Prog &g, int order, const int *state, const std::vector<char> &on,
               hipStream_t s) {
     if (g.mapped != on) {
         g.live.assign(g.k.size(), 0);
+        g.live_cubes.assign(g.k.size(), 0);
+        for (const auto &r : g.ranges)
+            if (on[r.patch]) g.live_cubes[r.launch] += r.cubes;
+        for (size_t i = 0; i < g.k.size(); i++)
+            g.live_cubes[i] = g.cube_max[i] > 0 && g.live_cubes[i] <= g.cube_max[i] ? 0 : -1;
         int ns = 0;
         for (const auto &r : g.ranges)
             if (on[r.patch]) {
-                g.pin_spans[ns++] = Span{r.first, g.k[r.launch].first + g.live[r.launch], r.n};
-                g.live[r.launch] += r.n;
+                const int i = r.launch;
+                if (g.live_cubes[i] >= 0) {
+                    g.pin_spans[ns++] = Span{r.sel, g.cube_at[i] + g.live_cubes[i], r.cubes, r.lev};
+                    g.live_cubes[i] += r.cubes;
+                }
+                g.pin_spans[ns++] = Span{r.first, g.k[i].first + g.live[i], r.n, -1};
+                g.live[i] += r.n;
             }
         g.mapped = on;
         if (ns > 0) {
             BHIP(hipMemcpyAsync(g.spans, g.pin_spans, ns * sizeof(Span), hipMemcpyHostToDevice, s));
-            kb_spans<<<ns, 256, 0, s>>>(g.spans, B->map);
+            kb_spans<<<ns, 256, 0, s>>>(g.spans, B->map, g.cubes);
         }
     }
     for (size_t i = 0; i < g.k.size(); i++) {
         const Launch &k = g.k[i];
-        if (k.kind == K_FIN || g.live[i] == k.count) launch(B, k, order, state, s);
-        else if (g.live[i] > 0) launch(B, k, order, state, s, g.live[i]);
+        if (g.live_cubes[i] >= 0) {
+            if (g.live_cubes[i] == 0) continue;
+            launch_cubes(B, g, i, g.fused[i], order, state, s);
+            if (g.fused[i]) i++;  // the restriction has run
+        } else if (k.kind == K_FIN || g.live[i] == k.count) {
+            launch(B, k, order, state, s);
+        } else if (g.live[i] > 0) {
+            launch(B, k, order, state, s, g.live[i]);
+        }
     }
     BHIP(hipGetLastError());
 }
@@ -1377,6 +1561,14 @@ mg_status solve_batch_phased(mg_batch *B, const double *const *rho, double *cons
     // is the initial one, already taken.
     std::vector<int> run;
     std::vector<char> on(n);
+    // the state words on the device, by slot: copied only when they change
+    std::vector<int> sent[3];
+    const auto send = [&](int slot, int *dev, hipStream_t so) {
+        const int *v = B->pin_state + slot * n;
+        if ((int)sent[slot].size() == n && !memcmp(sent[slot].data(), v, n * sizeof(int))) return;
+        BHIP(hipMemcpyAsync(dev, v, n * sizeof(int), hipMemcpyHostToDevice, so));
+        sent[slot].assign(v, v + n);
+    };
     for (int round = 0;; round++) {
         run.clear();
         for (int p = 0; p < n; p++)
@@ -1387,7 +1579,7 @@ mg_status solve_batch_phased(mg_batch *B, const double *const *rho, double *cons
             sp[p] = S[p].active ? 2 : 0;
             on[p] = S[p].active;
         }
-        BHIP(hipMemcpyAsync(B->state[3], sp, n * sizeof(int), hipMemcpyHostToDevice, s));
+        send(0, B->state[3], s);
         run_program(B, B->pre, 2, B->state[3], &on);
         BHIP(hipMemcpyAsync(B->norm2_host, B->norm2, 2 * n * sizeof(double), hipMemcpyDeviceToHost, s));
         BHIP(hipStreamSynchronize(s));
@@ -1417,7 +1609,7 @@ mg_status solve_batch_phased(mg_batch *B, const double *const *rho, double *cons
             const bool aside = o == 1 && !B->opt.use_graph;
             const hipStream_t so = aside ? B->side : s;
             if (aside) BHIP(hipStreamWaitEvent(so, B->forked, 0));
-            BHIP(hipMemcpyAsync(B->state[o], sv, n * sizeof(int), hipMemcpyHostToDevice, so));
+            send(o, B->state[o], so);
             run_program(B, B->cycle[o], o, B->state[o], &on, so);
             if (aside) {
                 BHIP(hipEventRecord(B->joined, so));
