@@ -817,7 +817,10 @@ void ensure_coarse_clean(mg_hierarchy *H, int order) {
     H->coarse_order_state = order;
 }
 
+// Zero iterates of a coarse level, whose active cells depend on the order; the
+// finest level's are the same in both and its other cells always hold zero.
 void zero_level_x(mg_hierarchy *H, int l) {
+    if (l == 0) return;
     Level &L = H->lev[l];
     for (int b = 0; b < 2; b++) HIPCHK(hipMemsetAsync(L.x[b], 0, L.n * sizeof(double), H->stream));
 }
@@ -1613,9 +1616,15 @@ mg_status mg_vcycle(mg_hierarchy *H, int32_t order, double *x_dev, const double 
         const OrderData &od0 = odata(H, 0, order);
         ensure_coarse_clean(H, order);
         launch_copy_masked(L0, 0, od0, x_dev, L0.x[0], H->stream);
-        HIPCHK(hipMemcpyAsync(L0.f, f_dev, L0.n * sizeof(double), hipMemcpyDeviceToDevice, H->stream));
         Cur cur;
         for (int l = 0; l < MAXL; l++) cur.c[l] = 0;
+        // the cycle reads the caller's right-hand side in place
+        struct Lend {
+            Level &L;
+            double *own;
+            ~Lend() { L.f = own; }
+        } lend{L0, L0.f};
+        L0.f = const_cast<double *>(f_dev);
         mg_level(H, 0, order, false, cur, false);
         launch_store(L0, od0, L0.x[cur.c[0]], x_dev, H->stream);
         HIPCHK(hipStreamSynchronize(H->stream));

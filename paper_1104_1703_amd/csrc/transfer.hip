@@ -24,22 +24,69 @@ __device__ __forceinline__ bool block_tile(const int *tiles, int ntiles, int per
     return true;
 }
 
+// Cells of a thread in the copying kernels below: QZ planes of one column of a
+// tile.  Every cell waits for its code before its values, so a thread with one
+// cell (and a block with one plane) waited two memory latencies for 16 bytes;
+// the loads of QZ planes are in flight together.  Inactive cells load the
+// array's first value instead of their own.  160 x 144 x 176, 1.4 M active
+// cells: fold 24.0 -> 20.8 us, copy in 13.0 -> 10.5, store 10.8 -> 7.7.
+struct Cells {
+    size_t p[QZ];
+    bool ok[QZ];
+};
+__device__ __forceinline__ Cells cells(int tile, int part, int ntx, int nty, int nx, int ny, int nz) {
+    Cells c;
+#pragma unroll
+    for (int q = 0; q < QZ; q++) {
+        const TileCoord t = tile_cell(tile, part * QZ + q, ntx, nty, nx, ny, nz);
+        c.ok[q] = t.ok;
+        c.p[q] = t.ok ? (size_t)t.k * nx * ny + (size_t)t.j * nx + t.i : 0;
+    }
+    return c;
+}
+
 __global__ __launch_bounds__(NT) void k_fold(const int *__restrict__ tiles, int ntiles, int ntx, int nty, int nx,
                                              int ny, int nz, double ih2, const uint8_t *__restrict__ code,
                                              const double *__restrict__ rho, const double *__restrict__ B,
                                              const double *__restrict__ phi, double *__restrict__ f,
                                              double *__restrict__ x) {
-    int tile, kk, w;
-    if (!block_tile(tiles, ntiles, TZ, tile, kk, w)) return;
-    fold_cell(tile_cell(tile, kk, ntx, nty, nx, ny, nz), nx, ny, ih2, code, rho, B, phi, f, x);
+    int tile, part, w;
+    if (!block_tile(tiles, ntiles, NQ, tile, part, w)) return;
+    const Cells c = cells(tile, part, ntx, nty, nx, ny, nz);
+    uint8_t cd[QZ];
+    double r[QZ], g[QZ];
+#pragma unroll
+    for (int q = 0; q < QZ; q++) cd[q] = code[c.p[q]];
+#pragma unroll
+    for (int q = 0; q < QZ; q++) {
+        const size_t p = cd[q] != CODE_OFF ? c.p[q] : 0;
+        r[q] = rho[p];
+        g[q] = phi ? phi[p] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < QZ; q++) {
+        if (!c.ok[q]) continue;
+        const size_t p = c.p[q];
+        f[p] = cd[q] == CODE_OFF ? 0.0 : fold_value(p, cd[q], r[q], nx, ny, ih2, code, B);
+        if (x) x[p] = cd[q] == CODE_OFF ? 0.0 : g[q];
+    }
 }
 
 __global__ __launch_bounds__(NT) void k_store(const int *__restrict__ tiles, int ntiles, int ntx, int nty, int nx,
                                               int ny, int nz, const uint8_t *__restrict__ code,
                                               const double *__restrict__ x, double *__restrict__ phi) {
-    int tile, kk, w;
-    if (!block_tile(tiles, ntiles, TZ, tile, kk, w)) return;
-    store_cell(tile_cell(tile, kk, ntx, nty, nx, ny, nz), nx, ny, code, x, phi);
+    int tile, part, w;
+    if (!block_tile(tiles, ntiles, NQ, tile, part, w)) return;
+    const Cells c = cells(tile, part, ntx, nty, nx, ny, nz);
+    uint8_t cd[QZ];
+    double v[QZ];
+#pragma unroll
+    for (int q = 0; q < QZ; q++) cd[q] = code[c.p[q]];
+#pragma unroll
+    for (int q = 0; q < QZ; q++) v[q] = x[cd[q] != CODE_OFF ? c.p[q] : 0];
+#pragma unroll
+    for (int q = 0; q < QZ; q++)
+        if (c.ok[q] && cd[q] != CODE_OFF) phi[c.p[q]] = v[q];
 }
 
 template <bool FINE>
@@ -47,12 +94,18 @@ __global__ __launch_bounds__(NT) void k_copy_masked(const int *__restrict__ tile
                                                     int nx, int ny, int nz, const uint8_t *__restrict__ code,
                                                     const double *__restrict__ dco, const double *__restrict__ src,
                                                     double *__restrict__ dst) {
-    int tile, kk, w;
-    if (!block_tile(tiles, ntiles, TZ, tile, kk, w)) return;
-    const TileCoord t = tile_cell(tile, kk, ntx, nty, nx, ny, nz);
-    if (!t.ok) return;
-    const size_t p = (size_t)t.k * nx * ny + (size_t)t.j * nx + t.i;
-    dst[p] = diag_at<double, FINE>(code, dco, p) != 0.0 ? src[p] : 0.0;
+    int tile, part, w;
+    if (!block_tile(tiles, ntiles, NQ, tile, part, w)) return;
+    const Cells c = cells(tile, part, ntx, nty, nx, ny, nz);
+    bool act[QZ];
+    double v[QZ];
+#pragma unroll
+    for (int q = 0; q < QZ; q++) act[q] = diag_at<double, FINE>(code, dco, c.p[q]) != 0.0;
+#pragma unroll
+    for (int q = 0; q < QZ; q++) v[q] = src[act[q] ? c.p[q] : 0];
+#pragma unroll
+    for (int q = 0; q < QZ; q++)
+        if (c.ok[q]) dst[c.p[q]] = act[q] ? v[q] : 0.0;
 }
 
 // Sum of squares of the residual: partial sums per block (tile quarter), then
@@ -264,23 +317,23 @@ __global__ __launch_bounds__(NT) void k_zero_tiles(const int *__restrict__ tiles
 void launch_fold(const Level &L, const OrderData &od, const double *rho, const double *B, const double *phi,
                  double *f, double *x, hipStream_t s) {
     if (!od.ntiles) return;
-    k_fold<<<gridt(od.ntiles), NT, 0, s>>>(od.tiles, od.ntiles, L.ntx, L.nty, L.nx, L.ny, L.nz, 1.0 / (L.h * L.h),
+    k_fold<<<gridc(od.ntiles), NT, 0, s>>>(od.tiles, od.ntiles, L.ntx, L.nty, L.nx, L.ny, L.nz, 1.0 / (L.h * L.h),
                                            L.code, rho, B, phi, f, x);
 }
 
 void launch_store(const Level &L, const OrderData &od, const double *x, double *phi, hipStream_t s) {
     if (!od.ntiles) return;
-    k_store<<<gridt(od.ntiles), NT, 0, s>>>(od.tiles, od.ntiles, L.ntx, L.nty, L.nx, L.ny, L.nz, L.code, x, phi);
+    k_store<<<gridc(od.ntiles), NT, 0, s>>>(od.tiles, od.ntiles, L.ntx, L.nty, L.nx, L.ny, L.nz, L.code, x, phi);
 }
 
 void launch_copy_masked(const Level &L, int level, const OrderData &od, const double *src, double *dst,
                         hipStream_t s) {
     if (!od.ntiles) return;
     if (level == 0)
-        k_copy_masked<true><<<gridt(od.ntiles), NT, 0, s>>>(od.tiles, od.ntiles, L.ntx, L.nty, L.nx, L.ny, L.nz,
+        k_copy_masked<true><<<gridc(od.ntiles), NT, 0, s>>>(od.tiles, od.ntiles, L.ntx, L.nty, L.nx, L.ny, L.nz,
                                                             L.code, nullptr, src, dst);
     else
-        k_copy_masked<false><<<gridt(od.ntiles), NT, 0, s>>>(od.tiles, od.ntiles, L.ntx, L.nty, L.nx, L.ny, L.nz,
+        k_copy_masked<false><<<gridc(od.ntiles), NT, 0, s>>>(od.tiles, od.ntiles, L.ntx, L.nty, L.nx, L.ny, L.nz,
                                                              nullptr, od.d, src, dst);
 }
 

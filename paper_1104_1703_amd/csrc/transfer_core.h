@@ -137,6 +137,24 @@ __device__ __forceinline__ void column_residual(const T *__restrict__ x, const T
 // the ghost is 2 g_ij - x_i with g_ij = (B_i + B_j)/2 (Sec. 3, Fig. "ghost"),
 // so the known part B_i + B_j moves to the right-hand side.  Active cells are
 // never on the box edge (validated), so their six neighbours exist.
+// f of active cell p with code c and density fv.
+__device__ __forceinline__ double fold_value(size_t p, uint8_t c, double fv, int nx, int ny, double ih2,
+                                             const uint8_t *__restrict__ code, const double *__restrict__ B) {
+    if (B && c > 6) {  // some face neighbour is inactive
+        const size_t pl = (size_t)nx * ny;
+        const double bi = B[p];
+        double g = 0.0;
+        if (code[p - 1] == CODE_OFF) g += bi + B[p - 1];
+        if (code[p + 1] == CODE_OFF) g += bi + B[p + 1];
+        if (code[p - nx] == CODE_OFF) g += bi + B[p - nx];
+        if (code[p + nx] == CODE_OFF) g += bi + B[p + nx];
+        if (code[p - pl] == CODE_OFF) g += bi + B[p - pl];
+        if (code[p + pl] == CODE_OFF) g += bi + B[p + pl];
+        fv -= ih2 * g;
+    }
+    return fv;
+}
+
 __device__ __forceinline__ void fold_cell(const TileCoord &t, int nx, int ny, double ih2,
                                           const uint8_t *__restrict__ code, const double *__restrict__ rho,
                                           const double *__restrict__ B, const double *__restrict__ phi,
@@ -150,19 +168,7 @@ __device__ __forceinline__ void fold_cell(const TileCoord &t, int nx, int ny, do
         if (x) x[p] = 0.0;
         return;
     }
-    double fv = rho[p];
-    if (B && c > 6) {  // some face neighbour is inactive
-        const double bi = B[p];
-        double g = 0.0;
-        if (code[p - 1] == CODE_OFF) g += bi + B[p - 1];
-        if (code[p + 1] == CODE_OFF) g += bi + B[p + 1];
-        if (code[p - nx] == CODE_OFF) g += bi + B[p - nx];
-        if (code[p + nx] == CODE_OFF) g += bi + B[p + nx];
-        if (code[p - pl] == CODE_OFF) g += bi + B[p - pl];
-        if (code[p + pl] == CODE_OFF) g += bi + B[p + pl];
-        fv -= ih2 * g;
-    }
-    f[p] = fv;
+    f[p] = fold_value(p, c, rho[p], nx, ny, ih2, code, B);
     if (x) x[p] = phi ? phi[p] : 0.0;
 }
 
