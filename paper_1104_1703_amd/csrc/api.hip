@@ -499,10 +499,9 @@ void create(mg_hierarchy *H, const int8_t *mask, int nx, int ny, int nz, double 
     unsigned long long *ctr = (unsigned long long *)back, *nact = ctr + 3;
     uint8_t *flags = (uint8_t *)(ctr + NCTR);
     HIPCHK(hipMemsetAsync(ctr, 0, NCTR * sizeof(unsigned long long), s));
-    launch_validate(mask, nx, ny, nz, ctr, s);
-    launch_count0(mask, lev[0].cnt, lev[0].n, s);
+    launch_validate(mask, nx, ny, nz, lev[0].cnt, ctr, s);
     for (int l = 1; l < L; l++) launch_count_up(lev[l - 1], lev[l], s);
-    launch_code0(lev[0], nact, s);
+    launch_code0(lev[0], s);
     {
         uint8_t *fl = flags;
         for (int l = 0; l < L; l++)
@@ -530,7 +529,7 @@ void create(mg_hierarchy *H, const int8_t *mask, int nx, int ny, int nz, double 
         throw Fail{MG_ERR_NO_ACTIVE};
     }
     const unsigned long long *ha = hv + 3;
-    lev[0].od[1].nact = lev[0].od[2].nact = (int64_t)ha[0];
+    lev[0].od[1].nact = lev[0].od[2].nact = (int64_t)hv[2];
     for (int o = 1; o <= 2; o++) {
         H->nlev[o] = 1;
         for (int l = 1; l < L; l++) {

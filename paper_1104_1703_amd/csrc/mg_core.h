@@ -196,10 +196,11 @@ void set_error(const std::string &s);
 bool hip_ok(hipError_t e, const char *what);
 
 // -------- setup kernels (setup.hip) --------
-void launch_validate(const int8_t *mask, int nx, int ny, int nz, unsigned long long *bad, hipStream_t s);
-void launch_count0(const int8_t *mask, int32_t *cnt, size_t n, hipStream_t s);
+// mask checks into bad[3], finest counts into cnt
+void launch_validate(const int8_t *mask, int nx, int ny, int nz, int32_t *cnt, unsigned long long *bad,
+                     hipStream_t s);
 void launch_count_up(const Level &fine, const Level &coarse, hipStream_t s);
-void launch_code0(const Level &L, unsigned long long *nact, hipStream_t s);
+void launch_code0(const Level &L, hipStream_t s);
 void launch_diag(const Level &L, int level, int order, double *d, unsigned long long *nact, hipStream_t s);
 void launch_tile_flags(const Level &L, int level, int order, uint8_t *flags, hipStream_t s);
 void launch_to_float(const double *a, float *b, size_t n, hipStream_t s);

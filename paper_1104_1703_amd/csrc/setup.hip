@@ -4,6 +4,8 @@
 // average of their children.  Averages are kept as exact integer counts c of
 // active finest descendants (m = 2c/8^l - 1), so the domain test m > 0 is
 // 2c > 8^l and the first-order test m = 1 (Sec. 4) is c = 8^l, both exact.
+#include <algorithm>
+
 #include "mg_core.h"
 #include "smooth_core.h"
 
@@ -11,26 +13,54 @@ namespace mg {
 
 namespace {
 
-__global__ void k_validate(const int8_t *__restrict__ mask, int nx, int ny, int nz,
-                           unsigned long long *__restrict__ bad) {
-    size_t n = (size_t)nx * ny * nz;
-    unsigned bad_val = 0, bad_frame = 0, act = 0;
-    for (size_t p = blockIdx.x * (size_t)blockDim.x + threadIdx.x; p < n; p += (size_t)gridDim.x * blockDim.x) {
-        int v = mask[p];
-        int i = (int)(p % nx), j = (int)((p / nx) % ny), k = (int)(p / ((size_t)nx * ny));
-        bool frame = (i == 0 || j == 0 || k == 0 || i == nx - 1 || j == ny - 1 || k == nz - 1);
-        bad_val += (v != 1 && v != -1);
-        bad_frame += (frame && v != -1);
-        act += (v == 1);
-    }
-    if (bad_val) atomicAdd(&bad[0], (unsigned long long)bad_val);
-    if (bad_frame) atomicAdd(&bad[1], (unsigned long long)bad_frame);
-    if (act) atomicAdd(&bad[2], (unsigned long long)act);
+// Sum over the block (of at most 1024 threads), for thread 0.
+__device__ __forceinline__ unsigned block_total(unsigned v) {
+    __shared__ unsigned sm[16];
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
+    __syncthreads();
+    unsigned t = 0;
+    if (threadIdx.x == 0)
+        for (unsigned q = 0; q < (blockDim.x + 63) / 64; q++) t += sm[q];
+    __syncthreads();
+    return t;
 }
 
-__global__ void k_count0(const int8_t *__restrict__ mask, int32_t *__restrict__ cnt, size_t n) {
-    for (size_t p = blockIdx.x * (size_t)blockDim.x + threadIdx.x; p < n; p += (size_t)gridDim.x * blockDim.x)
-        cnt[p] = (mask[p] == 1) ? 1 : 0;
+// Mask checks (bad[0]: values other than +1/-1, bad[1]: active cells in the
+// outermost layer, bad[2]: active cells) and the finest counts.  A thread takes
+// 8 cells at a time; the sums take one atomic a block, of at most
+// 1024: one a wave, of up to 16384 on one line of memory, took 172 us at 128^3,
+// this 15 us (64^3: 34 -> 7).
+__global__ __launch_bounds__(256) void k_validate(const int8_t *__restrict__ mask, int nx, int ny, int nz,
+                                                  int32_t *__restrict__ cnt, unsigned long long *__restrict__ bad) {
+    constexpr int U = 8;
+    const size_t n = (size_t)nx * ny * nz, step = (size_t)gridDim.x * 256 * U;
+    unsigned bad_val = 0, bad_frame = 0, act = 0;
+    for (size_t p0 = (size_t)blockIdx.x * 256 * U + threadIdx.x; p0 < n; p0 += step) {
+        int v[U];
+#pragma unroll
+        for (int q = 0; q < U; q++) v[q] = p0 + q * 256 < n ? mask[p0 + q * 256] : -1;
+#pragma unroll
+        for (int q = 0; q < U; q++) {
+            const size_t p = p0 + q * 256;
+            if (p >= n) break;
+            cnt[p] = v[q] == 1 ? 1 : 0;
+            bad_val += (v[q] != 1 && v[q] != -1);
+            act += (v[q] == 1);
+            if (v[q] != -1) {
+                const int i = (int)(p % nx), j = (int)((p / nx) % ny), k = (int)(p / ((size_t)nx * ny));
+                bad_frame += (i == 0 || j == 0 || k == 0 || i == nx - 1 || j == ny - 1 || k == nz - 1);
+            }
+        }
+    }
+    bad_val = block_total(bad_val);
+    bad_frame = block_total(bad_frame);
+    act = block_total(act);
+    if (threadIdx.x == 0) {
+        if (bad_val) atomicAdd(&bad[0], (unsigned long long)bad_val);
+        if (bad_frame) atomicAdd(&bad[1], (unsigned long long)bad_frame);
+        if (act) atomicAdd(&bad[2], (unsigned long long)act);
+    }
 }
 
 // R1 sum of the mask counts: coarse cell I gets the sum over its 8 children.
@@ -58,30 +88,26 @@ __device__ __forceinline__ bool is_active(int32_t c, int level, int order) {
 // Finest level: with the boundary on the face (theta = 1/2) the diagonal of an
 // active cell's equation is (#active) + 2 (#inactive) = 12 - (#active face
 // neighbours); the code holds it (6..12), CODE_OFF (0) for an inactive cell,
-// so that a zero-filled (skipped) load reads as inactive.
-__global__ void k_code0(const int32_t *__restrict__ cnt, int nx, int ny, int nz, uint8_t *__restrict__ code,
-                        unsigned long long *__restrict__ nact) {
+// so that a zero-filled (skipped) load reads as inactive.  (The active cells
+// have been counted by k_validate: counting them here too, with an atomic a
+// block, made this 147 us at 160 x 144 x 176; 128^3 takes 12 without.)
+__global__ void k_code0(const int32_t *__restrict__ cnt, int nx, int ny, int nz, uint8_t *__restrict__ code) {
     size_t n = (size_t)nx * ny * nz;
     size_t p = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    int a = 0;
-    if (p < n) {
-        int i = (int)(p % nx), j = (int)((p / nx) % ny), k = (int)(p / ((size_t)nx * ny));
-        if (cnt[p] == 1) {
-            a = 1;
-            int na = 0;
-            na += (i > 0 && cnt[p - 1] == 1);
-            na += (i < nx - 1 && cnt[p + 1] == 1);
-            na += (j > 0 && cnt[p - nx] == 1);
-            na += (j < ny - 1 && cnt[p + nx] == 1);
-            na += (k > 0 && cnt[p - (size_t)nx * ny] == 1);
-            na += (k < nz - 1 && cnt[p + (size_t)nx * ny] == 1);
-            code[p] = (uint8_t)(12 - na);
-        } else {
-            code[p] = CODE_OFF;
-        }
+    if (p >= n) return;
+    if (cnt[p] != 1) {
+        code[p] = CODE_OFF;
+        return;
     }
-    int c = __syncthreads_count(a);
-    if (threadIdx.x == 0 && c) atomicAdd(nact, (unsigned long long)c);
+    int i = (int)(p % nx), j = (int)((p / nx) % ny), k = (int)(p / ((size_t)nx * ny));
+    int na = 0;
+    na += (i > 0 && cnt[p - 1] == 1);
+    na += (i < nx - 1 && cnt[p + 1] == 1);
+    na += (j > 0 && cnt[p - nx] == 1);
+    na += (j < ny - 1 && cnt[p + nx] == 1);
+    na += (k > 0 && cnt[p - (size_t)nx * ny] == 1);
+    na += (k < nz - 1 && cnt[p + (size_t)nx * ny] == 1);
+    code[p] = (uint8_t)(12 - na);
 }
 
 // Coarse diagonal (Sec. 3 ghost value; Sec. 4 first order).  For an active
@@ -90,18 +116,18 @@ __global__ void k_code0(const int32_t *__restrict__ cnt, int nx, int ny, int nz,
 // theta = m_i/(m_i - m_j) is where the linearly interpolated mask crosses 0.
 // In counts: 1/theta = (2c_i - 2c_j)/(2c_i - 8^l), one correctly rounded
 // division of exact integers.  First order pins every cell with m < 1 to 0
-// at its centre: theta = 1.
-__global__ void k_diag(const int32_t *__restrict__ cnt, int nx, int ny, int nz, int level, int order,
+// at its centre: theta = 1.  The active cells are counted with one atomic a
+// block, of at most 1024.
+__global__ __launch_bounds__(256) void k_diag(const int32_t *__restrict__ cnt, int nx, int ny, int nz, int level, int order,
                        double *__restrict__ d, unsigned long long *__restrict__ nact) {
     size_t n = (size_t)nx * ny * nz;
-    size_t p = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    int a = 0;
-    if (p < n) {
+    unsigned a = 0;
+    for (size_t p = blockIdx.x * (size_t)blockDim.x + threadIdx.x; p < n; p += (size_t)gridDim.x * blockDim.x) {
         int i = (int)(p % nx), j = (int)((p / nx) % ny), k = (int)(p / ((size_t)nx * ny));
         const int32_t ci = cnt[p];
         double dv = 0.0;
         if (is_active(ci, level, order)) {
-            a = 1;
+            a++;
             const int64_t N = (int64_t)1 << (3 * level);
             const size_t pl = (size_t)nx * ny;
             int32_t cj[6];
@@ -124,8 +150,8 @@ __global__ void k_diag(const int32_t *__restrict__ cnt, int nx, int ny, int nz, 
         }
         d[p] = dv;
     }
-    int c = __syncthreads_count(a);
-    if (threadIdx.x == 0 && c) atomicAdd(nact, (unsigned long long)c);
+    a = block_total(a);
+    if (threadIdx.x == 0 && a) atomicAdd(nact, (unsigned long long)a);
 }
 
 // One block per tile: flag = 1 if any cell of the tile is active.
@@ -190,15 +216,11 @@ inline unsigned grid_for(size_t n, unsigned bs = 256) {
 
 }  // namespace
 
-void launch_validate(const int8_t *mask, int nx, int ny, int nz, unsigned long long *bad, hipStream_t s) {
-    size_t n = (size_t)nx * ny * nz;
-    unsigned g = grid_for(n);
-    if (g > 4096) g = 4096;
-    k_validate<<<g, 256, 0, s>>>(mask, nx, ny, nz, bad);
-}
-
-void launch_count0(const int8_t *mask, int32_t *cnt, size_t n, hipStream_t s) {
-    k_count0<<<grid_for(n), 256, 0, s>>>(mask, cnt, n);
+void launch_validate(const int8_t *mask, int nx, int ny, int nz, int32_t *cnt, unsigned long long *bad,
+                     hipStream_t s) {
+    const size_t n = (size_t)nx * ny * nz;
+    const unsigned g = std::min(grid_for(n, 2048), 1024u);
+    k_validate<<<g, 256, 0, s>>>(mask, nx, ny, nz, cnt, bad);
 }
 
 void launch_count_up(const Level &fine, const Level &coarse, hipStream_t s) {
@@ -206,12 +228,12 @@ void launch_count_up(const Level &fine, const Level &coarse, hipStream_t s) {
                                                    coarse.nz);
 }
 
-void launch_code0(const Level &L, unsigned long long *nact, hipStream_t s) {
-    k_code0<<<(unsigned)((L.n + 255) / 256), 256, 0, s>>>(L.cnt, L.nx, L.ny, L.nz, L.code, nact);
+void launch_code0(const Level &L, hipStream_t s) {
+    k_code0<<<(unsigned)((L.n + 255) / 256), 256, 0, s>>>(L.cnt, L.nx, L.ny, L.nz, L.code);
 }
 
 void launch_diag(const Level &L, int level, int order, double *d, unsigned long long *nact, hipStream_t s) {
-    k_diag<<<(unsigned)((L.n + 255) / 256), 256, 0, s>>>(L.cnt, L.nx, L.ny, L.nz, level, order, d, nact);
+    k_diag<<<std::min(grid_for(L.n), 1024u), 256, 0, s>>>(L.cnt, L.nx, L.ny, L.nz, level, order, d, nact);
 }
 
 void launch_tile_flags(const Level &L, int level, int order, uint8_t *flags, hipStream_t s) {
