@@ -82,6 +82,16 @@ struct ConvOut {
     int cup = 0;
 };
 
+// Place of weight (co, ci) within a tap in fragment order: the 16 x 32 weights
+// of one B fragment as its lanes hold them, 8 channels a lane.  A fragment is
+// then 1024 consecutive bytes; in [co][ci] order it is 16 pieces of 64 bytes,
+// and fetching those held the layers of 32 and more channels back: 192 -> 64
+// channels on 8 x 16^3 voxels 48 -> 30 us, 96 -> 32 on 8 x 32^3 58 -> 47, 128 ->
+// 128 on 8 x 8^3 20 -> 14.
+__device__ __forceinline__ size_t frag_place(int co, int ci, int cin) {
+    return ((size_t)((co >> 4) * (cin >> 5) + (ci >> 5)) * 64 + (ci >> 3 & 3) * 16 + (co & 15)) * 8 + (ci & 7);
+}
+
 __device__ __forceinline__ bf16x8 gated(bf16x8 v, const bf16x8 &g) {
 #pragma unroll
     for (int j = 0; j < 8; j++)
@@ -94,7 +104,7 @@ __global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina,
                                                    const bf16 *__restrict__ inb, int cb, const bf16 *__restrict__ wt,
                                                    const float *__restrict__ bias, bf16 *__restrict__ out, int cout,
                                                    int relu, int D, int H, int W, int ntx, int nty, int ntz,
-                                                   int nblk, ConvOut eo) {
+                                                   int nblk, ConvOut eo, int frag) {
     constexpr int CKP = CK + 8;
     constexpr int MT = 4;
     static_assert(MT == TY && NTH / 64 == TZ && TX == 16, "a wave owns the 16 x 4 voxels of one tile plane");
@@ -154,7 +164,9 @@ __global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina,
         const bool full = CK == 32 && (!HALF || cin - c0 >= 32);
         unsigned wl[NTC];  // byte offsets within a tap's weights (K entries c0 + 8 grp .. + 7)
 #pragma unroll
-        for (int nt = 0; nt < NTC; nt++) wl[nt] = (unsigned)(((co_base + nt * 16 + row) * cin + c0 + grp * 8) * 2);
+        for (int nt = 0; nt < NTC; nt++)
+            wl[nt] = frag ? (unsigned)((((co_base >> 4) + nt) * (cin >> 5) + (c0 >> 5)) * 1024 + lane * 16)
+                          : (unsigned)(((co_base + nt * 16 + row) * cin + c0 + grp * 8) * 2);
         bf16x8 bfr[2][3][NTC];
         const auto fetch = [&](int r) {
 #pragma unroll
@@ -551,6 +563,19 @@ __global__ void k_flip(const bf16 *__restrict__ w, bf16 *__restrict__ wt, int co
         const int co = (int)((e / cin) % cout);
         const int tap = (int)(e / ((long long)cin * cout));
         wt[((size_t)(26 - tap) * cin + ci) * cout + co] = w[e];
+    }
+}
+
+// The weights as the network's convolutions read them, from w[tap][co][ci]:
+// fwd (cin a multiple of 32) in fragment order, flip as k_flip's, in fragment
+// order if cout is a multiple of 32.
+__global__ void k_layout(const bf16 *__restrict__ w, bf16 *__restrict__ fwd, bf16 *__restrict__ flip, int cout,
+                         int cin) {
+    const int per = cout * cin, n = 27 * per;
+    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
+        const int ci = e % cin, co = e / cin % cout, tap = e / per;
+        if (cin % 32 == 0) fwd[(size_t)tap * per + frag_place(co, ci, cin)] = w[e];
+        flip[(size_t)(26 - tap) * per + (cout % 32 == 0 ? frag_place(ci, co, cout) : (size_t)ci * cout + co)] = w[e];
     }
 }
 
@@ -1123,37 +1148,39 @@ static bool dims_ok(int n, int d, int h, int w) { return n > 0 && d > 0 && h > 0
 
 template <int CK, int NTC>
 void launch_tile(const bf16 *ina, int ca, int upa, const bf16 *inb, int cb, const bf16 *w, const float *bias, bf16 *out,
-                 int cout, int relu, const ConvOut &eo, int n, int D, int H, int W, hipStream_t s) {
+                 int cout, int relu, const ConvOut &eo, int n, int D, int H, int W, hipStream_t s, int frag) {
     const int ntx = (W + TX - 1) / TX, nty = (H + TY - 1) / TY, ntz = (D + TZ - 1) / TZ;
     const int nblk = n * ntx * nty * ntz;
     dim3 grid((unsigned)nblk, (unsigned)(cout / (16 * NTC)));
     if constexpr (CK == 32) {
         if ((ca + cb) % 32 == 16) {
             k_conv_tile<CK, NTC, true><<<grid, NTH, 0, s>>>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, D, H, W,
-                                                            ntx, nty, ntz, nblk, eo);
+                                                            ntx, nty, ntz, nblk, eo, 0);
             return;
         }
     }
     k_conv_tile<CK, NTC><<<grid, NTH, 0, s>>>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, D, H, W, ntx, nty, ntz,
-                                              nblk, eo);
+                                              nblk, eo, frag);
 }
 
 template <int CK>
 void launch_tile_ck(const bf16 *ina, int ca, int upa, const bf16 *inb, int cb, const bf16 *w, const float *bias,
-                    bf16 *out, int cout, int relu, const ConvOut &eo, int n, int D, int H, int W, hipStream_t s) {
+                    bf16 *out, int cout, int relu, const ConvOut &eo, int n, int D, int H, int W, hipStream_t s,
+                    int frag) {
     // widest output tiling that still gives about 1024 blocks
     const long long nblk = (long long)n * ((W + TX - 1) / TX) * ((H + TY - 1) / TY) * ((D + TZ - 1) / TZ);
     const int tiles = cout / 16;
     int ntc = 4;
     while (ntc > 1 && (tiles % ntc || nblk * (tiles / ntc) < 1024)) ntc--;
-    if (ntc == 4) launch_tile<CK, 4>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, eo, n, D, H, W, s);
-    else if (ntc == 3) launch_tile<CK, 3>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, eo, n, D, H, W, s);
-    else if (ntc == 2) launch_tile<CK, 2>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, eo, n, D, H, W, s);
-    else launch_tile<CK, 1>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, eo, n, D, H, W, s);
+    if (ntc == 4) launch_tile<CK, 4>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, eo, n, D, H, W, s, frag);
+    else if (ntc == 3) launch_tile<CK, 3>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, eo, n, D, H, W, s, frag);
+    else if (ntc == 2) launch_tile<CK, 2>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, eo, n, D, H, W, s, frag);
+    else launch_tile<CK, 1>(ina, ca, upa, inb, cb, w, bias, out, cout, relu, eo, n, D, H, W, s, frag);
 }
 
 static bool conv_run(const void *in_a, int ca, int up_a, const void *in_b, int cb, const void *w, const float *bias,
-                     void *out, int cout, int relu, const ConvOut &eo, int n, int d, int h, int wd, hipStream_t s) {
+                     void *out, int cout, int relu, const ConvOut &eo, int n, int d, int h, int wd, hipStream_t s,
+                     bool frag) {
     if (!in_a || !w || !out || ca <= 0 || cb < 0 || (cb > 0 && !in_b) || ca % 8 || cb % 8 || cout <= 0 ||
         cout % 16 || !dims_ok(n, d, h, wd) || (up_a && (d % 2 || h % 2 || wd % 2))) {
         set_error("conv3d: invalid arguments (input channels multiples of 8, output channels of 16)");
@@ -1161,21 +1188,25 @@ static bool conv_run(const void *in_a, int ca, int up_a, const void *in_b, int c
     }
     const bf16 *A = (const bf16 *)in_a, *B = (const bf16 *)in_b, *W = (const bf16 *)w;
     bf16 *O = (bf16 *)out;
-    if (ca + cb <= 16) launch_tile_ck<16>(A, ca, up_a, B, cb, W, bias, O, cout, relu, eo, n, d, h, wd, s);
-    else launch_tile_ck<32>(A, ca, up_a, B, cb, W, bias, O, cout, relu, eo, n, d, h, wd, s);
+    if (frag && (ca + cb) % 32) {
+        set_error("conv3d: weights in fragment order need input channels in multiples of 32");
+        return false;
+    }
+    if (ca + cb <= 16) launch_tile_ck<16>(A, ca, up_a, B, cb, W, bias, O, cout, relu, eo, n, d, h, wd, s, 0);
+    else launch_tile_ck<32>(A, ca, up_a, B, cb, W, bias, O, cout, relu, eo, n, d, h, wd, s, frag ? 1 : 0);
     return hip_ok(hipGetLastError(), "conv3d launch");
 }
 
 bool conv_fwd(const void *in_a, int ca, int up_a, const void *in_b, int cb, const void *w, const float *bias,
-              void *out, int cout, int relu, int n, int d, int h, int wd, hipStream_t s) {
-    return conv_run(in_a, ca, up_a, in_b, cb, w, bias, out, cout, relu, ConvOut{}, n, d, h, wd, s);
+              void *out, int cout, int relu, int n, int d, int h, int wd, hipStream_t s, bool frag) {
+    return conv_run(in_a, ca, up_a, in_b, cb, w, bias, out, cout, relu, ConvOut{}, n, d, h, wd, s, frag);
 }
 
 bool conv_grad(const void *dout, int cout, const void *wf, const void *gate, void *dx, int cin, int n, int d, int h,
                int wd, hipStream_t s) {
     ConvOut eo;
     eo.gate = (const bf16 *)gate;
-    return conv_run(dout, cout, 0, nullptr, 0, wf, nullptr, dx, cin, 0, eo, n, d, h, wd, s);
+    return conv_run(dout, cout, 0, nullptr, 0, wf, nullptr, dx, cin, 0, eo, n, d, h, wd, s, cout % 32 == 0);
 }
 
 bool conv_grad_split(const void *dout, int cout, const void *wf, int ca, int cb, const void *gate, void *dup,
@@ -1188,7 +1219,7 @@ bool conv_grad_split(const void *dout, int cout, const void *wf, int ca, int cb,
     eo.gate = (const bf16 *)gate;
     eo.up = (bf16 *)dup;
     eo.cup = ca;
-    return conv_run(dout, cout, 0, nullptr, 0, wf, nullptr, dskip, ca + cb, 0, eo, n, d, h, wd, s);
+    return conv_run(dout, cout, 0, nullptr, 0, wf, nullptr, dskip, ca + cb, 0, eo, n, d, h, wd, s, cout % 32 == 0);
 }
 
 bool conv_bwd_weight(const void *dout, int cout, const void *in_a, int ca, int up_a, const void *in_b, int cb,
@@ -1212,6 +1243,11 @@ bool weight_flip(const void *w, int cout, int cin, void *wt, hipStream_t s) {
     const long long n = 27LL * cout * cin;
     k_flip<<<blocks_for(n), 256, 0, s>>>((const bf16 *)w, (bf16 *)wt, cout, cin);
     return hip_ok(hipGetLastError(), "weight flip launch");
+}
+
+bool weight_layout(const void *w, int cout, int cin, void *fwd, void *flip, hipStream_t s) {
+    k_layout<<<blocks_for(27LL * cout * cin), 256, 0, s>>>((const bf16 *)w, (bf16 *)fwd, (bf16 *)flip, cout, cin);
+    return hip_ok(hipGetLastError(), "weight layout launch");
 }
 
 bool relu_bwd(void *dy, const void *y, long long count, hipStream_t s) {

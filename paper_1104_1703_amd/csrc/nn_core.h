@@ -8,9 +8,14 @@
 namespace mg {
 namespace nn {
 
-// out = [ReLU](conv3x3x3(concat(up2?(in_a), in_b)) + bias); weights [27][cout][cin].
+// out = [ReLU](conv3x3x3(concat(up2?(in_a), in_b)) + bias); weights [27][cout][cin]
+// (frag: in fragment order, see weight_layout).
 bool conv_fwd(const void *in_a, int ca, int up_a, const void *in_b, int cb, const void *w, const float *bias,
-              void *out, int cout, int relu, int n, int d, int h, int wd, hipStream_t s);
+              void *out, int cout, int relu, int n, int d, int h, int wd, hipStream_t s, bool frag = false);
+// The weights as the network's convolutions read them: fwd in fragment order
+// (written if cin is a multiple of 32), flip as weight_flip's wt, in fragment
+// order if cout is a multiple of 32 (as conv_grad and conv_grad_split take it).
+bool weight_layout(const void *w, int cout, int cin, void *fwd, void *flip, hipStream_t s);
 // Input gradient of a layer, dout convolved with its flipped weights wf; gate
 // (may be null): the activation whose ReLU lies below, dx zeroed where it is
 // not positive.

@@ -68,7 +68,9 @@ struct mg_unet {
     long long np = 0;
     long long woff[NLAYER], boff[NLAYER], head_w = 0, head_b = 0;
     float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
-    bf16 *pb = nullptr, *pf = nullptr;  // BF16 weights and their flipped copies (same offsets)
+    // BF16 weights, and (same offsets) the copies the convolutions read: forward
+    // in fragment order, flipped for the input gradients
+    bf16 *pb = nullptr, *pw = nullptr, *pf = nullptr;
     int step = 0;
     double *st = nullptr;  // per-sample input statistics
     int st_cap = 0;
@@ -177,7 +179,8 @@ bool refresh_weights(mg_unet *U) {
     if (!hip_ok(hipGetLastError(), "weight conversion launch")) return false;
     for (int l = 0; l < NLAYER; l++) {
         const int cin = kLayers[l].ca + kLayers[l].cb;
-        if (!mg::nn::weight_flip(U->pb + U->woff[l], kLayers[l].cout, cin, U->pf + U->woff[l], U->stream))
+        if (!mg::nn::weight_layout(U->pb + U->woff[l], kLayers[l].cout, cin, U->pw + U->woff[l], U->pf + U->woff[l],
+                                   U->stream))
             return false;
     }
     return true;
@@ -188,8 +191,9 @@ bool forward(mg_unet *U) {
     const int n = U->wn;
     auto conv = [&](int l, const void *a, int ca, int up, const void *b, int cb) {
         const int lv = kLayers[l].level - 1;
-        return mg::nn::conv_fwd(a, ca, up, b, cb, U->pb + U->woff[l], U->p + U->boff[l], U->act[l], kLayers[l].cout,
-                                1, n, U->wd >> lv, U->wh >> lv, U->ww >> lv, U->stream);
+        const bool frag = (ca + cb) % 32 == 0;
+        return mg::nn::conv_fwd(a, ca, up, b, cb, (frag ? U->pw : U->pb) + U->woff[l], U->p + U->boff[l], U->act[l],
+                                kLayers[l].cout, 1, n, U->wd >> lv, U->wh >> lv, U->ww >> lv, U->stream, frag);
     };
     auto pool = [&](const void *in, void *out, int c, int level) {
         const int lv = level - 1;
@@ -377,12 +381,13 @@ mg_status mg_unet_create(uint64_t seed, const mg_allocator *alloc, void *stream,
     U->m = (float *)raw_alloc(U, fb);
     U->v = (float *)raw_alloc(U, fb);
     U->pb = (bf16 *)raw_alloc(U, hb);
+    U->pw = (bf16 *)raw_alloc(U, hb);
     U->pf = (bf16 *)raw_alloc(U, hb);
     U->loss_dev = (double *)raw_alloc(U, sizeof(double));
-    for (void *p : {(void *)U->p, (void *)U->g, (void *)U->m, (void *)U->v, (void *)U->pb, (void *)U->pf,
+    for (void *p : {(void *)U->p, (void *)U->g, (void *)U->m, (void *)U->v, (void *)U->pb, (void *)U->pw, (void *)U->pf,
                     (void *)U->loss_dev})
         if (p) U->fixed.push_back(p);
-    if (U->fixed.size() != 7 || hipHostMalloc((void **)&U->loss_host, sizeof(double)) != hipSuccess) {
+    if (U->fixed.size() != 8 || hipHostMalloc((void **)&U->loss_host, sizeof(double)) != hipSuccess) {
         mg_unet_destroy(U);
         set_error("mg_unet_create: allocation failed");
         return MG_ERR_ALLOC;
