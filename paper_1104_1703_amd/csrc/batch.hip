@@ -320,8 +320,8 @@ __global__ __launch_bounds__(tr::NT) void kb_fold(const BRef *__restrict__ refs,
     if (!take(refs, map, count, state, order, r, w)) return;
     const BLev &L = lev[r.lev];
     const int p = r.lev / MAXL, idx = r.w & IDX_MASK;
-    tr::fold_cell(tr::tile_cell(L.tiles[idx / TZ], idx % TZ, L.ntx, L.nty, L.nx, L.ny, L.nz), L.nx, L.ny, L.ih2,
-                  L.code, rho[p], dir[p], phi[p], L.f, L.x[0]);
+    tr::fold_cells(tr::cells(L.tiles[idx / tr::NQ], idx % tr::NQ, L.ntx, L.nty, L.nx, L.ny, L.nz), L.nx, L.ny, L.ih2,
+                   L.code, rho[p], dir[p], phi[p], L.f, L.x[0]);
 }
 
 __global__ __launch_bounds__(tr::NT) void kb_store(const BRef *__restrict__ refs, const int *__restrict__ map, int count,
@@ -332,8 +332,8 @@ __global__ __launch_bounds__(tr::NT) void kb_store(const BRef *__restrict__ refs
     if (!take(refs, map, count, state, order, r, w)) return;
     const BLev &L = lev[r.lev];
     const int p = r.lev / MAXL, idx = r.w & IDX_MASK, sel = r.w >> WBITS;
-    tr::store_cell(tr::tile_cell(L.tiles[idx / TZ], idx % TZ, L.ntx, L.nty, L.nx, L.ny, L.nz), L.nx, L.ny, L.code,
-                   L.x[sel & 1], phi[p]);
+    tr::store_cells(tr::cells(L.tiles[idx / tr::NQ], idx % tr::NQ, L.ntx, L.nty, L.nx, L.ny, L.nz), L.code,
+                    L.x[sel & 1], phi[p]);
 }
 
 __host__ __device__ inline unsigned grid8(int items) { return (unsigned)(((items + 7) / 8) * 8); }
@@ -490,12 +490,12 @@ __device__ __attribute__((noinline)) void p_cell(int kind, const BLev &L, int id
             break;
         }
         case K_FOLD:
-            tr::fold_cell(tr::tile_cell(L.tiles[idx / TZ], idx % TZ, L.ntx, L.nty, L.nx, L.ny, L.nz), L.nx, L.ny,
-                          L.ih2, L.code, rho, dir, phi, L.f, L.x[0]);
+            tr::fold_cells(tr::cells(L.tiles[idx / tr::NQ], idx % tr::NQ, L.ntx, L.nty, L.nx, L.ny, L.nz), L.nx, L.ny,
+                           L.ih2, L.code, rho, dir, phi, L.f, L.x[0]);
             break;
         case K_STORE:
-            tr::store_cell(tr::tile_cell(L.tiles[idx / TZ], idx % TZ, L.ntx, L.nty, L.nx, L.ny, L.nz), L.nx, L.ny,
-                           L.code, L.x[sel & 1], phi);
+            tr::store_cells(tr::cells(L.tiles[idx / tr::NQ], idx % tr::NQ, L.ntx, L.nty, L.nx, L.ny, L.nz), L.code,
+                            L.x[sel & 1], phi);
             break;
         default: break;
     }
@@ -824,7 +824,7 @@ struct Planner {
     }
     void tiles0(int kind) {
         open(kind);
-        for (int p = 0; p < B->n; p++) add(p, 0, od(p, 0).ntiles * TZ, 0);
+        for (int p = 0; p < B->n; p++) add(p, 0, od(p, 0).ntiles * tr::NQ, 0);
         close();
     }
 };
@@ -990,7 +990,7 @@ int validate_tables(const mg_batch *B, std::string *msg) {
                         break;
                     case K_FOLD:
                     case K_STORE:
-                        if (l != 0 || idx >= od.ntiles * TZ || !od.tiles || !bufs) fail(where + ": tile-plane item");
+                        if (l != 0 || idx >= od.ntiles * tr::NQ || !od.tiles || !bufs) fail(where + ": tile-column item");
                         break;
                     default:
                         fail(where + ": unknown kind");

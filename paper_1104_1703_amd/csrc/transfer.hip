@@ -24,27 +24,6 @@ __device__ __forceinline__ bool block_tile(const int *tiles, int ntiles, int per
     return true;
 }
 
-// Cells of a thread in the copying kernels below: QZ planes of one column of a
-// tile.  Every cell waits for its code before its values, so a thread with one
-// cell (and a block with one plane) waited two memory latencies for 16 bytes;
-// the loads of QZ planes are in flight together.  Inactive cells load the
-// array's first value instead of their own.  160 x 144 x 176, 1.4 M active
-// cells: fold 24.0 -> 20.8 us, copy in 13.0 -> 10.5, store 10.8 -> 7.7.
-struct Cells {
-    size_t p[QZ];
-    bool ok[QZ];
-};
-__device__ __forceinline__ Cells cells(int tile, int part, int ntx, int nty, int nx, int ny, int nz) {
-    Cells c;
-#pragma unroll
-    for (int q = 0; q < QZ; q++) {
-        const TileCoord t = tile_cell(tile, part * QZ + q, ntx, nty, nx, ny, nz);
-        c.ok[q] = t.ok;
-        c.p[q] = t.ok ? (size_t)t.k * nx * ny + (size_t)t.j * nx + t.i : 0;
-    }
-    return c;
-}
-
 __global__ __launch_bounds__(NT) void k_fold(const int *__restrict__ tiles, int ntiles, int ntx, int nty, int nx,
                                              int ny, int nz, double ih2, const uint8_t *__restrict__ code,
                                              const double *__restrict__ rho, const double *__restrict__ B,
@@ -52,24 +31,7 @@ __global__ __launch_bounds__(NT) void k_fold(const int *__restrict__ tiles, int 
                                              double *__restrict__ x) {
     int tile, part, w;
     if (!block_tile(tiles, ntiles, NQ, tile, part, w)) return;
-    const Cells c = cells(tile, part, ntx, nty, nx, ny, nz);
-    uint8_t cd[QZ];
-    double r[QZ], g[QZ];
-#pragma unroll
-    for (int q = 0; q < QZ; q++) cd[q] = code[c.p[q]];
-#pragma unroll
-    for (int q = 0; q < QZ; q++) {
-        const size_t p = cd[q] != CODE_OFF ? c.p[q] : 0;
-        r[q] = rho[p];
-        g[q] = phi ? phi[p] : 0.0;
-    }
-#pragma unroll
-    for (int q = 0; q < QZ; q++) {
-        if (!c.ok[q]) continue;
-        const size_t p = c.p[q];
-        f[p] = cd[q] == CODE_OFF ? 0.0 : fold_value(p, cd[q], r[q], nx, ny, ih2, code, B);
-        if (x) x[p] = cd[q] == CODE_OFF ? 0.0 : g[q];
-    }
+    fold_cells(cells(tile, part, ntx, nty, nx, ny, nz), nx, ny, ih2, code, rho, B, phi, f, x);
 }
 
 __global__ __launch_bounds__(NT) void k_store(const int *__restrict__ tiles, int ntiles, int ntx, int nty, int nx,
@@ -77,16 +39,7 @@ __global__ __launch_bounds__(NT) void k_store(const int *__restrict__ tiles, int
                                               const double *__restrict__ x, double *__restrict__ phi) {
     int tile, part, w;
     if (!block_tile(tiles, ntiles, NQ, tile, part, w)) return;
-    const Cells c = cells(tile, part, ntx, nty, nx, ny, nz);
-    uint8_t cd[QZ];
-    double v[QZ];
-#pragma unroll
-    for (int q = 0; q < QZ; q++) cd[q] = code[c.p[q]];
-#pragma unroll
-    for (int q = 0; q < QZ; q++) v[q] = x[cd[q] != CODE_OFF ? c.p[q] : 0];
-#pragma unroll
-    for (int q = 0; q < QZ; q++)
-        if (c.ok[q] && cd[q] != CODE_OFF) phi[c.p[q]] = v[q];
+    store_cells(cells(tile, part, ntx, nty, nx, ny, nz), code, x, phi);
 }
 
 template <bool FINE>

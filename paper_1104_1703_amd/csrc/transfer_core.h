@@ -132,51 +132,91 @@ __device__ __forceinline__ void column_residual(const T *__restrict__ x, const T
     }
 }
 
+// Cells of a thread in the fold, copy and store kernels: QZ planes of one column of a
+// tile.  Every cell waits for its code before its values, so a thread with one
+// cell (and a block with one plane) waited two memory latencies for 16 bytes;
+// the loads of QZ planes are in flight together.  Inactive cells load the
+// array's first value instead of their own.  160 x 144 x 176, 1.4 M active
+// cells: fold 24.0 -> 20.8 us (16.5 as fold_value is now), copy in 13.0 -> 10.5, store 10.8 -> 7.7.
+struct Cells {
+    size_t p[QZ];
+    bool ok[QZ];
+};
+__device__ __forceinline__ Cells cells(int tile, int part, int ntx, int nty, int nx, int ny, int nz) {
+    Cells c;
+#pragma unroll
+    for (int q = 0; q < QZ; q++) {
+        const TileCoord t = tile_cell(tile, part * QZ + q, ntx, nty, nx, ny, nz);
+        c.ok[q] = t.ok;
+        c.p[q] = t.ok ? (size_t)t.k * nx * ny + (size_t)t.j * nx + t.i : 0;
+    }
+    return c;
+}
+
 // ---- fold the Dirichlet values into the right-hand side, load the guess ----
 // With the boundary on the face between active i and inactive j (theta = 1/2),
 // the ghost is 2 g_ij - x_i with g_ij = (B_i + B_j)/2 (Sec. 3, Fig. "ghost"),
 // so the known part B_i + B_j moves to the right-hand side.  Active cells are
 // never on the box edge (validated), so their six neighbours exist.
-// f of active cell p with code c and density fv.
+// f of active cell p with code c and density fv.  The six neighbours' codes and
+// values are loaded together: one after the other, each value behind its code,
+// they were most of a fold with Dirichlet data (96 patches of up to 96 cells an
+// edge 277 -> 188 us; 160 x 144 x 176 20.8 -> 16.5).
 __device__ __forceinline__ double fold_value(size_t p, uint8_t c, double fv, int nx, int ny, double ih2,
                                              const uint8_t *__restrict__ code, const double *__restrict__ B) {
     if (B && c > 6) {  // some face neighbour is inactive
         const size_t pl = (size_t)nx * ny;
+        const size_t q[6] = {p - 1, p + 1, p - nx, p + nx, p - pl, p + pl};
+        uint8_t cq[6];
+        double bq[6];
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            cq[k] = code[q[k]];
+            bq[k] = B[q[k]];
+        }
         const double bi = B[p];
         double g = 0.0;
-        if (code[p - 1] == CODE_OFF) g += bi + B[p - 1];
-        if (code[p + 1] == CODE_OFF) g += bi + B[p + 1];
-        if (code[p - nx] == CODE_OFF) g += bi + B[p - nx];
-        if (code[p + nx] == CODE_OFF) g += bi + B[p + nx];
-        if (code[p - pl] == CODE_OFF) g += bi + B[p - pl];
-        if (code[p + pl] == CODE_OFF) g += bi + B[p + pl];
+#pragma unroll
+        for (int k = 0; k < 6; k++) g = cq[k] == CODE_OFF ? g + (bi + bq[k]) : g;
         fv -= ih2 * g;
     }
     return fv;
 }
 
-__device__ __forceinline__ void fold_cell(const TileCoord &t, int nx, int ny, double ih2,
-                                          const uint8_t *__restrict__ code, const double *__restrict__ rho,
-                                          const double *__restrict__ B, const double *__restrict__ phi,
-                                          double *__restrict__ f, double *__restrict__ x) {
-    if (!t.ok) return;
-    const size_t pl = (size_t)nx * ny;
-    const size_t p = (size_t)t.k * pl + (size_t)t.j * nx + t.i;
-    const uint8_t c = code[p];
-    if (c == CODE_OFF) {
-        f[p] = 0.0;
-        if (x) x[p] = 0.0;
-        return;
+__device__ __forceinline__ void fold_cells(const Cells &c, int nx, int ny, double ih2,
+                                           const uint8_t *__restrict__ code, const double *__restrict__ rho,
+                                           const double *__restrict__ B, const double *__restrict__ phi,
+                                           double *__restrict__ f, double *__restrict__ x) {
+    uint8_t cd[QZ];
+    double r[QZ], g[QZ];
+#pragma unroll
+    for (int q = 0; q < QZ; q++) cd[q] = code[c.p[q]];
+#pragma unroll
+    for (int q = 0; q < QZ; q++) {
+        const size_t p = cd[q] != CODE_OFF ? c.p[q] : 0;
+        r[q] = rho[p];
+        g[q] = phi ? phi[p] : 0.0;
     }
-    f[p] = fold_value(p, c, rho[p], nx, ny, ih2, code, B);
-    if (x) x[p] = phi ? phi[p] : 0.0;
+#pragma unroll
+    for (int q = 0; q < QZ; q++) {
+        if (!c.ok[q]) continue;
+        const size_t p = c.p[q];
+        f[p] = cd[q] == CODE_OFF ? 0.0 : fold_value(p, cd[q], r[q], nx, ny, ih2, code, B);
+        if (x) x[p] = cd[q] == CODE_OFF ? 0.0 : g[q];
+    }
 }
 
-__device__ __forceinline__ void store_cell(const TileCoord &t, int nx, int ny, const uint8_t *__restrict__ code,
-                                           const double *__restrict__ x, double *__restrict__ phi) {
-    if (!t.ok) return;
-    const size_t p = (size_t)t.k * nx * ny + (size_t)t.j * nx + t.i;
-    if (code[p] != CODE_OFF) phi[p] = x[p];
+__device__ __forceinline__ void store_cells(const Cells &c, const uint8_t *__restrict__ code,
+                                            const double *__restrict__ x, double *__restrict__ phi) {
+    uint8_t cd[QZ];
+    double v[QZ];
+#pragma unroll
+    for (int q = 0; q < QZ; q++) cd[q] = code[c.p[q]];
+#pragma unroll
+    for (int q = 0; q < QZ; q++) v[q] = x[cd[q] != CODE_OFF ? c.p[q] : 0];
+#pragma unroll
+    for (int q = 0; q < QZ; q++)
+        if (c.ok[q] && cd[q] != CODE_OFF) phi[c.p[q]] = v[q];
 }
 
 // ---- residual norm of a column: sum over its active cells of (L x - f)^2 ----
