@@ -57,8 +57,9 @@ __device__ __forceinline__ double residual_item(ResLds<T> &L, const T *__restric
     static_assert(SEGZ + 4 <= rb::MAXPL, "work item longer than the mask array");
     // The update's outputs (12 bytes a cell beside 21 read) are next read a
     // pass later, when other arrays have long gone through L2; stored
-    // non-temporally at every size: 512^3 porous solve 167.8 -> 163.6 ms,
-    // 256^3 20.69 -> 20.54, 192^3 12.36 -> 11.93.
+    // non-temporally they leave the halo lines there that neighbouring items
+    // share: 512^3 porous 1050 -> 968 us (reads 4.0 -> 3.35 GB), the solve 167.8
+    // -> 163.6 ms; 256^3 20.69 -> 20.54, 192^3 12.36 -> 11.93.
     constexpr int OUT = MODE == RM_AXPY32 ? STREAM : 0;
     auto &xs = L.xs;
     auto &ms = L.ms;

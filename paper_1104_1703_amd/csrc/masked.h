@@ -34,8 +34,8 @@ __device__ __forceinline__ V bload(__amdgpu_buffer_rsrc_t r, int off) {
     else if constexpr (sizeof(V) == 4) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
     else return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0));
 }
-// AUX: cache policy bits; STREAM marks a store as non-temporal, so that its
-// lines do not push lines out of L2 that neighbouring items still read.
+// AUX: cache policy bits; STREAM marks a store as non-temporal (its lines give
+// way first).
 constexpr int STREAM = 2;
 template <typename V, int AUX = 0>
 __device__ __forceinline__ void bstore(V v, __amdgpu_buffer_rsrc_t r, int off) {

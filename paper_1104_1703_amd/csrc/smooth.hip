@@ -226,16 +226,19 @@ void launch_rbgs_restrict32(const Level &L, const Level &C, int order, const Ord
 }
 
 // Calls launch with a finest pass's item depth and the cache policy of its
-// stores.  The result is stored non-temporally when what a pass
-// touches (x in and out, f and the code, on active cells) is more than the
-// 256 MiB last-level cache holds.  The next pass then finds nothing of it
-// there anyway, while the stored lines would push halo lines out of L2; below
-// that size it reads the result back from that cache.  Solve times, without
-// and with: FP64 192^3 porous (166 MB) 12.57 / 13.69 ms, 256^3 holes (152 MB)
-// 12.56 / 13.26, 256^3 porous (394 MB) 25.7 / 25.1, 384^3 holes (510 MB) 38.7
-// / 38.4, 512^3 holes (1.2 GB) 89.8 / 87.9; mixed precision (with the update's
-// outputs always stored so) 256^3 porous (205 MB) 20.5 / 21.6, 320^3 (400 MB)
-// 44.0 / 43.5, 512^3 (1.6 GB) 163.6 / 162.2.
+// stores.  The result is stored non-temporally when what a pass touches (x in
+// and out, f and the code, on active cells) is more than the 256 MiB last-level
+// cache holds: the next pass then finds nothing of it there anyway.  Below that
+// size it reads the result back from that cache.  At 512^3 porous the FP32
+// passes take 1-4% less time so (plain 475 -> 458 us, residual 666 -> 653,
+// prolongation 605 -> 588), the passes with the larger halos also reading less
+// (residual 839 -> 773 MiB by the uncalibrated counter); the FP64 plain pass
+// 890 -> 866 us, though it reads 4% more.  Solve times, without and with: FP64
+// 192^3 porous (166 MB) 12.57 / 13.69 ms, 256^3 holes (152 MB) 12.56 / 13.26,
+// 256^3 porous (394 MB) 25.7 / 25.1, 384^3 holes (510 MB) 38.7 / 38.4, 512^3
+// holes (1.2 GB) 89.8 / 87.9; mixed precision (with the update's outputs always
+// stored so) 256^3 porous (205 MB) 20.5 / 21.6, 320^3 (400 MB) 44.0 / 43.5,
+// 512^3 (1.6 GB) 163.6 / 162.2.
 template <typename T, typename F>
 void with_fine_pass(const OrderData &od, F &&launch) {
     const bool stream = (size_t)od.nact * (3 * sizeof(T) + 1) > ((size_t)256 << 20);
