@@ -232,7 +232,7 @@ void launch_rbgs_restrict32(const Level &L, const Level &C, int order, const Ord
 // size it reads the result back from that cache.  At 512^3 porous the FP32
 // passes take 1-4% less time so (plain 475 -> 458 us, residual 666 -> 653,
 // prolongation 605 -> 588), the passes with the larger halos also reading less
-// (residual 839 -> 773 MiB by the uncalibrated counter); the FP64 plain pass
+// (residual 1.72 -> 1.58 GB); the FP64 plain pass
 // 890 -> 866 us, though it reads 4% more.  Solve times, without and with: FP64
 // 192^3 porous (166 MB) 12.57 / 13.69 ms, 256^3 holes (152 MB) 12.56 / 13.26,
 // 256^3 porous (394 MB) 25.7 / 25.1, 384^3 holes (510 MB) 38.7 / 38.4, 512^3
