@@ -1422,6 +1422,7 @@ mg_status solve_batch_persistent(mg_batch *B, const double *const *rho, double *
     hipStream_t s = B->stream;
     std::vector<SolveState> S(n);
     BHIP(hipStreamSynchronize(s));  // no copy of an earlier solve still reads the staging
+    BHIP(hipStreamSynchronize(B->side));
     BHIP(hipEventRecord(B->ev0, s));
     for (int p = 0; p < n; p++) {
         const mg_status st = phase_init(B->patches[p], phi[p], tol, &infos[p], S[p]);
@@ -1528,6 +1529,7 @@ mg_status solve_batch_phased(mg_batch *B, const double *const *rho, double *cons
     hipStream_t s = B->stream;
     std::vector<SolveState> S(n);
     BHIP(hipStreamSynchronize(s));  // no copy of an earlier solve still reads the staging
+    BHIP(hipStreamSynchronize(B->side));  // (nor, where one ended with an error, its first-order cycle)
     BHIP(hipEventRecord(B->ev0, s));
     for (int p = 0; p < n; p++) {
         const mg_status st = phase_init(B->patches[p], phi[p], tol, &infos[p], S[p]);
