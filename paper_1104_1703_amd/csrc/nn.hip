@@ -51,9 +51,12 @@ __device__ __forceinline__ f32x4 mfma(const bf16x8 &a, const bf16x8 &b, const f3
 // concatenation resolved while staging).  The tap loop then reads every A
 // fragment from LDS at a uniform tap offset, with no bounds tests.  Wave w
 // computes z-plane w of the tile; its fragment mt is row y = mt, lane row r
-// the voxel x = r.  A voxel's LDS row is CK + 8 channels long (an odd number
-// of 16-byte bank groups), so the 16 x-consecutive rows of a fragment fall in
-// 16 distinct bank groups.  A chunk holding only 16 input channels (CK = 16,
+// the voxel x = r.  With CK = 32 a voxel's LDS row is 40 channels long (an odd
+// number of 16-byte bank groups), so the 16 x-consecutive rows of a fragment
+// fall in 16 distinct bank groups.  Rows of 16 channels are not padded: the
+// eight lanes a 16-byte read serves at a time fall in distinct groups anyhow,
+// and a tile of 21 KB lets seven blocks share a CU instead of five (16 -> 16
+// channels on 8 x 64^3 57 -> 50 us).  A chunk holding only 16 input channels (CK = 16,
 // or with HALF the last chunk when C_in = 32 q + 16) takes two taps per K step
 // of 32 (lane groups 0, 1: tap 2p; 2, 3: tap 2p + 1) instead of padding K
 // with zeros.
@@ -63,9 +66,9 @@ __device__ __forceinline__ f32x4 mfma(const bf16x8 &a, const bf16x8 &b, const f3
 // bytes.  All pieces of a tile are in flight together while it is staged, the
 // weights run a tap row ahead of the products, and every LDS address is a
 // constant beyond a base per lane.  8 x 64^3 voxels, before and after: 16 -> 16
-// channels 95 -> 57 us (134 MB: 2.4 TB/s, bound by its LDS reads and the
-// staging's latency), 16 -> 48 278 -> 138 us (three channel groups share a
-// tile: 268 MB at 1.9 TB/s), 48 -> 16 (32 up-sampled) 212 -> 152 us; 8 x 32^3:
+// channels 95 -> 50 us (134 MB: 2.7 TB/s, bound by its LDS reads and the
+// staging's latency), 16 -> 48 278 -> 137 us (three channel groups share a
+// tile: 268 MB at 2.0 TB/s), 48 -> 16 (32 up-sampled) 212 -> 152 us; 8 x 32^3:
 // 96 -> 32 72 -> 58 us (750 TFLOP/s); 8 x 8^3: 128 -> 128 24 -> 20 us (bound by
 // latency: 64 blocks, a chain of four chunks).
 constexpr int TX = 16, TY = 4, TZ = 4;
@@ -105,7 +108,7 @@ __global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina,
                                                    const float *__restrict__ bias, bf16 *__restrict__ out, int cout,
                                                    int relu, int D, int H, int W, int ntx, int nty, int ntz,
                                                    int nblk, ConvOut eo, int frag) {
-    constexpr int CKP = CK + 8;
+    constexpr int CKP = CK == 16 ? CK : CK + 8;
     constexpr int MT = 4;
     static_assert(MT == TY && NTH / 64 == TZ && TX == 16, "a wave owns the 16 x 4 voxels of one tile plane");
     constexpr int UP = TX * TY * TZ * NTC * 16;  // up-sampled part of a split output, on its way to the sums
