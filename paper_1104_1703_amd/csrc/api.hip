@@ -952,9 +952,12 @@ void solve_begin(mg_hierarchy *H, const double *rho, double *phi, const double *
     HIPCHK(hipEventRecord(H->ev0, s));
     launch_set_halt(H->halt_dev, 0, s);
     launch_fold(L0, od0, rho, B, phi, L0.f, L0.x[0], s);
-    launch_resnorm(L0, 0, od0, nullptr, L0.f, H->part, H->norm_dev, 1, s);
-    if (S.mixed) launch_resnorm32(L0, od0, L0.x[0], L0.f, L0.f32, H->part, H->norm_dev, 0, s);
-    else launch_resnorm(L0, 0, od0, L0.x[0], L0.f, H->part, H->norm_dev, 0, s);
+    if (S.mixed) {
+        launch_resnorm(L0, 0, od0, nullptr, L0.f, H->part, H->norm_dev, 1, s);
+        launch_resnorm32(L0, od0, L0.x[0], L0.f, L0.f32, H->part, H->norm_dev, 0, s);
+    } else {
+        launch_start_norms(L0, od0, L0.x[0], L0.f, H->part, H->norm_dev, s);
+    }
     HIPCHK(hipMemcpyAsync(H->norm_host, H->norm_dev, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
 }
 

@@ -288,6 +288,11 @@ void launch_copy_masked(const Level &L, int level, const OrderData &od, const do
 void launch_resnorm(const Level &L, int level, const OrderData &od, const double *x, const double *f, double *part,
                     double *out, int slot, hipStream_t s, const StopTest *stop = nullptr,
                     double *host_out = nullptr);
+// Norms of L x - f into out[0] and of f into out[1] (finest level), a solve's
+// first two, in two launches where there were four (32^3 solve 671 -> 641 us);
+// part: room for twice the level's work items.
+void launch_start_norms(const Level &L, const OrderData &od, const double *x, const double *f, double *part,
+                        double *out, hipStream_t s);
 // The fixed-order total of n partials into out[slot], with `stop` also the
 // stop test on it (halt flag of L) -- the final step of launch_resnorm;
 // host_out (device address of coherent host memory): the total is also

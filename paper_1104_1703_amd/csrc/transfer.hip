@@ -84,15 +84,15 @@ __global__ __launch_bounds__(NT) void k_item_norm(const double *__restrict__ x, 
                                                   const Seg *__restrict__ segs, double *__restrict__ part,
                                                   const int *__restrict__ halt) {
     if (halt && *halt) return;
-    const double t = block_sum(item_norm(segs[blockIdx.x], x, f, code, nx, ny, nz, ih2));
-    if (threadIdx.x == 0) part[blockIdx.x] = t;
+    const double *xx = blockIdx.y == 0 ? x : nullptr;
+    const double t = block_sum(item_norm(segs[blockIdx.x], xx, f, code, nx, ny, nz, ih2));
+    if (threadIdx.x == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = t;
 }
 
-__global__ __launch_bounds__(1024) void k_finalize(const double *__restrict__ part, int n, double *__restrict__ out,
-                                                   int slot, StopTest *__restrict__ stop, int *__restrict__ halt,
-                                                   double *__restrict__ host_out = nullptr) {
+// The sum of part[0 .. n), for thread 0, in the order of every norm's final sum
+// (blocks of 1024 threads).
+__device__ __forceinline__ double fixed_sum(const double *__restrict__ part, int n) {
     __shared__ double sm[1024];
-    if (halt && *halt) return;
     double v = 0.0;
     for (int q = threadIdx.x; q < n; q += 1024) v += part[q];
     sm[threadIdx.x] = v;
@@ -101,13 +101,28 @@ __global__ __launch_bounds__(1024) void k_finalize(const double *__restrict__ pa
         if ((int)threadIdx.x < o) sm[threadIdx.x] += sm[threadIdx.x + o];
         __syncthreads();
     }
+    return sm[0];
+}
+
+// out[b] = sum of the b-th n partials.
+__global__ __launch_bounds__(1024) void k_finalize_each(const double *__restrict__ part, int n,
+                                                        double *__restrict__ out) {
+    const double t = fixed_sum(part + (size_t)blockIdx.x * n, n);
+    if (threadIdx.x == 0) out[blockIdx.x] = t;
+}
+
+__global__ __launch_bounds__(1024) void k_finalize(const double *__restrict__ part, int n, double *__restrict__ out,
+                                                   int slot, StopTest *__restrict__ stop, int *__restrict__ halt,
+                                                   double *__restrict__ host_out = nullptr) {
+    if (halt && *halt) return;
+    const double sum = fixed_sum(part, n);
     if (threadIdx.x == 0) {
-        out[slot] = sm[0];
+        out[slot] = sum;
         if (host_out)  // coherent host memory: a system-scope store reaches it directly
-            __hip_atomic_store(reinterpret_cast<unsigned long long *>(host_out), __double_as_longlong(sm[0]),
+            __hip_atomic_store(reinterpret_cast<unsigned long long *>(host_out), __double_as_longlong(sum),
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         if (stop) {
-            const double r = sqrt(sm[0]);
+            const double r = sqrt(sum);
             const bool h = !(r > stop->thresh) || !isfinite(r) || (stop->check_switch && r / stop->rprev > stop->eta);
             stop->rprev = r;
             *halt = h ? 1 : 0;
@@ -314,6 +329,21 @@ void launch_resnorm(const Level &L, int level, const OrderData &od, const double
                                                                       L.nz, ih2, nullptr, od.d, x, f, part, nullptr);
     k_finalize<<<1, 1024, 0, s>>>(part, od.ntiles * NQ, out, slot, const_cast<StopTest *>(stop), halt_rw(L),
                                   host_out);
+}
+
+void launch_start_norms(const Level &L, const OrderData &od, const double *x, const double *f, double *part,
+                        double *out, hipStream_t s) {
+    const double ih2 = 1.0 / (L.h * L.h);
+    if (od.nsegs && od.few)
+        k_item_norm<<<dim3(od.nsegs, 2), NT, 0, s>>>(x, f, L.code, L.nx, L.ny, L.nz, ih2, od.segs, part, L.halt);
+    else if (od.nsegs)
+        with_fine_depth(od.depth, [&](auto Z) {
+            for (int q = 0; q < 2; q++)
+                k_residual_march<double, decltype(Z)::value, RM_NORM><<<grid8(od.nsegs), NT, 0, s>>>(
+                    q ? nullptr : x, f, L.code, L.nx, L.ny, L.nz, ih2, od.segs, od.pmask, od.nsegs, nullptr, 0, 0,
+                    nullptr, part + (size_t)q * od.nsegs, nullptr, nullptr, nullptr, L.halt);
+        });
+    k_finalize_each<<<2, 1024, 0, s>>>(part, od.nsegs, out);
 }
 
 void launch_finalize(const Level &L, const double *part, int n, double *out, int slot, const StopTest *stop,
