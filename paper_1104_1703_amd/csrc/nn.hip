@@ -912,52 +912,54 @@ __global__ __launch_bounds__(NTH) void k_up2(const double *__restrict__ c, doubl
     typedef double d2 __attribute__((ext_vector_type(2)));
     const int e = blockIdx.x * NTH + threadIdx.x;  // row (y) and x of a coarse plane
     if (e >= Hc * Wc) return;
-    const int pz = blockIdx.y, py = e / Wc, px = e - py * Wc;
+    const int py = e / Wc, px = e - py * Wc;
     const size_t base = (size_t)blockIdx.z * Dc * Hc * Wc, cpl = (size_t)Hc * Wc;
     const size_t H = 2 * (size_t)Hc, W = 2 * (size_t)Wc;
-    const size_t f0 = (((size_t)blockIdx.z * 2 * Dc + 2 * pz) * H + 2 * py) * W + 2 * px;
-    bool act[2][2][2];
-    bool any = false;
+    for (int pz = blockIdx.y; pz < Dc; pz += gridDim.y) {
+        const size_t f0 = (((size_t)blockIdx.z * 2 * Dc + 2 * pz) * H + 2 * py) * W + 2 * px;
+        bool act[2][2][2];
+        bool any = false;
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-        const size_t o = f0 + ((q >> 1) * H + (q & 1)) * W;
+        for (int q = 0; q < 4; q++) {
+            const size_t o = f0 + ((q >> 1) * H + (q & 1)) * W;
 #pragma unroll
-        for (int dx = 0; dx < 2; dx++) any |= (act[q >> 1][q & 1][dx] = !mask || mask[o + dx] == 1);
-    }
-    const auto mix = [](double near, double far) { return __builtin_fma(0.75, near, 0.25 * far); };
-    const auto put = [&](int dz, int dy, double v0, double v1) {
-        const size_t o = f0 + (dz * H + dy) * W;
-        v0 = act[dz][dy][0] ? v0 : 0.0;
-        v1 = act[dz][dy][1] ? v1 : 0.0;
-        if constexpr (VEC) {
-            *(d2 *)(f + o) = d2{v0, v1};
-        } else {
-            f[o] = v0;
-            f[o + 1] = v1;
+            for (int dx = 0; dx < 2; dx++) any |= (act[q >> 1][q & 1][dx] = !mask || mask[o + dx] == 1);
         }
-    };
-    if (!any) {
+        const auto mix = [](double near, double far) { return __builtin_fma(0.75, near, 0.25 * far); };
+        const auto put = [&](int dz, int dy, double v0, double v1) {
+            const size_t o = f0 + (dz * H + dy) * W;
+            v0 = act[dz][dy][0] ? v0 : 0.0;
+            v1 = act[dz][dy][1] ? v1 : 0.0;
+            if constexpr (VEC) {
+                *(d2 *)(f + o) = d2{v0, v1};
+            } else {
+                f[o] = v0;
+                f[o + 1] = v1;
+            }
+        };
+        if (!any) {
 #pragma unroll
-        for (int q = 0; q < 4; q++) put(q >> 1, q & 1, 0.0, 0.0);
-        return;
-    }
-    double v[3][3][3];
-#pragma unroll
-    for (int k = 0; k < 27; k++) {
-        const int z = min(max(pz + k / 9 - 1, 0), Dc - 1), y = min(max(py + k / 3 % 3 - 1, 0), Hc - 1),
-                  x = min(max(px + k % 3 - 1, 0), Wc - 1);
-        v[k / 9][k / 3 % 3][k % 3] = c[base + z * cpl + (size_t)y * Wc + x];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-        double r[2];
-#pragma unroll
-        for (int dx = 0; dx < 2; dx++) {
-            const int qz = (q >> 1) ? 2 : 0, qy = (q & 1) ? 2 : 0, qx = dx ? 2 : 0;
-            r[dx] = mix(mix(mix(v[1][1][1], v[1][1][qx]), mix(v[1][qy][1], v[1][qy][qx])),
-                        mix(mix(v[qz][1][1], v[qz][1][qx]), mix(v[qz][qy][1], v[qz][qy][qx])));
+            for (int q = 0; q < 4; q++) put(q >> 1, q & 1, 0.0, 0.0);
+            continue;
         }
-        put(q >> 1, q & 1, r[0], r[1]);
+        double v[3][3][3];
+#pragma unroll
+        for (int k = 0; k < 27; k++) {
+            const int z = min(max(pz + k / 9 - 1, 0), Dc - 1), y = min(max(py + k / 3 % 3 - 1, 0), Hc - 1),
+                      x = min(max(px + k % 3 - 1, 0), Wc - 1);
+            v[k / 9][k / 3 % 3][k % 3] = c[base + z * cpl + (size_t)y * Wc + x];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            double r[2];
+#pragma unroll
+            for (int dx = 0; dx < 2; dx++) {
+                const int qz = (q >> 1) ? 2 : 0, qy = (q & 1) ? 2 : 0, qx = dx ? 2 : 0;
+                r[dx] = mix(mix(mix(v[1][1][1], v[1][1][qx]), mix(v[1][qy][1], v[1][qy][qx])),
+                            mix(mix(v[qz][1][1], v[qz][1][qx]), mix(v[qz][qy][1], v[qz][qy][qx])));
+            }
+            put(q >> 1, q & 1, r[0], r[1]);
+        }
     }
 }
 
@@ -1339,7 +1341,7 @@ bool head(const void *x, const float *w, const float *b, const double *st, const
 }
 
 bool up2(const double *c, double *f, int n, int dc, int hc, int wc, const int8_t *mask, hipStream_t s) {
-    const dim3 grid((unsigned)(((long long)hc * wc + NTH - 1) / NTH), (unsigned)dc, (unsigned)n);
+    const dim3 grid((unsigned)(((long long)hc * wc + NTH - 1) / NTH), (unsigned)std::min(dc, 65535), (unsigned)n);
     if (((uintptr_t)f & 15) == 0) k_up2<true><<<grid, NTH, 0, s>>>(c, f, dc, hc, wc, mask);
     else k_up2<false><<<grid, NTH, 0, s>>>(c, f, dc, hc, wc, mask);
     return hip_ok(hipGetLastError(), "up-sampling launch");

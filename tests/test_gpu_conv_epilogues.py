@@ -106,3 +106,25 @@ def test_guess_from_unaligned_fields(mg, stride):
     # at stride 1 the input scale is summed by atomics: a last bit may differ
     assert torch.equal(got, ref) if stride > 1 else torch.allclose(got, ref, rtol=1e-2, atol=1e-3 * float(ref.abs().max()))
     net.close()
+
+
+def test_upsample_of_more_planes_than_a_grid_dimension(mg):
+    """A column of 65,540 coarse planes: more than one block row of the launch."""
+    import ctypes as C
+    nz = 65540
+    c = torch.randn(nz, 1, 2, dtype=torch.float64, device="cuda")
+    m = torch.ones(2 * nz, 2, 4, dtype=torch.int8, device="cuda")
+    f = torch.full((2 * nz, 2, 4), float("nan"), dtype=torch.float64, device="cuda")
+    st = mg.load_library().mg_upsample_guess(C.c_void_p(c.data_ptr()), 2, 1, nz, C.c_void_p(m.data_ptr()),
+                                             C.c_void_p(f.data_ptr()),
+                                             C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == 0
+    # per axis 3/4 of the parent and 1/4 of the next cell on the child's side (edge cells repeated)
+    ref = c
+    for ax in range(3):
+        n = ref.shape[ax]
+        i = torch.arange(n, device="cuda")
+        lo = ref.index_select(ax, (i - 1).clamp(min=0))
+        hi = ref.index_select(ax, (i + 1).clamp(max=n - 1))
+        ref = torch.stack([0.75 * ref + 0.25 * lo, 0.75 * ref + 0.25 * hi], dim=ax + 1).flatten(ax, ax + 1)
+    assert float((f - ref).abs().max()) <= 1e-14 * float(ref.abs().max())
