@@ -40,6 +40,7 @@
 
 #include "coarse_core.h"
 #include "cube_core.h"
+#include "live_items.h"
 #include "march_core.h"
 
 namespace mg {
@@ -110,10 +111,7 @@ __device__ __forceinline__ bool take(const BRef *__restrict__ refs, const int *_
 // leave, yet a finest launch of dead blocks still took 15-22 us of its 58 (96
 // patches).  Each span copies the positions of one patch's items of one launch
 // into that launch's map, so that its grid holds live items only; with
-// lev >= 0 it lists the patch level's cubes instead (src: their selector).
-struct Span {
-    int src, dst, n, lev;
-};
+// lev >= 0 it lists the patch level's cubes instead.
 __global__ void kb_spans(const Span *__restrict__ spans, int *__restrict__ map, BRef *__restrict__ cubes) {
     const Span s = spans[blockIdx.x];
     if (s.lev < 0)
@@ -610,16 +608,9 @@ struct mg_batch {
         std::vector<mg::Launch> k;
         hipGraphExec_t exec = nullptr;
         // direct launches: each launch's item ranges by patch, the patches the
-        // launches' maps hold now (empty: none) and their live items
-        struct Range {
-            int launch, patch, first, n;
-            int lev, sel, cubes;  // the items' level and selector; smoother launches: the level's cubes
-        };
-        std::vector<Range> ranges;
-        std::vector<char> mapped;
-        std::vector<int> live, live_cubes;  // live_cubes: -1 where a launch runs its items
-        std::vector<int> cube_max, cube_at;  // per launch: most live cubes it runs over (0: its items always), their place
-        std::vector<char> fused;             // a smoother launch and the restriction after it serve the same patches
+        // launches' maps hold now and their live items
+        mg::LiveItems items;
+        std::vector<char> fused;  // a smoother launch and the restriction after it serve the same patches
         mg::Span *spans = nullptr, *pin_spans = nullptr;  // device, pinned: two per range
         mg::BRef *cubes = nullptr;                        // device: the launches' live cubes
     };
@@ -1072,46 +1063,48 @@ bool build_programs(mg_batch *B) {
     B->refs = upload(B, refs);
     B->map = balloc<int>(B, refs.size());
     for (mg_batch::Prog *g : {&B->pre, &B->cycle[1], &B->cycle[2]}) {
+        LiveItems &I = g->items;
         for (size_t i = 0; i < g->k.size(); i++) {
             const Launch &k = g->k[i];
+            I.first.push_back(k.first);
             if (k.kind == K_FIN) continue;
             for (int j = 0; j < k.count;) {  // a launch lists its patches one after the other
                 const BRef r0 = refs[k.first + j];
                 const int p = r0.lev / MAXL, l = r0.lev % MAXL, j0 = j;
                 while (j < k.count && refs[k.first + j].lev / MAXL == p) j++;
                 const int o = g == &B->cycle[1] ? 1 : 2;
-                g->ranges.push_back({(int)i, p, j0, j - j0, r0.lev, r0.w & ~IDX_MASK,
-                                     4 * B->patches[p]->lev[l].od[l == 0 ? 2 : o].ntiles});
+                I.ranges.push_back({(int)i, p, j0, j - j0, r0.lev, r0.w & ~IDX_MASK,
+                                    4 * B->patches[p]->lev[l].od[l == 0 ? 2 : o].ntiles});
             }
         }
         const auto of = [&](size_t i) {  // patches and levels of launch i
             std::vector<int> v;
-            for (const auto &r : g->ranges)
+            for (const auto &r : I.ranges)
                 if (r.launch == (int)i) v.push_back(r.lev);
             return v;
         };
-        g->cube_max.assign(g->k.size(), 0);
-        g->cube_at.assign(g->k.size(), 0);
+        I.cube_max.assign(g->k.size(), 0);
+        I.cube_at.assign(g->k.size(), 0);
         int ncubes = 0;
         g->fused.assign(g->k.size(), 0);
         for (size_t i = 0; i < g->k.size() && !B->opt.fuse_passes; i++) {
             const int kind = g->k[i].kind;
             if (kind <= K_SM2P || kind == K_SM0N) {
                 int all = 0;
-                for (const auto &r : g->ranges)
+                for (const auto &r : I.ranges)
                     if (r.launch == (int)i) all += r.cubes;
                 const bool fine = kind == K_SM0 || kind == K_SM0P || kind == K_SM0N;
-                g->cube_max[i] = std::min(all, fine ? LIVE_CUBES_FINE : LIVE_CUBES_COARSE);
-                g->cube_at[i] = ncubes;
-                ncubes += g->cube_max[i];
+                I.cube_max[i] = std::min(all, fine ? LIVE_CUBES_FINE : LIVE_CUBES_COARSE);
+                I.cube_at[i] = ncubes;
+                ncubes += I.cube_max[i];
             }
             const bool plain = kind == K_SM0 || kind == K_SM1 || kind == K_SM2;
             g->fused[i] = plain && i + 1 < g->k.size() && g->k[i + 1].kind == (kind == K_SM0 ? K_RES0 : K_RESC) &&
                           of(i) == of(i + 1);
         }
-        g->spans = balloc<Span>(B, 2 * g->ranges.size());
+        g->spans = balloc<Span>(B, 2 * I.ranges.size());
         g->cubes = balloc<BRef>(B, ncubes);
-        BHIP(hipHostMalloc((void **)&g->pin_spans, std::max<size_t>(1, 2 * g->ranges.size()) * sizeof(Span),
+        BHIP(hipHostMalloc((void **)&g->pin_spans, std::max<size_t>(1, 2 * I.ranges.size()) * sizeof(Span),
                            hipHostMallocDefault));
     }
     B->nfirst = upload(B, first);
@@ -1253,8 +1246,8 @@ void launch(mg_batch *B, const Launch &k, int order, const int *state, hipStream
 void launch_cubes(mg_batch *B, const mg_batch::Prog &g, size_t i, bool fused, int order, const int *state,
                   hipStream_t s) {
     const Launch &k = g.k[i];
-    const BRef *c = g.cubes + g.cube_at[i];
-    const int n = g.live_cubes[i];
+    const BRef *c = g.cubes + g.items.cube_at[i];
+    const int n = g.items.live_cubes[i];
     const BLev *lev = B->lev[order];
     const unsigned gr = grid8(n);
     constexpr int NT = cube::NT;
@@ -1272,9 +1265,9 @@ void launch_cubes(mg_batch *B, const mg_batch::Prog &g, size_t i, bool fused, in
         case K_SM1P:
         case K_SM2P: kb_cube<false, true><<<gr, NT, 0, s>>>(c, n, lev, state, order); break;
         case K_SM0N: {
-            const bool whole = g.live[i] == k.count;
-            const unsigned gi = grid8(g.live[i]);
-            kb_cube_norm<<<gi + gr, NT, 0, s>>>(B->refs + k.first, whole ? nullptr : B->map + k.first, g.live[i],
+            const int live = g.items.live[i];
+            const unsigned gi = grid8(live);
+            kb_cube_norm<<<gi + gr, NT, 0, s>>>(B->refs + k.first, live == k.count ? nullptr : B->map + k.first, live,
                                                 (int)gi, c, n, lev, state, order, B->part, k.poff);
             break;
         }
@@ -1287,40 +1280,26 @@ void launch_cubes(mg_batch *B, const mg_batch::Prog &g, size_t i, bool fused, in
 // live cubes run over those instead of their items.
 void run_live(mg_batch *B, mg_batch::Prog &g, int order, const int *state, const std::vector<char> &on,
               hipStream_t s) {
-    if (g.mapped != on) {
-        g.live.assign(g.k.size(), 0);
-        g.live_cubes.assign(g.k.size(), 0);
-        for (const auto &r : g.ranges)
-            if (on[r.patch]) g.live_cubes[r.launch] += r.cubes;
-        for (size_t i = 0; i < g.k.size(); i++)
-            g.live_cubes[i] = g.cube_max[i] > 0 && g.live_cubes[i] <= g.cube_max[i] ? 0 : -1;
-        int ns = 0;
-        for (const auto &r : g.ranges)
-            if (on[r.patch]) {
-                const int i = r.launch;
-                if (g.live_cubes[i] >= 0) {
-                    g.pin_spans[ns++] = Span{r.sel, g.cube_at[i] + g.live_cubes[i], r.cubes, r.lev};
-                    g.live_cubes[i] += r.cubes;
-                }
-                g.pin_spans[ns++] = Span{r.first, g.k[i].first + g.live[i], r.n, -1};
-                g.live[i] += r.n;
-            }
-        g.mapped = on;
+    LiveItems &I = g.items;
+    if (!I.holds(on)) {
+        const int ns = I.plan(on, g.pin_spans);
         if (ns > 0) {
             BHIP(hipMemcpyAsync(g.spans, g.pin_spans, ns * sizeof(Span), hipMemcpyHostToDevice, s));
             kb_spans<<<ns, 256, 0, s>>>(g.spans, B->map, g.cubes);
+            BHIP(hipGetLastError());
         }
+        I.hold(on);
     }
     for (size_t i = 0; i < g.k.size(); i++) {
         const Launch &k = g.k[i];
-        if (g.live_cubes[i] >= 0) {
-            if (g.live_cubes[i] == 0) continue;
+        if (I.live_cubes[i] >= 0) {
+            if (I.live_cubes[i] == 0) continue;
             launch_cubes(B, g, i, g.fused[i], order, state, s);
             if (g.fused[i]) i++;  // the restriction has run
-        } else if (k.kind == K_FIN || g.live[i] == k.count) {
+        } else if (k.kind == K_FIN || I.live[i] == k.count) {
             launch(B, k, order, state, s);
-        } else if (g.live[i] > 0) {
-            launch(B, k, order, state, s, g.live[i]);
+        } else if (I.live[i] > 0) {
+            launch(B, k, order, state, s, I.live[i]);
         }
     }
     BHIP(hipGetLastError());
