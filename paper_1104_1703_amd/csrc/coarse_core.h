@@ -244,9 +244,17 @@ __device__ void smooth(const Lv<T> &L, int passes) {
 // unit right-hand side of cell j, k_deep_matrix); 64 half-sweeps of a 4^3 level
 // take 9 us, each an LDS round trip, the product about 1 us.  16 lanes share a
 // row, lane q summing columns q, q + 16, ... in order, then an exchange tree:
-// the same sums for any thread count.  DEEP_MAX cells: a matrix of 512 KB, which
+// the same sums for any thread count.  A cell whose right-hand side does not
+// reach a row (another part of the domain, or out of the passes' reach) has a
+// zero there and is left out, so that an infinity or a NaN of its stays with the
+// cells that the passes would carry it to.  DEEP_MAX cells: a matrix of 512 KB, which
 // one workgroup reads in less time than the passes take.
 constexpr int DEEP_MAX = 256;
+
+template <typename T>
+__device__ __forceinline__ T deep_term(T m, T f, T s) {
+    return m != T(0) ? fma_t<T>(m, f, s) : s;
+}
 
 template <typename T, int NTH>
 __device__ void deep_solve(const Lv<T> &L, const T *__restrict__ M) {
@@ -255,7 +263,7 @@ __device__ void deep_solve(const Lv<T> &L, const T *__restrict__ M) {
         const int row = row0 + (int)(threadIdx.x >> 4);
         T s = T(0);
         if (row < L.n)
-            for (int j = q; j < L.n; j += 16) s = fma_t<T>(M[row * L.n + j], L.f[j], s);
+            for (int j = q; j < L.n; j += 16) s = deep_term<T>(M[row * L.n + j], L.f[j], s);
 #pragma unroll
         for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o);
         if (row < L.n && q == 0) L.x[row] = L.d[row] != T(0) ? s : T(0);
@@ -607,9 +615,9 @@ __device__ __forceinline__ void small_fast(T *sm, const SmallLevels<T> &S, const
                 if (inreg) {
 #pragma unroll
                     for (int k = 0; k < 4; k++)
-                        if (q + 16 * k < nd) s = fma_t<T>(mreg[k], fd[q + 16 * k], s);
+                        if (q + 16 * k < nd) s = deep_term<T>(mreg[k], fd[q + 16 * k], s);
                 } else {
-                    for (int j = q; j < nd; j += 16) s = fma_t<T>(S.deep[row * nd + j], fd[j], s);
+                    for (int j = q; j < nd; j += 16) s = deep_term<T>(S.deep[row * nd + j], fd[j], s);
                 }
             }
 #pragma unroll
