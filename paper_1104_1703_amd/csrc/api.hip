@@ -495,7 +495,35 @@ void create(mg_hierarchy *H, const int8_t *mask, int nx, int ny, int nz, double 
         else
             for (int o = 1; o <= 2; o++) A.want(lev[l].od[o].d, lev[l].n);
     }
-    A.alloc(H);
+    // the refusal of an invalid mask by k_validate's counts
+    const auto check = [](const unsigned long long *c) {
+        if (c[0]) {
+            set_error("mask holds " + std::to_string(c[0]) + " values other than +1/-1");
+            throw Fail{MG_ERR_ARG};
+        }
+        if (c[1]) {
+            set_error("mask has " + std::to_string(c[1]) + " active cells in the outermost layer");
+            throw Fail{MG_ERR_ARG};
+        }
+        if (c[2] == 0) {
+            set_error("mask has no active cell");
+            throw Fail{MG_ERR_NO_ACTIVE};
+        }
+    };
+    try {
+        A.alloc(H);
+    } catch (const Fail &) {
+        // too little memory for the arrays: an invalid mask is refused as one all the same
+        const std::string why = mg_last_error();
+        unsigned long long *c = alloc_n<unsigned long long>(H, 3), hc[3];
+        HIPCHK(hipMemsetAsync(c, 0, sizeof(hc), s));
+        launch_validate(mask, nx, ny, nz, nullptr, c, s);
+        HIPCHK(hipMemcpyAsync(hc, c, sizeof(hc), hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        check(hc);
+        set_error(why);
+        throw;
+    }
     unsigned long long *ctr = (unsigned long long *)back, *nact = ctr + 3;
     uint8_t *flags = (uint8_t *)(ctr + NCTR);
     HIPCHK(hipMemsetAsync(ctr, 0, NCTR * sizeof(unsigned long long), s));
@@ -516,18 +544,7 @@ void create(mg_hierarchy *H, const int8_t *mask, int nx, int ny, int nz, double 
     HIPCHK(hipStreamSynchronize(s));
     unsigned long long hv[NCTR];
     memcpy(hv, hb.data(), sizeof(hv));
-    if (hv[0]) {
-        set_error("mask holds " + std::to_string(hv[0]) + " values other than +1/-1");
-        throw Fail{MG_ERR_ARG};
-    }
-    if (hv[1]) {
-        set_error("mask has " + std::to_string(hv[1]) + " active cells in the outermost layer");
-        throw Fail{MG_ERR_ARG};
-    }
-    if (hv[2] == 0) {
-        set_error("mask has no active cell");
-        throw Fail{MG_ERR_NO_ACTIVE};
-    }
+    check(hv);
     const unsigned long long *ha = hv + 3;
     lev[0].od[1].nact = lev[0].od[2].nact = (int64_t)hv[2];
     for (int o = 1; o <= 2; o++) {

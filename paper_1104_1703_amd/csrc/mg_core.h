@@ -196,7 +196,7 @@ void set_error(const std::string &s);
 bool hip_ok(hipError_t e, const char *what);
 
 // -------- setup kernels (setup.hip) --------
-// mask checks into bad[3], finest counts into cnt
+// mask checks into bad[3], finest counts into cnt (may be null)
 void launch_validate(const int8_t *mask, int nx, int ny, int nz, int32_t *cnt, unsigned long long *bad,
                      hipStream_t s);
 void launch_count_up(const Level &fine, const Level &coarse, hipStream_t s);

@@ -27,7 +27,7 @@ __device__ __forceinline__ unsigned block_total(unsigned v) {
 }
 
 // Mask checks (bad[0]: values other than +1/-1, bad[1]: active cells in the
-// outermost layer, bad[2]: active cells) and the finest counts.  A thread takes
+// outermost layer, bad[2]: active cells) and the finest counts (cnt may be null).  A thread takes
 // 8 cells at a time; the sums take one atomic a block, of at most
 // 1024: one a wave, of up to 16384 on one line of memory, took 172 us at 128^3,
 // this 15 us (64^3: 34 -> 7).
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(256) void k_validate(const int8_t *__restrict__ mas
         for (int q = 0; q < U; q++) {
             const size_t p = p0 + q * 256;
             if (p >= n) break;
-            cnt[p] = v[q] == 1 ? 1 : 0;
+            if (cnt) cnt[p] = v[q] == 1 ? 1 : 0;
             bad_val += (v[q] != 1 && v[q] != -1);
             act += (v[q] == 1);
             if (v[q] != -1) {
