@@ -21,6 +21,7 @@
 #include "mg.h"
 #include "mg_core.h"
 #include "nn_core.h"
+#include "nn_plan.h"
 
 namespace mg {
 namespace nn {
@@ -364,16 +365,15 @@ __global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina,
 // atomic per weight and block; one address takes about 50 ns per atomic, so
 // the sums of single waves (8 times as many) took most of a launch.
 //
-// Against the earlier kernel, which re-staged its input for every tap and
-// transposed it element by element (8 x 64^3 voxels unless stated): 16 -> 16
+// Against the kernel per tap (below), which re-stages its input for every tap
+// and transposes it element by element (8 x 64^3 voxels unless stated): 16 -> 16
 // channels 1190 -> 46 us (134 MB read: 2.9 TB/s; 34 us of it the march, the
 // rest the sums), 48 -> 16 2360 -> 114 us, 96 -> 32 on 8 x 32^3 600 -> 72 us
 // (650 TFLOP/s), 64 -> 64 on 8 x 16^3 50 -> 18 us.  The fine resolutions are
 // bound by the bytes staged, the coarse ones by the march's latency and the
 // sums at the end.
-constexpr int BW_T = 16;                 // voxels of a row, and rows of the column
+// BW_T (nn_plan.h): voxels of a row, and rows of the column
 constexpr int BW_H = BW_T + 2;           // ... with halo
-constexpr int BW_NT = 512;
 constexpr int BW_G = 4;                  // taps reduced at a time (28 with the bias)
 constexpr int BW_XN = 2 * BW_H * BW_H;   // 16-byte pieces (8 channels of a voxel) of an X plane
 constexpr int BW_DN = 2 * BW_T * BW_T;   // ... of a dout plane: one per thread
@@ -553,6 +553,115 @@ __global__ __launch_bounds__(BW_NT, 2) void k_conv_bwd_w(const bf16 *__restrict_
             if (t < 27) atomicAdd(&dw[((size_t)t * cout + co0 + co) * cin + ci0 + ci], v);
             else if (bias && ci == 0) atomicAdd(&dbias[co0 + co], v);
         }
+    }
+}
+
+// The same gradient for few voxels, or maps much smaller than a column: a block
+// takes one tap, 64 output channels (one 16-channel tile per wave) and a chunk
+// of the voxels of all samples in a row; 32 voxels at a time are staged in LDS
+// (dout rows and shifted input rows), then read back transposed element by
+// element as MFMA fragments.  Its work follows the voxels, whatever the shape of
+// the map, where the march pays for whole 16 x 16 columns and 27 tiles of atomics
+// a block: 512 samples of 2^3 voxels, 64 -> 128 channels, 31 us here against 967,
+// 256 of 4^3, 64 -> 64, 40 against 296, one of 64^2 x 1, 16 -> 16, 5 against 12.
+// Large maps are the march's (line in per_tap).
+
+template <int NCI>  // input-channel tiles of 16 (cin = 16 * NCI)
+__global__ __launch_bounds__(NTH) void k_conv_bwd_w_tap(const bf16 *__restrict__ dout, int cout,
+                                                     const bf16 *__restrict__ ina, int ca, int upa,
+                                                     const bf16 *__restrict__ inb, int cb, float *__restrict__ dw,
+                                                     float *__restrict__ dbias, int D, int H, int W, long long V,
+                                                     int chunk) {
+    __shared__ bf16 sd[BW_KV][64 + 8];       // dout rows (64 channels of this block), padded
+    __shared__ bf16 sx[BW_KV][16 * NCI + 8]; // shifted input rows
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int row = lane & 15, grp = lane >> 4;
+    const int tap = blockIdx.x;  // the 27 taps of one voxel chunk run side by side and share L2
+    const int co_blk = blockIdx.z * 64;
+    const int cin = 16 * NCI;
+    const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
+    const int Dc = D >> 1, Hc = H >> 1, Wc = W >> 1;
+    const long long v0 = (long long)blockIdx.y * chunk;
+    const long long v1 = v0 + chunk < V ? v0 + chunk : V;
+    f32x4 acc[NCI];
+#pragma unroll
+    for (int t = 0; t < NCI; t++) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float bsum = 0.f;
+    const bool wave_ok = co_blk + wave * 16 < cout;
+    for (long long vb = v0; vb < v1; vb += BW_KV) {
+        __syncthreads();
+        // stage dout[vb .. vb+32)[co_blk .. co_blk+64) : 32 x 64 bf16, 8 per thread
+        {
+            const int e = threadIdx.x * 8;          // 256 threads x 8 = 2048 = 32 x 64
+            const int vr = e / 64, c = e % 64;
+            const long long v = vb + vr;
+            bf16x8 val = zero8();
+            if (v < v1 && co_blk + c < cout) val = *(const bf16x8 *)(dout + v * cout + co_blk + c);
+#pragma unroll
+            for (int j = 0; j < 8; j++) sd[vr][c + j] = val[j];
+        }
+        // stage X[v + tap shift][0 .. cin) : 32 x cin bf16, 8 per thread per pass
+        for (int e = threadIdx.x * 8; e < BW_KV * cin; e += NTH * 8) {
+            const int vr = e / cin, c = e % cin;
+            const long long v = vb + vr;
+            bf16x8 val = zero8();
+            if (v < v1) {
+                long long t = v;
+                const int x = (int)(t % W) + dx;
+                t /= W;
+                const int y = (int)(t % H) + dy;
+                t /= H;
+                const int z = (int)(t % D) + dz;
+                const int n = (int)(t / D);
+                if (z >= 0 && z < D && y >= 0 && y < H && x >= 0 && x < W) {
+                    if (c < ca) {
+                        size_t vox;
+                        if (upa) vox = (((size_t)n * Dc + (z >> 1)) * Hc + (y >> 1)) * Wc + (x >> 1);
+                        else vox = (((size_t)n * D + z) * H + y) * W + x;
+                        val = *(const bf16x8 *)(ina + vox * ca + c);
+                    } else {
+                        const size_t vox = (((size_t)n * D + z) * H + y) * W + x;
+                        val = *(const bf16x8 *)(inb + vox * cb + (c - ca));
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 8; j++) sx[vr][c + j] = val[j];
+        }
+        __syncthreads();
+        if (wave_ok) {
+            // A[m = co][k = voxel]: lane takes co = row, voxels 8*grp .. 8*grp+7
+            bf16x8 afr;
+#pragma unroll
+            for (int j = 0; j < 8; j++) afr[j] = sd[grp * 8 + j][wave * 16 + row];
+            if (tap == 13 && dbias) {
+#pragma unroll
+                for (int j = 0; j < 8; j++) bsum += (float)afr[j];
+            }
+#pragma unroll
+            for (int t = 0; t < NCI; t++) {
+                bf16x8 bfr;  // B[k = voxel][n = ci]
+#pragma unroll
+                for (int j = 0; j < 8; j++) bfr[j] = sx[grp * 8 + j][t * 16 + row];
+                acc[t] = mfma(afr, bfr, acc[t]);
+            }
+        }
+    }
+    if (!wave_ok) return;
+    // D[m = co][n = ci]: lane holds co = 4*grp + r, ci = row
+#pragma unroll
+    for (int t = 0; t < NCI; t++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int co = co_blk + wave * 16 + grp * 4 + r;
+            const int ci = t * 16 + row;
+            if (co < cout) atomicAdd(&dw[((size_t)tap * cout + co) * cin + ci], acc[t][r]);
+        }
+    if (tap == 13 && dbias) {
+        // lanes with the same row hold partial sums of channel co = row over different voxel groups
+        bsum += __shfl_xor(bsum, 16);
+        bsum += __shfl_xor(bsum, 32);
+        if (grp == 0) atomicAdd(&dbias[co_blk + wave * 16 + row], bsum);
     }
 }
 
@@ -1122,30 +1231,38 @@ inline unsigned blocks_for(long long n, int per = 256) {
     return (unsigned)(g > 0 ? g : 1);
 }
 
+template <int NCI>
+void launch_bww_tap(const bf16 *dout, int cout, const bf16 *ina, int ca, int upa, const bf16 *inb, int cb, float *dw,
+                    float *db, int D, int H, int W, long long V, hipStream_t s) {
+    const int groups = (cout + 63) / 64;
+    const long long chunk = tap_chunk(V, groups);
+    dim3 grid(27, (unsigned)((V + chunk - 1) / chunk), (unsigned)groups);
+    k_conv_bwd_w_tap<NCI><<<grid, NTH, 0, s>>>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, V, (int)chunk);
+}
+
 void launch_bww(const bf16 *dout, int cout, const bf16 *ina, int ca, int upa, const bf16 *inb, int cb, float *dw,
                 float *db, int n, int D, int H, int W, hipStream_t s) {
-    const int ntx = (W + BW_T - 1) / BW_T, nty = (H + BW_T - 1) / BW_T;
-    const long long tiles = (long long)(ca + cb) / 16 * (cout / 16), cols = (long long)ntx * nty * n * tiles;
-    // z chunks: the split with the shortest march over the rounds it takes (one
-    // block per CU at once, two planes more staged than multiplied, and about
-    // six steps' worth of reduction at the end of a block)
-    int nzc = 1;
-    long long best = 0;
-    for (int k = 1; k <= D; k++) {
-        const int zc = (D + k - 1) / k;
-        const long long t = (cols * ((D + zc - 1) / zc) + 255) / 256 * (zc + 8);
-        if (k == 1 || t < best) {
-            best = t;
-            nzc = k;
+    const long long V = (long long)n * D * H * W;
+    const MarchPlan m = march_plan(n, D, H, W, ca + cb, cout);
+    if (per_tap(m, ca + cb, cout, V, H, W)) {
+        switch ((ca + cb) / 16) {
+            case 1: launch_bww_tap<1>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, V, s); break;
+            case 2: launch_bww_tap<2>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, V, s); break;
+            case 3: launch_bww_tap<3>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, V, s); break;
+            case 4: launch_bww_tap<4>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, V, s); break;
+            case 6: launch_bww_tap<6>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, V, s); break;
+            case 8: launch_bww_tap<8>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, V, s); break;
+            default: launch_bww_tap<12>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, V, s); break;
         }
+        return;
     }
-    const int zc = (D + nzc - 1) / nzc;
-    nzc = (D + zc - 1) / zc;
-    dim3 grid((unsigned)((long long)ntx * nty * nzc * n), (unsigned)tiles);
+    dim3 grid((unsigned)(m.cols * m.nzc), (unsigned)m.tiles);
     if (W % BW_T || H % BW_T)
-        k_conv_bwd_w<true><<<grid, BW_NT, 0, s>>>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, ntx, nty, nzc, zc);
+        k_conv_bwd_w<true><<<grid, BW_NT, 0, s>>>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, m.ntx, m.nty,
+                                                  m.nzc, m.zc);
     else
-        k_conv_bwd_w<false><<<grid, BW_NT, 0, s>>>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, ntx, nty, nzc, zc);
+        k_conv_bwd_w<false><<<grid, BW_NT, 0, s>>>(dout, cout, ina, ca, upa, inb, cb, dw, db, D, H, W, m.ntx, m.nty,
+                                                   m.nzc, m.zc);
 }
 
 // ------------------------------------------------ host launchers (nn_core.h)
