@@ -103,14 +103,27 @@ __device__ __forceinline__ bf16x8 gated(bf16x8 v, const bf16x8 &g) {
     return v;
 }
 
+// Blocks per CU that the tilings' registers have to leave room for.  A lane
+// holds 16 NTC sums, 72 registers of voxels and 12 NTC of weights; with the
+// weights a tap row ahead of the products and the staged pieces the compiler
+// took 276 to 314 registers at NTC = 3 (HALF) and 4 and 201 at NTC = 2, which
+// left one block on a CU, and two, where LDS allows three.  So the wide tilings
+// of 32-channel chunks fetch a row's weights when its products come (NTC = 3 of
+// whole chunks alone has room for both), and the bound keeps the rest of the
+// schedule within 256 and 168 registers.  8 x 64^3 voxels: 32 -> 64 channels
+// 467 -> 334 us, 48 -> 64 602 -> 411, 64 -> 64 1037 -> 870, 48 -> 48 489 -> 354;
+// 64 maps of 64 x 1 x 64, 48 -> 64, 269 -> 170.
+constexpr int conv_blocks(int ck, int ntc) { return ntc >= 3 ? 2 : ck == 32 && ntc == 2 ? 3 : 1; }
+
 template <int CK, int NTC, bool HALF = false>
-__global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina, int ca, int upa,
+__global__ __launch_bounds__(NTH, conv_blocks(CK, NTC)) void k_conv_tile(const bf16 *__restrict__ ina, int ca, int upa,
                                                    const bf16 *__restrict__ inb, int cb, const bf16 *__restrict__ wt,
                                                    const float *__restrict__ bias, bf16 *__restrict__ out, int cout,
                                                    int relu, int D, int H, int W, int ntx, int nty, int ntz,
                                                    int nblk, ConvOut eo, int frag) {
     constexpr int CKP = CK == 16 ? CK : CK + 8;
     constexpr int MT = 4;
+    constexpr bool AHEAD = NTC == 1 || (NTC == 3 && !HALF);
     static_assert(MT == TY && NTH / 64 == TZ && TX == 16, "a wave owns the 16 x 4 voxels of one tile plane");
     constexpr int UP = TX * TY * TZ * NTC * 16;  // up-sampled part of a split output, on its way to the sums
     __shared__ __attribute__((aligned(16))) bf16 tile[HV * CKP > UP ? HV * CKP : UP];
@@ -164,23 +177,23 @@ __global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina,
     const size_t wtap = (size_t)cout * cin;
     for (int c0 = 0; c0 < cin; c0 += CK) {
         // Whole chunks of 32 channels: B fragments of a (dz, dy) row of taps are
-        // fetched a row ahead, the first before the staging
+        // fetched a row ahead, the first before the staging (AHEAD)
         const bool full = CK == 32 && (!HALF || cin - c0 >= 32);
         unsigned wl[NTC];  // byte offsets within a tap's weights (K entries c0 + 8 grp .. + 7)
 #pragma unroll
         for (int nt = 0; nt < NTC; nt++)
             wl[nt] = frag ? (unsigned)((((co_base >> 4) + nt) * (cin >> 5) + (c0 >> 5)) * 1024 + lane * 16)
                           : (unsigned)(((co_base + nt * 16 + row) * cin + c0 + grp * 8) * 2);
-        bf16x8 bfr[2][3][NTC];
+        bf16x8 bfr[AHEAD ? 2 : 1][3][NTC];
         const auto fetch = [&](int r) {
 #pragma unroll
             for (int dx = 0; dx < 3; ++dx) {
                 const char *wb = (const char *)(wt + (r * 3 + dx) * wtap);  // uniform
 #pragma unroll
-                for (int nt = 0; nt < NTC; nt++) bfr[r & 1][dx][nt] = *(const bf16x8 *)(wb + wl[nt]);
+                for (int nt = 0; nt < NTC; nt++) bfr[AHEAD ? r & 1 : 0][dx][nt] = *(const bf16x8 *)(wb + wl[nt]);
             }
         };
-        if (full) fetch(0);
+        if (AHEAD && full) fetch(0);
         __syncthreads();
         {
             const int c = c0 + sub * 8;  // this thread's 8 channels: all of a or all of b (8 | ca)
@@ -189,7 +202,11 @@ __global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina,
             const bf16 *const *rb = rowb[isa ? 0 : 1];
             // voxel hv = row hr (z-major over (z, y)) x HX + hx, stepped by VPT.
             // Pieces outside the box load the tensor's first one and are zeroed,
-            // so that no branch keeps the loads from being in flight together.
+            // so that no branch keeps the loads from being in flight together;
+            // in the wide tilings of 32-channel chunks they are left out, which
+            // costs nothing there and saves a flat map most of its loads (512
+            // maps of 1 x 64, 96 -> 32: 90 -> 81 us).
+            constexpr bool SKIP = CK == 32 && NTC > 1;
             constexpr int SDR = VPT / HX, SDX2 = VPT % HX, NK = (HV + VPT - 1) / VPT;
             int hx = hv0 % HX, hr = hv0 / HX;
             bf16x8 v[NK];
@@ -200,7 +217,12 @@ __global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina,
                 const bf16 *bp = rb[min(hr, HZ * HY - 1)];
                 ok[k] = cok && bp && (unsigned)gx < (unsigned)W;
                 // x < 2^24, channels < 2^24
-                v[k] = *(const bf16x8 *)(ok[k] ? bp + (__umul24((unsigned)(gx >> sh), (unsigned)cs) + coff) : ina);
+                if constexpr (SKIP) {
+                    v[k] = zero8();
+                    if (ok[k]) v[k] = *(const bf16x8 *)(bp + (__umul24((unsigned)(gx >> sh), (unsigned)cs) + coff));
+                } else {
+                    v[k] = *(const bf16x8 *)(ok[k] ? bp + (__umul24((unsigned)(gx >> sh), (unsigned)cs) + coff) : ina);
+                }
                 hx += SDX2;
                 hr += SDR;
                 if (hx >= HX) {
@@ -228,7 +250,8 @@ __global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina,
 #pragma unroll
                 for (int dy = 0; dy < 3; dy++) {
                     const int r = dz * 3 + dy;
-                    if (r < 8) fetch(r + 1);
+                    if constexpr (!AHEAD) fetch(r);
+                    else if (r < 8) fetch(r + 1);
                     // keep the loads ahead of the products (with HALF the registers
                     // that takes cost more: 153 against 171 us)
                     if constexpr (!HALF) __builtin_amdgcn_sched_barrier(0);
@@ -238,7 +261,7 @@ __global__ __launch_bounds__(NTH) void k_conv_tile(const bf16 *__restrict__ ina,
                         for (int mt = 0; mt < MT; mt++)
 #pragma unroll
                             for (int nt = 0; nt < NTC; nt++)
-                                acc[mt][nt] = mfma(bfr[r & 1][dx][nt], afr[mt + dy][dx], acc[mt][nt]);
+                                acc[mt][nt] = mfma(bfr[AHEAD ? r & 1 : 0][dx][nt], afr[mt + dy][dx], acc[mt][nt]);
                 }
             }
         } else if constexpr (CK == 16 || HALF) {
