@@ -1037,17 +1037,21 @@ __global__ void k_head(const bf16 *__restrict__ x, const float *__restrict__ w, 
 // A thread forms the two z and y children and one x pair of a coarse cell from
 // its 27 neighbours and stores pairs (16 bytes with VEC): one thread per child,
 // with 64-bit index divisions and 8 loads for one store, took 66 us for
-// 128^3 -> 256^3, this 40 us (168 MB).
+// 128^3 -> 256^3, this 40 us (168 MB).  A block takes `per` coarse planes that
+// fit it side by side (one where a plane fills it): 100000 planes of 3 x 3 took
+// 112 us with one plane a block, 38 with a thread per child, 23 so.
 template <bool VEC>
 __global__ __launch_bounds__(NTH) void k_up2(const double *__restrict__ c, double *__restrict__ f, int Dc, int Hc,
-                                             int Wc, const int8_t *__restrict__ mask) {
+                                             int Wc, int per, const int8_t *__restrict__ mask) {
     typedef double d2 __attribute__((ext_vector_type(2)));
-    const int e = blockIdx.x * NTH + threadIdx.x;  // row (y) and x of a coarse plane
-    if (e >= Hc * Wc) return;
-    const int py = e / Wc, px = e - py * Wc;
+    const unsigned pl = (unsigned)Hc * (unsigned)Wc;     // (2^32 of them would not fit the device)
+    const int q0 = per > 1 ? (int)(threadIdx.x / pl) : 0;  // plane of the block's
+    const unsigned e = blockIdx.x * NTH + threadIdx.x - q0 * pl;  // row (y) and x of a coarse plane
+    if (q0 >= per || e >= pl) return;
+    const int py = (int)(e / (unsigned)Wc), px = (int)(e - (unsigned)py * Wc);
     const size_t base = (size_t)blockIdx.z * Dc * Hc * Wc, cpl = (size_t)Hc * Wc;
     const size_t H = 2 * (size_t)Hc, W = 2 * (size_t)Wc;
-    for (int pz = blockIdx.y; pz < Dc; pz += gridDim.y) {
+    for (int pz = (int)blockIdx.y * per + q0; pz < Dc; pz += (int)gridDim.y * per) {
         const size_t f0 = (((size_t)blockIdx.z * 2 * Dc + 2 * pz) * H + 2 * py) * W + 2 * px;
         bool act[2][2][2];
         bool any = false;
@@ -1481,9 +1485,11 @@ bool head(const void *x, const float *w, const float *b, const double *st, const
 }
 
 bool up2(const double *c, double *f, int n, int dc, int hc, int wc, const int8_t *mask, hipStream_t s) {
-    const dim3 grid((unsigned)(((long long)hc * wc + NTH - 1) / NTH), (unsigned)std::min(dc, 65535), (unsigned)n);
-    if (((uintptr_t)f & 15) == 0) k_up2<true><<<grid, NTH, 0, s>>>(c, f, dc, hc, wc, mask);
-    else k_up2<false><<<grid, NTH, 0, s>>>(c, f, dc, hc, wc, mask);
+    const long long pl = (long long)hc * wc;
+    const int per = pl < NTH ? (int)std::min<long long>(NTH / pl, dc) : 1;
+    const dim3 grid((unsigned)((pl + NTH - 1) / NTH), (unsigned)std::min((dc + per - 1) / per, 65535), (unsigned)n);
+    if (((uintptr_t)f & 15) == 0) k_up2<true><<<grid, NTH, 0, s>>>(c, f, dc, hc, wc, per, mask);
+    else k_up2<false><<<grid, NTH, 0, s>>>(c, f, dc, hc, wc, per, mask);
     return hip_ok(hipGetLastError(), "up-sampling launch");
 }
 
