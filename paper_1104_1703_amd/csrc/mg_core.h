@@ -32,16 +32,26 @@ constexpr int item_depth(int level) {
 constexpr bool depth_supported(int level, int depth) {
     return level == 0 ? (depth == 8 || depth == 16 || depth == 32) : (depth == 2 || depth == 4 || depth == 8);
 }
-// A level of at most this many 8^3 cubes (four per active tile) runs all its
-// passes over cubes: two rounds of blocks at most, each one memory latency and
-// three barriers, where a march takes a latency and two barriers per plane on a
-// chip its items cannot fill.  Finest passes (plain, norm, residual, prolonging,
-// FP64, march against cubes): 64^3 sphere with holes 15 / 18 / 22 / 20 us
-// against 5.0 / 8.3 / 9.2 / 8.8; 136 x 72 x 104 (2340 cubes) 17 / 21 / 25 / 23
-// against 10.8 / 16.3 / 19.3 / 18.1; at 160 x 144 x 176 (about 3400 active
-// cubes) a whole cycle takes the same either way, above that the cubes' 3.4
-// times larger halo traffic loses.
+// A level of at most this many 8^3 cubes (four per active tile) runs its passes
+// over cubes: two rounds of blocks at most, each one memory latency and three
+// barriers, where a march takes a latency and two barriers per plane on a chip
+// its items cannot fill.  That is the line of the plain finest pass (64^3 boxes,
+// 512 cubes, FP64, march against cubes: 15.0 / 5.6 us, 128^3, 4096: 19.4 / 18.7)
+// and of the coarse passes that smooth, and smooth and restrict (a full 128^3
+// level 2: 28.8 / 19.1 and 44 / 36 us).
 constexpr int FEW_CUBES = 4096;
+// The finest passes with wider halos (input norm, residual, prolongation) load
+// 2.7 to 3.4 times the cells of a plain cube and cross the march earlier: at
+// 3136 cubes (a 112^3 box, FP64) 22.2 / 21.1, 28.3 / 26.5 and 26.1 / 24.6 us, at
+// 3600 (120^3) 22.5 / 24.9, 28.7 / 30.7 and 25.4 / 28.1; FP32 residual and
+// prolongation 24.5 / 22.2 and 24.2 / 21.3, at 3600 24.6 / 25.0 and 23.6 / 23.8.
+constexpr int FEW_CUBES_WIDE = 3328;
+// The prolonging pass of level 1, whose march has items of eight planes (FP64)
+// or four (FP32): 1728 cubes 17.3 / 16.3 us and 12.2 / 13.7, 1896 17.3 / 18.3,
+// 2592 20.4 / 23.4 and 14.8 / 19.4; FP32 at 1080 11.9 / 11.1, 1152 11.8 / 12.0.
+// On the levels below, FP64 cubes always win (41.3 / 32.7 us at 4096), FP32 ones
+// never by more than the runs differ (40 to 500 cubes 7.6 / 8.2, 4096 26.6 / 27.1).
+constexpr int FEW_CUBES_PROLONG1 = 1792, FEW_CUBES_PROLONG1_32 = 1152;
 // Coarse-level option value selecting 8^3 cube items for plain passes (the
 // passes that apply the prolongation keep the default march).
 constexpr int DEPTH_CUBE = 1;
@@ -87,8 +97,14 @@ struct OrderData {
     int ntiles = 0, nsegs = 0;
     int depth = 0;  // planes per work item of segs (its masks hold depth + 4 words per item)
     bool cube = false;  // coarse levels: plain passes over 8^3 cubes loaded whole (no z march)
-    bool few = false;   // too few work items to fill the chip: every pass of the level over cubes
+    bool few = false;   // too few work items to fill the chip: the passes cross over to cubes at their lines
     bool cubes() const { return cube || few; }
+    bool few_wide() const { return few && 4 * ntiles <= FEW_CUBES_WIDE; }  // finest passes with wider halos
+    bool few_prolong(int level, bool f32) const {
+        if (!few || level == 0) return few_wide();
+        if (level > 1) return !f32;
+        return 4 * ntiles <= (f32 ? FEW_CUBES_PROLONG1_32 : FEW_CUBES_PROLONG1);
+    }
     int64_t nact = 0;
 };
 

@@ -252,7 +252,7 @@ template <typename T>
 hipError_t launch_fine_res(const Level &L, const OrderData &od, const T *xin, T *xout, const T *f, const Level &C,
                            const T *cd, T *fc, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     if (od.nsegs == 0) return hipSuccess;
-    if (od.few) return launch_cube_restrict<T, true>(xin, xout, f, L, od, C, cd, fc, s, e0, e1);
+    if (od.few_wide()) return launch_cube_restrict<T, true>(xin, xout, f, L, od, C, cd, fc, s, e0, e1);
     const T h2 = (T)(L.h * L.h), ih2 = (T)(1.0 / (L.h * L.h));
     hipError_t err = hipSuccess;
     with_fine_pass<T>(od, [&](auto Z, auto P) {
@@ -324,7 +324,7 @@ hipError_t launch_rbgs(const Level &L, int level, const OrderData &od, const dou
 hipError_t launch_rbgs_norm(const Level &L, const OrderData &od, const double *xin, double *xout, const double *f,
                             double *part, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     if (od.nsegs == 0) return hipSuccess;
-    if (od.few)
+    if (od.few_wide())
         return launch_k(k_rbgs_cube_norm, (unsigned)od.nsegs + grid8(4 * od.ntiles), s, e0, e1, xin, xout, f, L.code,
                         L.nx, L.ny, L.nz, L.ntx, L.nty, L.h * L.h, 1.0 / (L.h * L.h), od.tiles, od.ntiles, od.segs,
                         od.nsegs, L.halt, part);
@@ -340,7 +340,7 @@ hipError_t launch_rbgs_prolong(const Level &L, int level, const OrderData &od, c
                                const double *xin, double *xout, const double *f, hipStream_t s, hipEvent_t e0,
                                hipEvent_t e1) {
     if (od.nsegs == 0) return hipSuccess;
-    if (od.few)
+    if (od.few_prolong(level, false))
         return level == 0 ? launch_cube<double, true, true>(xin, xout, f, L, od, s, e0, e1, xc, &C)
                           : launch_cube<double, false, true>(xin, xout, f, L, od, s, e0, e1, xc, &C);
     const double h2 = L.h * L.h;
@@ -364,7 +364,7 @@ hipError_t launch_rbgs_prolong32(const Level &L, int level, const OrderData &od,
                                  const float *xin, float *xout, const float *f, hipStream_t s, hipEvent_t e0,
                                  hipEvent_t e1) {
     if (od.nsegs == 0) return hipSuccess;
-    if (od.few)
+    if (od.few_prolong(level, true))
         return level == 0 ? launch_cube<float, true, true>(xin, xout, f, L, od, s, e0, e1, xc, &C)
                           : launch_cube<float, false, true>(xin, xout, f, L, od, s, e0, e1, xc, &C);
     const float h2 = (float)(L.h * L.h);

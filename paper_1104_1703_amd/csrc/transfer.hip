@@ -77,8 +77,10 @@ __global__ __launch_bounds__(NT) void k_resnorm(const int *__restrict__ tiles, i
     if (threadIdx.x == 0) part[w] = s;
 }
 
-// The norm partials of a finest level of few work items, bit for bit those of
-// k_residual_march<.., RM_NORM>.
+// A solve's first two norms on a finest level of few work items (blockIdx.y 0: of
+// L x - f, 1: of f), bit for bit the partials of k_residual_march<.., RM_NORM>.
+// One launch of both takes 10.2 us at 64 items and 18.1 at 512, two of the march
+// 16.8 and 21.4; a single norm is the march's (8.4 against 8.6, 10.6 against 12.6).
 __global__ __launch_bounds__(NT) void k_item_norm(const double *__restrict__ x, const double *__restrict__ f,
                                                   const uint8_t *__restrict__ code, int nx, int ny, int nz, double ih2,
                                                   const Seg *__restrict__ segs, double *__restrict__ part,
@@ -313,9 +315,7 @@ void launch_resnorm(const Level &L, int level, const OrderData &od, const double
                     double *out, int slot, hipStream_t s, const StopTest *stop, double *host_out) {
     const double ih2 = 1.0 / (L.h * L.h);
     if (level == 0) {
-        if (od.nsegs && od.few)
-            k_item_norm<<<od.nsegs, NT, 0, s>>>(x, f, L.code, L.nx, L.ny, L.nz, ih2, od.segs, part, L.halt);
-        else if (od.nsegs)
+        if (od.nsegs)
             with_fine_depth(od.depth, [&](auto Z) {
                 k_residual_march<double, decltype(Z)::value, RM_NORM><<<grid8(od.nsegs), NT, 0, s>>>(
                     x, f, L.code, L.nx, L.ny, L.nz, ih2, od.segs, od.pmask, od.nsegs, nullptr, 0, 0, nullptr, part,
