@@ -78,10 +78,12 @@ typedef struct {
                                  (cached in the file named by MG_TUNE_CACHE, if set); 0 = the
                                  defaults below (default 0).  Every choice gives the same
                                  iterates bit for bit; only the order in which the residual
-                                 norm's partial sums are added depends on it.  A level of few
-                                 work items (about 10^6 active cells or fewer) whose depth the
-                                 options below do not fix runs its passes over 8 x 8 x 8 cubes
-                                 instead, with the same iterates and norms bit for bit. */
+                                 norm's partial sums are added depends on it.  A level with at
+                                 most 1024 active tiles of 32 x 8 x 8 cells (so at most 2.1
+                                 million active cells) whose depth the options below do not fix
+                                 runs its passes over 8 x 8 x 8 cubes where those are the faster
+                                 form by measurement, with the same iterates and norms bit for
+                                 bit; with tune = 1 that is one more variant timed. */
     int32_t item_depth_fine;  /* planes per finest-level work item: 8, 16 or 32; 0 = default
                                  (16) or tuned.  A non-zero value is used as given. */
     int32_t item_depth_l1;    /* level 1: 2, 4 or 8; 0 = default (4) or tuned; 1 = plain passes
@@ -184,8 +186,9 @@ int64_t mg_level_active(const mg_hierarchy *H, int32_t level, int32_t order);
 
 /* Planes per smoother work item of level l in boundary order `order` (the
  * default, the option's or the tuned value; work items are 32 x 8 cell
- * columns), 1 when the option or the tuner picked whole 8 x 8 x 8 cubes for
- * its plain passes; -1 for an invalid level or order.  Levels run by the
+ * columns), 1 when a coarse level's plain passes run over whole 8 x 8 x 8 cubes;
+ * -1 for an invalid level or order.  On the finest level always the planes of its
+ * items, whose residual-norm partial sums they group.  Levels run by the
  * one-workgroup small-level kernel keep their lists but use none. */
 int32_t mg_level_item_depth(const mg_hierarchy *H, int32_t level, int32_t order);
 

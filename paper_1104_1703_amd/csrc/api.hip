@@ -306,13 +306,23 @@ int start_depth(const mg_options &o, int l) {
     return (f && f != DEPTH_CUBE) ? f : item_depth(l);
 }
 
-// The tuning cache: lines "<key> <depth>" in the file MG_TUNE_CACHE names.
+// Whether every pass of a level may run over cubes (OrderData::few): few work
+// items, and no option that fixes their shape.
+bool few_items(const mg_hierarchy *H, int l, const OrderData &od) {
+    return !H->opt.fuse_passes && !forced_depth(H->opt, l) && 4 * od.ntiles <= FEW_CUBES;
+}
+
+// The tuning cache: lines "<key> <depth>" in the file MG_TUNE_CACHE names; the
+// depth is DEPTH_FEW where the passes take cubes at the default's lines.  Levels
+// on which that is a candidate have keys of their own: an entry measured without
+// it is no answer there.
 std::string tune_key(const mg_hierarchy *H, int l, int order, bool f32) {
     const Level &L = H->lev[l];
+    const OrderData &od = L.od[l == 0 ? 2 : order];
     char b[160];
-    snprintf(b, sizeof b, "gfx950:%dx%dx%d:l%d:o%d:%s:a%lld%s", H->lev[0].nx, H->lev[0].ny, H->lev[0].nz, l, order,
-             f32 ? "fp32" : "fp64", (long long)L.od[l == 0 ? 2 : order].nact,
-             l == 0 && H->opt.fuse_restrict && !H->opt.fuse_passes ? ":res" : "");
+    snprintf(b, sizeof b, "gfx950:%dx%dx%d:l%d:o%d:%s:a%lld%s%s", H->lev[0].nx, H->lev[0].ny, H->lev[0].nz, l, order,
+             f32 ? "fp32" : "fp64", (long long)od.nact,
+             l == 0 && H->opt.fuse_restrict && !H->opt.fuse_passes ? ":res" : "", few_items(H, l, od) ? ":few" : "");
     return b;
 }
 
@@ -338,57 +348,62 @@ void tune_cache_put(const std::string &key, int depth) {
     fclose(fp);
 }
 
-// Average time of the work a cycle runs over the work items of od on
-// level l, with HIP events on the hierarchy's stream (best of three runs):
-// on coarse levels one smoother pass; on the finest level, which runs
-// several kernels over the same items, a plain pass, the pass with the
-// residual and its restriction (or a plain pass and the residual march with
-// the restriction) and the pass forming its input's norm (FP64) or the
-// update with the outer residual (mixed).  At creation every iterate and
-// right-hand side buffer holds zeros, which this work keeps; it costs the
-// same on any values.
+// Average time of a level's share of a cycle over the work items of od, with
+// HIP events on the hierarchy's stream (best of three runs): two smoothing
+// passes, the second with the residual and its restriction, the pass that
+// applies the prolongation, and a last one.  On the finest level the first also
+// forms its input's norm (FP64), or the update with the outer residual follows
+// the last (mixed); a level without a coarser one only smooths.  At creation
+// every iterate and right-hand side buffer holds zeros, which this work keeps;
+// it costs the same on any values.
 float time_pass(mg_hierarchy *H, int l, int order, const OrderData &od, bool f32) {
     Level &L = H->lev[l];
-    const bool coarse = H->nlev[2] > 1;
-    // a coarse level with a coarser one restricts after every other pass
-    // (on cubes inside the pass itself)
-    const bool restricts = l > 0 && l + 1 < H->nlev[order];
-    auto pass = [&](int p) {
-        if (restricts && (p & 1)) {
-            Level &C = H->lev[l + 1];
-            if (od.cube) {
-                if (f32) launch_rbgs_restrict32(L, C, order, od, L.x32[p & 1], L.x32[(p & 1) ^ 1], L.f32, C.f32,
-                                                H->stream);
-                else launch_rbgs_restrict(L, C, order, od, L.x[p & 1], L.x[(p & 1) ^ 1], L.f, C.f, H->stream);
-            } else if (f32) {
-                HIPCHK(launch_rbgs32(L, l, od, L.x32[p & 1], L.x32[(p & 1) ^ 1], L.f32, H->stream));
-                launch_restrict32(L, C, l, order, L.x32[(p & 1) ^ 1], L.f32, C.f32, H->stream);
-            } else {
-                HIPCHK(launch_rbgs(L, l, od, L.x[p & 1], L.x[(p & 1) ^ 1], L.f, H->stream));
-                launch_restrict(L, C, l, order, L.x[(p & 1) ^ 1], L.f, C.f, H->stream);
-            }
-            return;
-        }
-        if (l == 0 && coarse && od.pmask3 && (p & 1)) {  // the pass that also restricts
-            Level &C = H->lev[1];
-            if (f32) HIPCHK(launch_rbgs_res_fine32(L, C, 2, od, L.x32[1], L.x32[0], L.f32, C.f32, H->stream));
-            else HIPCHK(launch_rbgs_res_fine(L, C, 2, od, L.x[1], L.x[0], L.f, C.f, H->stream));
-        } else if (f32) HIPCHK(launch_rbgs32(L, l, od, L.x32[p & 1], L.x32[(p & 1) ^ 1], L.f32, H->stream));
-        else HIPCHK(launch_rbgs(L, l, od, L.x[p & 1], L.x[(p & 1) ^ 1], L.f, H->stream));
-        if (l != 0 || (p & 1) == 0) return;
-        if (f32) {
-            if (coarse && !od.pmask3) launch_restrict32(L, H->lev[1], 0, 2, L.x32[0], L.f32, H->lev[1].f32, H->stream);
-            launch_axpy_resnorm32(L, od, L.x[0], L.x32[0], L.x[1], L.f, L.f32, H->part, H->norm_dev, 0, H->stream,
-                                  nullptr);
-        } else {
-            if (coarse && !od.pmask3) launch_restrict(L, H->lev[1], 0, 2, L.x[0], L.f, H->lev[1].f, H->stream);
-            HIPCHK(launch_rbgs_norm(L, od, L.x[0], L.x[1], L.f, H->part, H->stream));
+    const bool coarse = l + 1 < H->nlev[order];
+    const auto smooth = [&](int a) {
+        if (f32) HIPCHK(launch_rbgs32(L, l, od, L.x32[a], L.x32[a ^ 1], L.f32, H->stream));
+        else HIPCHK(launch_rbgs(L, l, od, L.x[a], L.x[a ^ 1], L.f, H->stream));
+    };
+    const auto pass = [&](int p) {
+        const int a = p & 1;
+        Level &C = H->lev[coarse ? l + 1 : l];  // (used only with `coarse`)
+        switch (p & 3) {
+            case 0:
+                if (l == 0 && !f32) HIPCHK(launch_rbgs_norm(L, od, L.x[a], L.x[a ^ 1], L.f, H->part, H->stream));
+                else smooth(a);
+                return;
+            case 1:
+                if (coarse && l == 0 && od.pmask3) {
+                    if (f32)
+                        HIPCHK(launch_rbgs_res_fine32(L, C, order, od, L.x32[a], L.x32[a ^ 1], L.f32, C.f32,
+                                                      H->stream));
+                    else HIPCHK(launch_rbgs_res_fine(L, C, order, od, L.x[a], L.x[a ^ 1], L.f, C.f, H->stream));
+                } else if (coarse && l > 0 && od.cubes()) {
+                    if (f32) launch_rbgs_restrict32(L, C, order, od, L.x32[a], L.x32[a ^ 1], L.f32, C.f32, H->stream);
+                    else launch_rbgs_restrict(L, C, order, od, L.x[a], L.x[a ^ 1], L.f, C.f, H->stream);
+                } else {
+                    smooth(a);
+                    if (!coarse) return;
+                    if (f32) launch_restrict32(L, C, l, order, L.x32[a ^ 1], L.f32, C.f32, H->stream);
+                    else launch_restrict(L, C, l, order, L.x[a ^ 1], L.f, C.f, H->stream);
+                }
+                return;
+            case 2:
+                if (!coarse) smooth(a);
+                else if (f32)
+                    HIPCHK(launch_rbgs_prolong32(L, l, od, C, C.x32[0], L.x32[a], L.x32[a ^ 1], L.f32, H->stream));
+                else HIPCHK(launch_rbgs_prolong(L, l, od, C, C.x[0], L.x[a], L.x[a ^ 1], L.f, H->stream));
+                return;
+            default:
+                smooth(a);
+                if (l == 0 && f32)
+                    launch_axpy_resnorm32(L, od, L.x[0], L.x32[0], L.x[1], L.f, L.f32, H->part, H->norm_dev, 0,
+                                          H->stream, nullptr);
         }
     };
     // the restriction march reads the finest lists from the level itself
     const OrderData saved = L.od[2];
     if (l == 0) L.od[2] = od;
-    const int n = l == 0 ? 10 : 20;
+    const int n = l == 0 ? 12 : 20;
     for (int p = 0; p < 4; p++) pass(p);
     float best = 1e30f;
     for (int rep = 0; rep < 3; rep++) {
@@ -404,11 +419,11 @@ float time_pass(mg_hierarchy *H, int l, int order, const OrderData &od, bool f32
     return best / n;
 }
 
-// Picks the planes per work item of every level and order that its
-// smoother passes run fastest with (each candidate timed on this
-// hierarchy), unless the options fix it; levels run by the one-workgroup
-// kernel take no work items.  The precision timed is the one the level's
-// passes run in (FP32 for a mixed-precision hierarchy).
+// Picks the planes per work item of every level and order that its passes run
+// fastest with (each candidate timed on this hierarchy), or cubes in their
+// place, unless the options fix it; levels run by the one-workgroup kernel take
+// no work items.  The precision timed is the one the level's passes run in (FP32
+// for a mixed-precision hierarchy).
 void tune_depths(mg_hierarchy *H) {
     const bool f32 = H->opt.precision == MG_MIXED;
     for (int l = 0; l < std::max(H->nlev[1], H->nlev[2]); l++)
@@ -419,38 +434,47 @@ void tune_depths(mg_hierarchy *H) {
             OrderData &od = H->lev[l].od[o];
             if (od.nsegs == 0) continue;
             const std::string key = tune_key(H, l, o, f32);
+            const bool few = few_items(H, l, od), cube = l > 0 && !H->opt.fuse_passes;
             int best = tune_cache_get(key);
-            if (!depth_supported(l, best) && !(l > 0 && best == DEPTH_CUBE && !H->opt.fuse_passes)) {
+            if (!depth_supported(l, best) && !(cube && best == DEPTH_CUBE) && !(few && best == DEPTH_FEW)) {
                 const int cand0[3] = {8, 16, 32}, cand1[3] = {2, 4, 8};
                 const int *cand = l == 0 ? cand0 : cand1;
-                float tbest = time_pass(H, l, o, od, f32);
-                best = od.depth;
-                for (int c = 0; c < 3; c++) {
-                    if (cand[c] == od.depth) continue;
-                    OrderData t = od;
-                    build_lists(H, l, o, cand[c], t);
+                float tbest = 1e30f;
+                const auto time = [&](const OrderData &t, int depth) {
                     const float tc = time_pass(H, l, o, t, f32);
-                    HIPCHK(hipStreamSynchronize(H->stream));
                     if (tc < tbest) {
                         tbest = tc;
-                        best = cand[c];
+                        best = depth;
                     }
-                    free_lists(H, t);
-                }
-                if (l > 0 && !H->opt.fuse_passes) {  // whole 8^3 cubes instead of a march
-                    OrderData t = od;
+                };
+                OrderData t = od;  // the default's lists
+                t.few = few;
+                time(t, few ? DEPTH_FEW : od.depth);
+                t.few = false;
+                if (few) time(t, od.depth);
+                if (cube) {
                     t.cube = true;
-                    if (time_pass(H, l, o, t, f32) < tbest) best = DEPTH_CUBE;
+                    time(t, DEPTH_CUBE);
+                }
+                for (int c = 0; c < 3; c++) {
+                    if (cand[c] == od.depth) continue;
+                    OrderData u = od;
+                    u.few = false;
+                    build_lists(H, l, o, cand[c], u);
+                    time(u, cand[c]);
+                    HIPCHK(hipStreamSynchronize(H->stream));
+                    free_lists(H, u);
                 }
                 tune_cache_put(key, best);
             }
-            const int march = best == DEPTH_CUBE ? od.depth : best;
+            const int march = best == DEPTH_CUBE || best == DEPTH_FEW ? od.depth : best;
             if (march != od.depth) {
                 HIPCHK(hipStreamSynchronize(H->stream));
                 free_lists(H, od);
                 build_lists(H, l, o, march, od);
             }
             od.cube = best == DEPTH_CUBE;
+            od.few = best == DEPTH_FEW;
         }
     H->lev[0].od[1] = H->lev[0].od[2];
 }
@@ -650,14 +674,11 @@ void create(mg_hierarchy *H, const int8_t *mask, int nx, int ny, int nz, double 
     for (int q = 0; q < 2; q++)
         HIPCHK(hipEventCreateWithFlags(&H->evn[q], hipEventDisableTiming | hipEventDisableSystemFence));
     HIPCHK(hipStreamSynchronize(s));
-    if (H->opt.tune) tune_depths(H);
-    // levels of few work items run every pass over cubes, unless the options
-    // fix their shape
+    // levels of few work items take cubes, unless the options fix their shape or
+    // the tuner finds a march faster
     for (int o = 1; o <= 2; o++)
-        for (int l = 0; l < H->nlev[o]; l++) {
-            OrderData &od = lev[l].od[o];
-            od.few = !H->opt.fuse_passes && !forced_depth(H->opt, l) && 4 * od.ntiles <= FEW_CUBES;
-        }
+        for (int l = 0; l < H->nlev[o]; l++) lev[l].od[o].few = few_items(H, l, lev[l].od[o]);
+    if (H->opt.tune) tune_depths(H);
     HIPCHK(hipStreamSynchronize(s));
     H->coarse_order_state = 0;
 }
@@ -1468,7 +1489,8 @@ mg_status mg_level_dims(const mg_hierarchy *H, int32_t level, int32_t *dims_out)
 int32_t mg_level_item_depth(const mg_hierarchy *H, int32_t level, int32_t order) {
     if (!H || level < 0 || (order != 1 && order != 2) || level >= H->nlev[order]) return -1;
     const OrderData &od = H->lev[level].od[level == 0 ? 2 : order];
-    return od.cube ? DEPTH_CUBE : od.depth;
+    const bool small = H->ls[order] >= 0 && level >= H->ls[order];
+    return level > 0 && od.cubes() && !small ? DEPTH_CUBE : od.depth;
 }
 
 int64_t mg_level_active(const mg_hierarchy *H, int32_t level, int32_t order) {
