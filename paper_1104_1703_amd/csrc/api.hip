@@ -647,7 +647,7 @@ void create(mg_hierarchy *H, const int8_t *mask, int nx, int ny, int nz, double 
         const int last = H->nlev[o] - 1;
         if (H->ls[o] < 0 && last >= 1 && small_lds_bytes(H, o, last, false) <= (size_t)small_lim) H->ls[o] = last;
         // a small deepest level below others is solved by its relaxation's matrix
-        if (H->ls[o] >= 0 && H->ls[o] < last && deep_matrix_fits(lev[last])) {
+        if (H->ls[o] >= 0 && small_direct(H, o, H->ls[o])) {
             OrderData &od = lev[last].od[o];
             A.want(od.deep, lev[last].n * lev[last].n);
             if (mixed) A.want(od.deep32, lev[last].n * lev[last].n);

@@ -89,7 +89,10 @@ void launch_impl(const mg_hierarchy *H, int order, int ls, bool zero_start, cons
 
 }  // namespace
 
-bool deep_matrix_fits(const Level &L) { return L.n <= (size_t)DEEP_MAX; }
+bool small_direct(const mg_hierarchy *H, int order, int ls) {
+    const int last = H->nlev[order] - 1;
+    return deep_product(last - ls + 1, H->lev[last].n, (long long)H->opt.n_cycles * H->opt.n_coarse_sweeps);
+}
 
 void launch_deep_matrix(const Level &L, const OrderData &od, int passes, hipStream_t s) {
     Lv<double> v{};
@@ -132,7 +135,7 @@ struct SmallDims {
             const Level &L = H->lev[ls + q];
             nx[q] = L.nx, ny[q] = L.ny, nz[q] = L.nz;
         }
-        direct = last > ls && deep_matrix_fits(H->lev[last]);
+        direct = small_direct(H, order, ls);
     }
 };
 

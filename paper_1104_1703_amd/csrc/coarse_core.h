@@ -3,6 +3,7 @@
 #pragma once
 
 #include "mg_core.h"
+#include "small_rule.h"
 #include "smooth_core.h"
 
 namespace mg {
@@ -241,19 +242,15 @@ __device__ void smooth(const Lv<T> &L, int passes) {
 // The deepest level's whole share of a cycle as one matrix product.  Its
 // n_cycles x n_coarse passes start from zero and are linear in f, so they are
 // x = M f with M formed once per hierarchy (column j: the passes applied to the
-// unit right-hand side of cell j, k_deep_matrix); 64 half-sweeps of a 4^3 level
-// take 9 us, each an LDS round trip, the product about 1 us.  16 lanes share a
-// row, lane q summing columns q, q + 16, ... in order, then an exchange tree:
-// the same sums for any thread count.  A cell whose right-hand side does not
-// reach a row (another part of the domain, or out of the passes' reach) has a
-// zero there and is left out, so that an infinity or a NaN of its stays with the
-// cells that the passes would carry it to.  DEEP_MAX cells: a matrix of 512 KB, which
-// one workgroup reads in less time than the passes take.
-constexpr int DEEP_MAX = 256;
-
+// unit right-hand side of cell j, k_deep_matrix).  16 lanes share a row, lane q
+// summing columns q, q + 16, ... in order, then an exchange tree: the same sums
+// for any thread count.  A cell whose right-hand side does not reach a row
+// (another part of the domain, or out of the passes' reach) has a zero there and
+// is left out, so that an infinity or a NaN of its stays with the cells that the
+// passes would carry it to.  Taken where deep_product (small_rule.h) says so.
 template <typename T>
 __device__ __forceinline__ T deep_term(T m, T f, T s) {
-    return m != T(0) ? fma_t<T>(m, f, s) : s;
+    return fma_t<T>(m, m != T(0) ? f : T(0), s);  // (selected ahead of the chain of sums)
 }
 
 template <typename T, int NTH>
@@ -342,8 +339,8 @@ __device__ void prolong_from(const Lv<T> &L, const Lv<T> &C) {
 // 256^3, against 25 and 29 us in the general path (30 and 32 us with the
 // deepest level relaxed); in a W-cycle 17 against 57 us; 17 x 9 x 13 relaxed 32
 // times 22 against 25 us, 6 x 32 x 32 in a batch 35 against 99 us.  The general
-// path stays for larger boxes, more than three levels and blocks of fewer
-// threads.
+// path stays for four levels and more, for single levels of more than 8192 cells
+// and for blocks of fewer threads.
 struct FastLds {  // offsets in elements
     int ra, xb, rb, xd, fd, end;
 };

@@ -284,7 +284,8 @@ size_t small_lds_bytes(const mg_hierarchy *H, int order, int ls, bool f32);
 // Whether that call takes the register path (coarse_core.h small_fast).
 bool small_fast_levels(const mg_hierarchy *H, int order, int ls);
 void launch_reciprocals(const Level &L, const OrderData &od, hipStream_t s);
-bool deep_matrix_fits(const Level &L);
+// Whether the call on the levels ls .. deepest takes the deepest as a matrix.
+bool small_direct(const mg_hierarchy *H, int order, int ls);
 // Forms od.deep (and od.deep32, if allocated) of a deepest level: `passes`
 // red-black passes from zero as a matrix.
 void launch_deep_matrix(const Level &L, const OrderData &od, int passes, hipStream_t s);
