@@ -49,8 +49,8 @@ def test_four_levels_match_oracle(mg, shape, min_dim, levels, opts):
                 assert np.abs(x.cpu().numpy() - x_o)[act].max() <= 1e-11 * np.abs(x_o[act]).max()
 
 
-# two levels, 125 and 216 cells in the deepest: a pass for every six cells and one more
-@pytest.mark.parametrize("shape,sweeps", [((20, 20, 20), 20), ((20, 20, 20), 21), ((24, 24, 24), 36), ((24, 24, 24), 37)])
+# two levels, 125 and 216 cells in the deepest: a pass for every five cells and one more
+@pytest.mark.parametrize("shape,sweeps", [((20, 20, 20), 25), ((20, 20, 20), 26), ((24, 24, 24), 43), ((24, 24, 24), 44)])
 def test_line_of_the_matrix_matches_oracle(mg, shape, sweeps):
     print("line", shape, sweeps, flush=True)
     p, (mask, rho, b) = problem(shape)
