@@ -179,11 +179,15 @@ __global__ __launch_bounds__(NTH, conv_blocks(CK, NTC)) void k_conv_tile(const b
         // Whole chunks of 32 channels: B fragments of a (dz, dy) row of taps are
         // fetched a row ahead, the first before the staging (AHEAD)
         const bool full = CK == 32 && (!HALF || cin - c0 >= 32);
-        unsigned wl[NTC];  // byte offsets within a tap's weights (K entries c0 + 8 grp .. + 7)
+        // byte offsets within a tap's weights (K entries c0 + 8 grp .. + 7; past the
+        // last channel, where the voxels are zeros, the last ones again: what
+        // follows them may be no number, or not be there at all)
+        unsigned wl[NTC];
+        const int cl = min(c0 + grp * 8, cin - 8);
 #pragma unroll
         for (int nt = 0; nt < NTC; nt++)
             wl[nt] = frag ? (unsigned)((((co_base >> 4) + nt) * (cin >> 5) + (c0 >> 5)) * 1024 + lane * 16)
-                          : (unsigned)(((co_base + nt * 16 + row) * cin + c0 + grp * 8) * 2);
+                          : (unsigned)(((co_base + nt * 16 + row) * cin + cl) * 2);
         bf16x8 bfr[AHEAD ? 2 : 1][3][NTC];
         const auto fetch = [&](int r) {
 #pragma unroll
