@@ -83,7 +83,8 @@ typedef struct {
                                  million active cells) whose depth the options below do not fix
                                  runs its passes over 8 x 8 x 8 cubes where those are the faster
                                  form by measurement, with the same iterates and norms bit for
-                                 bit; with tune = 1 that is one more variant timed. */
+                                 bit; with tune = 1 that is one more variant timed (on the
+                                 finest level with items of each depth). */
     int32_t item_depth_fine;  /* planes per finest-level work item: 8, 16 or 32; 0 = default
                                  (16) or tuned.  A non-zero value is used as given. */
     int32_t item_depth_l1;    /* level 1: 2, 4 or 8; 0 = default (4) or tuned; 1 = plain passes

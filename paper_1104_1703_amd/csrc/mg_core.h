@@ -55,9 +55,6 @@ constexpr int FEW_CUBES_PROLONG1 = 1792, FEW_CUBES_PROLONG1_32 = 1152;
 // Coarse-level option value selecting 8^3 cube items for plain passes (the
 // passes that apply the prolongation keep the default march).
 constexpr int DEPTH_CUBE = 1;
-// The tuner's value for a level of few work items whose passes take cubes at the
-// lines above.
-constexpr int DEPTH_FEW = -1;
 // Calls f(std::integral_constant<int, D>()) with D the finest-level item depth
 // in use (the kernel instance to launch).
 template <typename F>

@@ -25,7 +25,9 @@ def level(key):
 
 # value of the cache per level (finest, 1, 2 and coarser) and the depths reported
 CHOICES = {
-    "few": ((-1, -1, -1), (16, 1, 1)),
+    "few": ((-16, -4, -2), (16, 1, 1)),
+    "few8": ((-8, -4, -2), (8, 1, 1)),
+    "few32-march": ((-32, 2, -8), (32, 2, 1)),
     "march32-8-8": ((32, 8, 8), (32, 8, 8)),
     "march8-2-4": ((8, 2, 4), (8, 2, 4)),
     "cube": ((16, 1, 1), (16, 1, 1)),
