@@ -3,6 +3,7 @@
 #pragma once
 
 #include <algorithm>
+#include <cmath>
 
 namespace mg {
 namespace nn {
@@ -52,25 +53,27 @@ inline MarchPlan march_plan(int n, int D, int H, int W, int cin, int cout) {
 }
 
 // Whether the kernel per tap takes the layer.  Estimated times in us, fitted to
-// both kernels at 1032 shapes (1 to 512 samples of 1 to 64 voxels an edge, flat
-// ones among them, 16 to 192 channels; median error 10%): the kernel per tap
-// pays per voxel and channel tile and 2.3 ps per atomic of its blocks; the
-// march 30 ns for each block that adds to the same weights, 26 ns for each
-// block's atomics and 0.84 us per plane of a round of 256 blocks.  The line at
-// 1.1 times: over these shapes the choice takes 1.007 times the faster kernel's
-// time (geometric mean).  The march also leaves to the other kernel what its
-// grid and its 32-bit offsets cannot hold.
+// both kernels at 1487 shapes (1 to 512 samples of 1 to 64 voxels an edge, flat
+// and ragged ones among them, 16 to 256 channels; median errors 8 and 5%): the
+// kernel per tap takes a block's steps of 32 voxels one after the other, then
+// pays per voxel and channel tile and 2.6 ps per atomic of its blocks; the march
+// takes 41 ns for each block that adds to the same weights, and per plane 0.61 us
+// for a round of 256 blocks and 0.9 ns for each block.
+// The line at 1.05 times: over these shapes the choice takes 1.005 times the
+// faster kernel's time (geometric mean; 26 shapes more than 1.1 times, 9 more
+// than 1.2).  The march also leaves to the other kernel what its grid and its
+// 32-bit offsets cannot hold.
 inline bool per_tap(const MarchPlan &m, int cin, int cout, long long V, int H, int W) {
     const long long blocks = m.cols * m.nzc * m.tiles;
     if (m.tiles > 65535 || m.cols * m.nzc * BW_NT >= (1LL << 32)) return true;
     if ((long long)H * W * (std::max(cin, cout) / 8) >= (1LL << 31)) return true;
     const int groups = (cout + 63) / 64;
-    const double chunks = (double)((V + tap_chunk(V, groups) - 1) / tap_chunk(V, groups));
-    const double tap = 3.0 + 1e-3 * (double)V * groups * (0.27 + 0.24 * (cin / 16)) +
-                       2.3e-6 * chunks * 27 * groups * std::min(cout, 64) * cin;
-    const double march = 3.4 + 0.030 * (double)(m.cols * m.nzc) + 0.0265 * (double)blocks +
-                         0.84 * (double)((blocks + 255) / 256) * (m.zc + 2);
-    return tap < 1.1 * march;
+    const double chunk = (double)tap_chunk(V, groups), chunks = std::ceil((double)V / chunk);
+    const double tap = 2.1 + chunk / BW_KV * (0.72 + 0.148 * (cin / 16)) + 1.83e-4 * (double)V * groups * (cin / 16) +
+                       2.6e-6 * chunks * 27 * groups * std::min(cout, 64) * cin;
+    const double march = 0.1 + 0.041 * (double)(m.cols * m.nzc) +
+                         (m.zc + 11) * (0.61 * (double)((blocks + 255) / 256) + 0.0009 * (double)blocks);
+    return tap < 1.05 * march;
 }
 
 }  // namespace nn

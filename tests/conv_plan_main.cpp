@@ -21,7 +21,14 @@ static const Row rows[] = {
     {512, 1, 1, 64, 192, 64, 158.4, 4052.4},
     {4, 64, 1, 64, 16, 16, 10.7, 23.3},
     {1, 20, 20, 20, 16, 16, 7.8, 12.3},
-    // the network's maps and larger ones
+    // ragged and narrow maps of many channels
+    {32, 18, 5, 21, 96, 48, 146.8, 112.1},
+    {1, 9, 4, 19, 96, 64, 14.4, 10.9},
+    {2, 11, 3, 16, 32, 128, 20.5, 10.4},
+    {1, 4, 7, 19, 192, 32, 15.2, 9.1},
+    {4, 10, 10, 10, 16, 256, 19.8, 12.4},
+    {4, 17, 24, 3, 48, 192, 28.8, 44.2},
+    {4, 20, 14, 17, 48, 48, 29.6, 14.0},    // the network's maps and larger ones
     {8, 64, 64, 64, 16, 16, 1105.8, 47.1},
     {1, 64, 64, 64, 16, 16, 141.5, 24.3},
     {16, 16, 16, 16, 192, 64, 331.6, 70.8},
